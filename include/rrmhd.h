@@ -135,7 +135,11 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b);
 /* Advance n >= 0 time steps.  One step is tasks 1-6 of the algorithm at every
  * node: moments, equilibria, non-equilibrium Hermite coefficients with the
  * recursive third/fourth orders, regularised reconstruction, collision and
- * streaming (done as a pull, fused into one kernel).  Asynchronous. */
+ * streaming (done as a pull, fused into one kernel).  A two-buffer handle
+ * with its default launch takes two to five steps per pass over the state
+ * where the grid has a form for it (not with stochastic rounding, the
+ * closure or the equilibrium ablation); the state after n steps is bit for
+ * bit that of n passes of one step.  Asynchronous. */
 int rrmhd_step(rrmhd *h, int64_t n);
 
 /* Pre-collision macroscopic fields of the current state (task 1): rho
@@ -219,8 +223,9 @@ int rrmhd_load_state(rrmhd *h, const void *src, int64_t bytes,
 int rrmhd_save(rrmhd *h, const char *path);
 int rrmhd_load(rrmhd *h, const char *path);
 
-/* Launch shape of the step kernel (the tuning knob of the autotuner; the
- * default is picked from the grid).  bx x by threads per workgroup
+/* Launch shape of the one-step kernel (the tuning knob of the autotuner; the
+ * default is picked from the grid).  A handle whose shape was set takes one
+ * step per pass from then on.  bx x by threads per workgroup
  * (bx * by <= 256, bx >= 1, by >= 1), ry consecutive rows per thread (>= 1),
  * xcd = 1 renumbers workgroups so each XCD gets one contiguous run of tiles,
  * xcd = 2 so each XCD gets 8 neighbouring tiles out of every 64; nt bit 0
@@ -251,11 +256,11 @@ int rrmhd_set_stream(rrmhd *h, void *hip_stream);
  * default) launches every step directly.  EINVAL for chunk < 0. */
 int rrmhd_set_graph_chunk(rrmhd *h, int chunk);
 
-/* Debug aid: with on != 0, every later step first fills the buffer it
- * writes with a NaN pattern (all planes, padding included), so a stored
+/* Debug aid: with on != 0, every later pass over the state (one step or
+ * several) first fills the buffer it writes with a NaN pattern (all planes, padding included), so a stored
  * value that a step fails to write shows up as NaN in the moments and as
  * RRMHD_ENONFINITE from the diagnostics.  Results are otherwise unchanged
- * (a step reads only the other buffer); each step costs one more write of
+ * (a pass reads only the other buffer); each pass costs one more write of
  * the whole buffer.  For the callers that check kernel coverage (tests);
  * EINVAL for a single-buffer handle, whose steps read what they write. */
 int rrmhd_set_debug_poison(rrmhd *h, int on);

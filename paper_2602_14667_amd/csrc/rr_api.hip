@@ -94,6 +94,10 @@ struct rrmhd {
   int phase = 0;         // in-place: 0 pull layout, 1 swapped layout
   bool ready = false;
   rr::LaunchShape shape{};
+  // several steps per launch where multi_plan has a form for them; off once a
+  // launch shape was chosen (set_launch, RRMHD_TILE), which is for the
+  // one-step kernels
+  bool multi = true;
   void *diag_work = nullptr;
   void *fields_work = nullptr;  // 2 nx ny doubles for the j_z / w_z fields
   double *diag_out = nullptr;   // device, 8 doubles
@@ -108,6 +112,7 @@ struct rrmhd {
   int graph_chunk = 0;
   bool poison = false;  // debug: NaN-fill the destination buffer before each step
   hipGraphExec_t graph[2] = {nullptr, nullptr};
+  int graph_flip[2] = {0, 0};  // whether a replay of it ends in the other buffer / phase
   hipStream_t own = nullptr;
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
 };
@@ -129,6 +134,33 @@ static hipError_t poison_buffer(const rrmhd *h, void *buf, hipStream_t st) {
 static void free_graphs(rrmhd *h) {
   for (auto &g : h->graph)
     if (g) (void)hipGraphExecDestroy(g), g = nullptr;
+}
+
+// The default launch shape, several steps per launch where a form applies.
+static void default_launch(rrmhd *h) {
+  const rr::Domain &D = h->D;
+  h->multi = true;
+  h->shape = rr::default_shape(D);
+  if (h->inplace) {
+    // measured best for the alternating single-buffer steps at 8192^2, with
+    // eight neighbouring tiles per XCD and non-temporal stores: FP16 storage
+    // (round to nearest) on row-interleaved planes 64 x 2 threads with two
+    // nodes per thread; otherwise one node per thread and one row per
+    // workgroup, 128 wide (FP16 storage, or FP32 on row-interleaved planes)
+    // or 64 wide (FP32 on planes of [ny][nx])
+    const bool rows_wide = D.row != D.nx && D.nx >= 512;
+    h->shape.ry = 1;
+    h->shape.xcd = 2;
+    if (rows_wide && h->elem == 2 && D.nx % 2 == 0 && !D.sr) {
+      h->shape.bx = 64;
+      h->shape.by = 2;
+      h->shape.nt = 5;
+    } else {
+      h->shape.bx = (h->elem == 2 || rows_wide) ? 128 : 64;
+      h->shape.by = 1;
+      h->shape.nt = 1;
+    }
+  }
 }
 
 extern "C" {
@@ -253,27 +285,7 @@ int rrmhd_create(const rrmhd_grid *grid, double tau_f, double tau_m,
   D.sr = kind == RRMHD_STORE_F16_SR;
   D.inv_s = 1.0f / D.s;
   D.elem = (int)h->elem;
-  h->shape = rr::default_shape(D);
-  if (h->inplace) {
-    // measured best for the alternating single-buffer steps at 8192^2, with
-    // eight neighbouring tiles per XCD and non-temporal stores: FP16 storage
-    // (round to nearest) on row-interleaved planes 64 x 2 threads with two
-    // nodes per thread; otherwise one node per thread and one row per
-    // workgroup, 128 wide (FP16 storage, or FP32 on row-interleaved planes)
-    // or 64 wide (FP32 on planes of [ny][nx])
-    const bool rows_wide = D.row != D.nx && D.nx >= 512;
-    h->shape.ry = 1;
-    h->shape.xcd = 2;
-    if (rows_wide && h->elem == 2 && D.nx % 2 == 0 && !D.sr) {
-      h->shape.bx = 64;
-      h->shape.by = 2;
-      h->shape.nt = 5;
-    } else {
-      h->shape.bx = (h->elem == 2 || rows_wide) ? 128 : 64;
-      h->shape.by = 1;
-      h->shape.nt = 1;
-    }
-  }
+  default_launch(h);
 
   // environment overrides of the launch shape ("BXxBY" or "BXxBYxRY") and of
   // the debug poison mode (two-buffer handles), for runs driven from outside
@@ -285,6 +297,7 @@ int rrmhd_create(const rrmhd_grid *grid, double tau_f, double tau_m,
       h->shape.by = by;
       h->shape.ry = ry;
       h->shape.nt &= 1;  // a tile given this way is for the one-node update
+      h->multi = false;
     }
   }
   if (const char *e = std::getenv("RRMHD_DEBUG_POISON"))
@@ -323,6 +336,7 @@ int rrmhd_set_launch(rrmhd *h, int bx, int by, int ry, int xcd, int nt) {
   h->shape.ry = ry;
   h->shape.xcd = (xcd >= 0 && xcd <= 2) ? xcd : 0;
   h->shape.nt = nt & 15;
+  h->multi = false;
   return RRMHD_OK;
 }
 
@@ -363,7 +377,11 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b) {
 }
 
 static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
-  for (int64_t k = 0; k < n; ++k) {
+  const bool multi = h->multi && !h->inplace && !h->closure_on;
+  while (n > 0) {
+    rr::MultiPlan M{};
+    if (multi) M = rr::multi_plan(h->D, n);
+    int64_t taken = 1;
     // random bits of the stochastic-rounding codec: keyed by the step count
     h->D.sr_key = rr::mix32((uint32_t)h->steps * 0x27d4eb2fu + 0x165667b1u);
     if (h->inplace) {
@@ -371,16 +389,21 @@ static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
       h->phase ^= 1;
     } else {
       if (h->poison) HIP_OR_RETURN(poison_buffer(h, h->buf[h->cur ^ 1], st));
-      if (h->closure_on)
+      if (h->closure_on) {
         HIP_OR_RETURN(rr::launch_step_closure(h->storage, h->D, (const rr::MlpDev *)h->mlp,
                                               h->buf[h->cur], h->buf[h->cur ^ 1],
                                               h->closure_grid, st));
-      else
+      } else if (M.steps > 1) {
+        HIP_OR_RETURN(rr::launch_multi(M, h->storage, h->D, h->buf[h->cur], h->buf[h->cur ^ 1], st));
+        taken = M.steps;
+      } else {
         HIP_OR_RETURN(rr::launch_step(h->storage, h->D, h->buf[h->cur], h->buf[h->cur ^ 1],
                                       h->shape, st));
+      }
       h->cur ^= 1;
     }
-    h->steps++;
+    h->steps += taken;
+    n -= taken;
   }
   return RRMHD_OK;
 }
@@ -403,6 +426,7 @@ int rrmhd_step(rrmhd *h, int64_t n) {
       HIP_OR_RETURN(hipStreamBeginCapture(h->own, hipStreamCaptureModeThreadLocal));
       int rc = plain_steps(h, chunk, h->own);
       hipError_t ee = hipStreamEndCapture(h->own, &graph);
+      h->graph_flip[state] = h->inplace ? h->phase ^ p0 : h->cur ^ c0;
       h->cur = c0;  // the capture recorded the launches; nothing ran yet
       h->phase = p0;
       h->steps = s0;
@@ -416,10 +440,8 @@ int rrmhd_step(rrmhd *h, int64_t n) {
       if (ei != hipSuccess) return dev_err(ei, "hipGraphInstantiate");
     }
     HIP_OR_RETURN(hipGraphLaunch(g, h->own));
-    if (chunk & 1) {
-      h->cur ^= h->inplace ? 0 : 1;
-      h->phase ^= h->inplace ? 1 : 0;
-    }
+    h->cur ^= h->inplace ? 0 : h->graph_flip[state];
+    h->phase ^= h->inplace ? h->graph_flip[state] : 0;
     h->steps += chunk;
     left -= chunk;
   }
@@ -797,6 +819,11 @@ int rr_handle_info(const rrmhd *h, int *nx, int *ny, int *storage, hipStream_t *
 int rr_handle_walls(const rrmhd *h) { return h && h->D.walls ? 1 : 0; }
 
 int rr_handle_inplace(const rrmhd *h) { return h && h->inplace ? 1 : 0; }
+
+void rr_handle_default_launch(rrmhd *h) {
+  free_graphs(h);
+  default_launch(h);
+}
 
 int rr_handle_rows(const rrmhd *h) { return h && h->D.row != h->D.nx ? 1 : 0; }
 

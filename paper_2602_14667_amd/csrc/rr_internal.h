@@ -18,6 +18,8 @@ RR_HIDDEN void rr_handle_set_ready(rrmhd *h, int ready);
 RR_HIDDEN int rr_handle_walls(const rrmhd *h);
 // 1 when the handle streams in place in one population buffer
 RR_HIDDEN int rr_handle_inplace(const rrmhd *h);
+// the default launch shape again, with several steps per launch
+RR_HIDDEN void rr_handle_default_launch(rrmhd *h);
 // 1 when the handle keeps its planes row-interleaved
 RR_HIDDEN int rr_handle_rows(const rrmhd *h);
 }

@@ -38,6 +38,18 @@ struct LaunchShape {
 
 hipError_t launch_step(int storage, const Domain &D, const void *src, void *dst,
                        const LaunchShape &L, hipStream_t st);
+// Several steps in one pass (rr_multi.h).  steps = 0: none applies.
+struct MultiPlan {
+  int steps;  // steps per pass, 2 .. kMultiSteps
+  int tile;   // 0: marching strips; else the side of an LDS tile (16, 24, 32)
+  int wx, groups_x, out, rows;  // marching: windows per workgroup, workgroups
+                                // per row, nodes per window, rows per strip
+};
+constexpr int kMultiSteps = 5;
+MultiPlan multi_plan(const Domain &D, int64_t n);  // for n >= 2 remaining steps
+hipError_t launch_multi(const MultiPlan &M, int storage, const Domain &D, const void *src,
+                        void *dst, hipStream_t st);
+
 hipError_t launch_init(int storage, const Domain &D, const double *u,
                        const double *b, double bwx, double bwy, void *dst,
                        hipStream_t st);

@@ -1,0 +1,178 @@
+// rr_multi.h -- several time steps per pass over memory (unforced, periodic
+// grids; the tile form also walls and a body force).
+//
+// One step per launch streams all 19 planes through HBM (or, on small grids,
+// waits for a launch) every step.  Both forms here take T steps from one read
+// and one write of the state and repeat the one-step kernel's per-node
+// arithmetic exactly (the storage rounding between steps included), so the
+// state after T steps is bit for bit that of T single steps.
+//
+//  * march_strip: a wavefront owns a window of 64 neighbouring nodes and
+//    marches down a strip of rows.  Stage s of the march holds step s of one
+//    row; stage s + 1 works one row behind it.  Streaming in x is a one-lane
+//    DPP shift, streaming in y a register delay: the planes with c_y = 0 wait
+//    one row, those with c_y = +1 two, those with c_y = -1 none (19 registers
+//    per stage boundary).  No LDS; each step loses one node per side of the
+//    window (T = 4: 56 of 64 lanes store) and two rows per strip end.
+//  * tile_steps: a workgroup owns a BX x BY tile held one node per thread;
+//    between steps the populations that move are exchanged through LDS.  Each
+//    step after the first loses a one-node ring.  For grids too small to fill
+//    the chip with marching strips.
+#pragma once
+#include <utility>
+
+#include "rr_node.h"
+#include "rr_pull.h"
+
+namespace rr {
+
+__host__ __device__ constexpr int plane_cx(int p) { return p < kQ ? cx(p) : ex((p - kQ) / 2); }
+__host__ __device__ constexpr int plane_cy(int p) { return p < kQ ? cy(p) : ey((p - kQ) / 2); }
+__host__ __device__ constexpr int plane_opp(int p) {
+  return p < kQ ? opp_f(p) : gplane(opp_g((p - kQ) / 2), (p - kQ) & 1);
+}
+// Number of planes q < p with c_y = cyv: the plane's place in a delay line.
+__host__ __device__ constexpr int delay_slot(int p, int cyv) {
+  int n = 0;
+  for (int q = 0; q < p; ++q) n += plane_cy(q) == cyv;
+  return n;
+}
+constexpr int kDelayZero = delay_slot(kPlanes, 0), kDelayPlus = delay_slot(kPlanes, 1);
+
+// The value a step stores and the next one reads back.
+template <class C>
+__device__ __forceinline__ float through_storage(float v, float s, float inv_s) {
+  if constexpr (std::is_same_v<C, CodecF32>)
+    return v;
+  else
+    return C::dec(C::enc(v, s), inv_s);
+}
+
+// ---- marching strips -----------------------------------------------------------
+// Lane i takes the value of lane i - 1 (c_x = +1) or i + 1 (c_x = -1).  The
+// window's end lanes get zero: their values are lost to the halo anyway.
+template <int CX>
+__device__ __forceinline__ float lane_shift(float v) {
+  if constexpr (CX == 0) return v;
+  constexpr int ctrl = CX > 0 ? 0x138 : 0x130;  // wave_shr:1 / wave_shl:1
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false));
+}
+
+// Collide one row of the window: v holds the 19 post-collision planes of the
+// previous step at the rows they are pulled from, unshifted in x.
+template <class C, int... P>
+__device__ __forceinline__ void march_shift(float (&v)[kPlanes], std::integer_sequence<int, P...>) {
+  ((v[P] = lane_shift<plane_cx(P)>(v[P])), ...);
+}
+template <class C>
+__device__ __forceinline__ void march_stage(float (&v)[kPlanes], const CollideParams &P) {
+  march_shift<C>(v, std::make_integer_sequence<int, kPlanes>{});
+  float(&d)[kQ] = *reinterpret_cast<float(*)[kQ]>(v);
+  float(&g)[2 * kQm] = *reinterpret_cast<float(*)[2 * kQm]>(v + kQ);
+  collide<false>(d, g, P);
+}
+
+template <class C, int... P>
+__device__ __forceinline__ void march_load(const PlaneGeom &G, const typename C::T *rm,
+                                           const typename C::T *rz, const typename C::T *rp,
+                                           uint32_t xo, float (&v)[kPlanes],
+                                           std::integer_sequence<int, P...>) {
+  using T = typename C::T;
+  ((v[P] = C::dec(
+        ld_at<T, false>(
+            plane_ptr(plane_cy(P) == 0 ? rz : (plane_cy(P) > 0 ? rm : rp), P, G.plane), xo),
+        G.inv_s)),
+   ...);
+}
+template <class C, int... P>
+__device__ __forceinline__ void march_store(const PlaneGeom &G, typename C::T *row, uint32_t xo,
+                                            const float (&v)[kPlanes],
+                                            std::integer_sequence<int, P...>) {
+  using T = typename C::T;
+  ((st_at<T, false>(row + (int64_t)P * G.plane, xo, C::enc(v[P], G.s))), ...);
+}
+
+// T steps on the rows ys .. ys + rows - 1 of the calling wavefront's window:
+// lane 0 stands at node x0 (any sign; positions wrap), and the lanes with
+// `live` set store.  Every wavefront of a workgroup calls it with the same
+// `rows` (it holds barriers); rows at or past ny are not stored.  The barrier
+// per row keeps the workgroup's windows side by side, so the cache lines that
+// neighbouring windows both write are complete in L2 before they are evicted
+// (8192^2 FP32: 1.7 x slower without); the stores are plain for that reason.
+template <class C, int T>
+__device__ __forceinline__ void march_strip(const PlaneGeom &G, const CollideParams &P,
+                                            const typename C::T *__restrict__ src,
+                                            typename C::T *__restrict__ dst, int x0, bool live,
+                                            int ys, int rows) {
+  using TT = typename C::T;
+  constexpr auto planes = std::make_integer_sequence<int, kPlanes>{};
+  int x = x0 % G.nx;
+  x += x < 0 ? G.nx : 0;
+  uint32_t xo = (uint32_t)x * (uint32_t)sizeof(TT);
+  float z[T - 1][kDelayZero], p1[T - 1][kDelayPlus], p2[T - 1][kDelayPlus];
+#pragma unroll
+  for (int s = 0; s < T - 1; ++s) {
+#pragma unroll
+    for (int i = 0; i < kDelayZero; ++i) z[s][i] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kDelayPlus; ++i) p1[s][i] = p2[s][i] = 0.0f;
+  }
+  // rows y - 1, y, y + 1 of the first stage, y from ys - (T - 1)
+  auto wrap = [&](int v) {
+    v %= G.ny;
+    return v < 0 ? v + G.ny : v;
+  };
+  int ym = wrap(ys - T), yz = wrap(ys - T + 1), yp = wrap(ys - T + 2);
+  const int last = rows + 2 * (T - 1);
+  for (int i = 0; i < last; ++i) {
+    asm("" : "+v"(xo));  // keeps the 32-bit offset beside its use (scalar-base addressing)
+    float v[kPlanes];
+    march_load<C>(G, src + (int64_t)ym * G.row, src + (int64_t)yz * G.row,
+                  src + (int64_t)yp * G.row, xo, v, planes);
+    ym = yz;
+    yz = yp;
+    yp = yp == G.ny - 1 ? 0 : yp + 1;
+    march_stage<C>(v, P);
+#pragma unroll
+    for (int s = 0; s < T - 1; ++s) {
+      if (i < 2 * s) break;  // stage s has no valid row yet
+      float c[kPlanes];
+#pragma unroll
+      for (int p = 0; p < kPlanes; ++p) {
+        const float w = through_storage<C>(v[p], G.s, G.inv_s);
+        const int q = delay_slot(p, plane_cy(p));
+        if (plane_cy(p) < 0) {
+          c[p] = w;
+        } else if (plane_cy(p) == 0) {
+          c[p] = z[s][q];
+          z[s][q] = w;
+        } else {
+          c[p] = p2[s][q];
+          p2[s][q] = p1[s][q];
+          p1[s][q] = w;
+        }
+      }
+      if (i < 2 * (s + 1)) break;
+      march_stage<C>(c, P);
+#pragma unroll
+      for (int p = 0; p < kPlanes; ++p) v[p] = c[p];
+    }
+    __builtin_amdgcn_s_barrier();
+    const int yo = ys + i - 2 * (T - 1);
+    if (i >= 2 * (T - 1) && live && yo < G.ny)
+      march_store<C>(G, dst + (int64_t)yo * G.row, xo, v, planes);
+  }
+}
+
+// ---- tiles with LDS exchange -----------------------------------------------------
+// Populations that move, i.e. all but f_0 and g_0: 16 planes.
+__host__ __device__ constexpr bool plane_moves(int p) { return plane_cx(p) || plane_cy(p); }
+__host__ __device__ constexpr int moving_slot(int p) {
+  int n = 0;
+  for (int q = 0; q < p; ++q) n += plane_moves(q);
+  return n;
+}
+constexpr int kMoving = moving_slot(kPlanes);
+
+}  // namespace rr

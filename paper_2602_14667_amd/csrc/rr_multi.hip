@@ -1,0 +1,270 @@
+// rr_multi.hip -- kernels and launch rules of the multi-step forms
+// (rr_multi.h): T time steps from one read and one write of the state.
+#include <hip/hip_runtime.h>
+
+#include "rr_kernels.h"
+#include "rr_multi.h"
+#include "rr_node.h"
+#include "rr_pull.h"
+#include "rr_walls.h"
+
+namespace rr {
+
+// ---- marching strips -------------------------------------------------------------
+// A workgroup is four wavefronts: wx neighbouring windows of `out` stored
+// nodes each, times 4 / wx strips of `rows` rows (wx = 4 unless the grid is
+// narrower than that).  Eight neighbouring workgroups of every 64 share an XCD.
+//
+// Bound by the vector ALU: 8192^2 FP32, 4 steps per pass, 586 us per step
+// (114 GLUPS, 88 % of the issue rate at ~265 instructions per node and 56 of
+// 64 lanes storing) against 1652 us one step at a time, which HBM bounds.
+// Four steps and not more: 2 / 3 / 4 / 6 steps measured 1076 / 725 / 586 /
+// 625 us per step (six lose 12 of 64 lanes to the halo); two nodes per lane
+// need twice the delay registers and measured 694 us at three steps.  Four
+// neighbouring windows of 56 nodes are 7 x 128 B lines in FP32.
+constexpr int kMarchHalo = 4, kMarchOut = 64 - 2 * kMarchHalo;
+
+template <class C, int T>
+__global__ __launch_bounds__(256) void k_march(PlaneGeom G, CollideParams P, int groups_x, int wx,
+                                               int out, int rows,
+                                               const typename C::T *__restrict__ src,
+                                               typename C::T *__restrict__ dst) {
+  static_assert(T <= kMarchHalo, "each step loses one node per side");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int L = xcd_local(blockIdx.x, gridDim.x);
+  const int gy = L / groups_x, gx = L - gy * groups_x;
+  const int wy = wave / wx;
+  const int x0 = (gx * wx + (wave - wy * wx)) * out - kMarchHalo + lane;
+  const bool live = lane >= kMarchHalo && lane < kMarchHalo + out && x0 < G.nx;
+  march_strip<C, T>(G, P, src, dst, x0, live, (gy * (4 / wx) + wy) * rows, rows);
+}
+
+// ---- tiles with LDS exchange ---------------------------------------------------
+// A workgroup holds a B x B tile, one node per thread, and takes T steps: the
+// first pulls from memory, the later ones from the neighbours through LDS
+// (two buffers, so one barrier per step).  After T steps the inner B - 2 (T -
+// 1) square is valid and stored.  With walls the tiles cover [0, ny) in y,
+// threads beyond a wall idle, and bounce-back reads the node's own values as
+// the one-step kernel does.
+template <class C, int B, bool WALLS, bool FORCED>
+__global__ __launch_bounds__(B *B) void k_tile_steps(Domain D, int tiles_x, int T,
+                                                     const typename C::T *__restrict__ src,
+                                                     typename C::T *__restrict__ dst) {
+  constexpr int N = B * B;
+  __shared__ float ex[2][kMoving][N];
+  const int halo = T - 1, out = B - 2 * halo;
+  const int ty = blockIdx.x / tiles_x, tx = blockIdx.x - ty * tiles_x;
+  const int t = threadIdx.x, ly = t / B, lx = t - ly * B;
+  const int xr = tx * out - halo + lx, yr = ty * out - halo + ly;
+  int x = xr % D.nx;
+  x += x < 0 ? D.nx : 0;
+  int y = yr;
+  bool inside = true;
+  if constexpr (WALLS) {
+    inside = yr >= 0 && yr < D.ny;
+    y = inside ? yr : 0;
+  } else {
+    y %= D.ny;
+    y += y < 0 ? D.ny : 0;
+  }
+  const bool lo = WALLS && y == 0, hi = WALLS && y == D.ny - 1;
+  const CollideParams P{D.om_c, D.omm_c, D.Gx, D.Gy, D.src_c};
+  const PlaneGeom G{D.plane, D.nx, D.ny, D.s, D.inv_s, 0u, D.row};
+  float v[kPlanes];
+  float(&d)[kQ] = *reinterpret_cast<float(*)[kQ]>(v);
+  float(&g)[2 * kQm] = *reinterpret_cast<float(*)[2 * kQm]>(v + kQ);
+  if constexpr (WALLS)
+    pull_node<C, true>(D, src, x, y, d, g);
+  else
+    pull_node_per<C, false>(G, row_addr<RM_LANE>(G, src, y), x, d, g);
+#pragma unroll 1
+  for (int s = 1;; ++s) {
+    collide<FORCED>(d, g, P);
+    if (s == T) break;
+    float(&b)[kMoving][N] = ex[s & 1];
+#pragma unroll
+    for (int p = 0; p < kPlanes; ++p) {
+      v[p] = through_storage<C>(v[p], D.s, D.inv_s);
+      if (plane_moves(p)) b[moving_slot(p)][t] = v[p];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < kPlanes; ++p) {
+      if (!plane_moves(p)) continue;
+      // the upstream neighbour; cells past the tile's edge (whose values the
+      // halo discards) stay in bounds
+      const int o = t - plane_cx(p) - plane_cy(p) * B;
+      float w = b[moving_slot(p)][min(max(o, 0), N - 1)];
+      if constexpr (WALLS) {
+        if (plane_cy(p) != 0 && (plane_cy(p) > 0 ? lo : hi)) {
+          w = b[moving_slot(plane_opp(p))][t];
+          if (p >= kQ) w = ((p - kQ) & 1 ? D.bw2y : D.bw2x) - w;
+        }
+      }
+      v[p] = w;
+    }
+  }
+  if (inside && lx >= halo && lx < B - halo && ly >= halo && ly < B - halo && xr < D.nx &&
+      yr < D.ny)
+    store_node<C, false, RM_LANE>(G, dst, x, y, d, g);
+}
+
+// ---- launch rules ------------------------------------------------------------------
+template <class C>
+static void march_t(const MultiPlan &M, const Domain &D, const void *src, void *dst,
+                    hipStream_t st) {
+  using T = typename C::T;
+  const PlaneGeom G{D.plane, D.nx, D.ny, D.s, D.inv_s, 0u, D.row};
+  const CollideParams P{D.om_c, D.omm_c, 0.0f, 0.0f, 0.0f};
+  const int strips = 4 / M.wx;
+  const int groups_y = (D.ny + M.rows * strips - 1) / (M.rows * strips);
+  const dim3 grid(M.groups_x * groups_y), block(256);
+  auto s = (const T *)src;
+  auto d = (T *)dst;
+  if (M.steps == 4)
+    hipLaunchKernelGGL((k_march<C, 4>), grid, block, 0, st, G, P, M.groups_x, M.wx, M.out, M.rows, s, d);
+  else if (M.steps == 3)
+    hipLaunchKernelGGL((k_march<C, 3>), grid, block, 0, st, G, P, M.groups_x, M.wx, M.out, M.rows, s, d);
+  else
+    hipLaunchKernelGGL((k_march<C, 2>), grid, block, 0, st, G, P, M.groups_x, M.wx, M.out, M.rows, s, d);
+}
+
+template <class C, int B>
+static void tile_b(const MultiPlan &M, const Domain &D, const void *src, void *dst,
+                   hipStream_t st) {
+  using T = typename C::T;
+  const int out = B - 2 * (M.steps - 1);
+  const int tiles_x = (D.nx + out - 1) / out, tiles_y = (D.ny + out - 1) / out;
+  const dim3 grid(tiles_x * tiles_y), block(B * B);
+  const bool forced = D.Gx != 0.0f || D.Gy != 0.0f;
+  auto s = (const T *)src;
+  auto d = (T *)dst;
+  if (D.walls && forced)
+    hipLaunchKernelGGL((k_tile_steps<C, B, true, true>), grid, block, 0, st, D, tiles_x, M.steps, s, d);
+  else if (D.walls)
+    hipLaunchKernelGGL((k_tile_steps<C, B, true, false>), grid, block, 0, st, D, tiles_x, M.steps, s, d);
+  else if (forced)
+    hipLaunchKernelGGL((k_tile_steps<C, B, false, true>), grid, block, 0, st, D, tiles_x, M.steps, s, d);
+  else
+    hipLaunchKernelGGL((k_tile_steps<C, B, false, false>), grid, block, 0, st, D, tiles_x, M.steps, s, d);
+}
+
+template <class C>
+static void multi_t(const MultiPlan &M, const Domain &D, const void *src, void *dst,
+                    hipStream_t st) {
+  if (M.tile == 0)
+    march_t<C>(M, D, src, dst, st);
+  else if (M.tile == 16)
+    tile_b<C, 16>(M, D, src, dst, st);
+  else if (M.tile == 24)
+    tile_b<C, 24>(M, D, src, dst, st);
+  else
+    tile_b<C, 32>(M, D, src, dst, st);
+}
+
+constexpr int kCUs = 256;
+
+// Estimated time (us) of one pass of four marching steps with w workgroups per
+// CU and strips of `rows` rows: per row each wavefront on a SIMD issues four
+// collisions (1.8 us), each strip adds its halo rows, plus the launch.  Fits
+// the measured passes of 20 grids from 320^2 to 5000^2, 1 to 16 workgroups
+// per CU, to 4 % on average.
+static double march_us(double w, int rows) {
+  return 6.0 + (1.1 + 1.75 * (w > 1.0 ? w : 1.0)) * (rows + 2.5);
+}
+// The same for a pass of T steps in 32 x 32 tiles, one workgroup per CU at a
+// time (131 KB of LDS), q tiles per CU.
+static double tile32_us(int T, double q) { return T == 5 ? 1.5 + 13.0 * q : 2.0 + 11.5 * q; }
+// One step of the one-step kernels: a launch, or the state through HBM.
+static double single_us(const Domain &D) {
+  return 3.0 + (double)D.nx * D.ny * D.elem * 2 * kStatePlanes / 5.4e6;
+}
+
+// Tiles per CU of a pass of T steps in B x B tiles.
+static int64_t tiles_per_cu(const Domain &D, int B, int T) {
+  const int64_t out = B - 2 * (T - 1);
+  return ((D.nx + out - 1) / out * ((D.ny + out - 1) / out) + kCUs - 1) / kCUs;
+}
+
+// The form and the number of steps of the next pass with n steps to go.
+//
+// Tiles of the smallest size whose workgroups are at most one per CU: a pass
+// is then one round, bound by latency (64^2 FP32: 16 x 16 tiles, 5 steps, 1.27
+// us per step against 3.12 one at a time; 128^2 1.64 / 3.26; 256^2 with 24 x
+// 24 2.55 / 3.92; 320^2 with 32 x 32 2.9 / 4.5; 400^2, 4 steps, 3.6 / 7.3; FP16 within
+// 15 % of these).  Above that the estimates decide between 32 x 32 tiles and
+// marching strips (512^2 FP32 5.7 / 9.6 in tiles, 768^2 9.8 / 20.0, 1024^2 14.9
+// / 30.5, 2048^2 45 / 108, 8192^2 586 / 1652 marching; FP16 1024^2 15.8 / 19.6,
+// 4096^2 155 / 222).  Short remainders stay one step at a time where the halo
+// costs more than the launches saved, and grids so narrow or short that the
+// estimate exceeds the one-step kernel's: two steps in 24 x 24 tiles at 256^2
+// measured 5.0 us per step against 3.9, three 3.9; FP16 grids narrower than
+// 128 nodes with more than one tile per CU 5.3 against 4.75.  Walls and forces
+// exist as tiles only: unforced up to six tiles per CU (FP16 four), forced (FP64
+// arithmetic) up to two: 512 x 256 4.5 / 5.9 us, but 1000 x 600 18.7 / 18.6.
+MultiPlan multi_plan(const Domain &D, int64_t n) {
+  MultiPlan M{};
+  if (n < 2 || D.feq || D.sr || D.nx > (1 << 30) || D.ny > (1 << 30)) return M;
+  const bool forced = D.Gx != 0.0f || D.Gy != 0.0f;
+  auto tile = [&](int B, int T) {
+    MultiPlan P{};
+    P.tile = B;
+    P.steps = n < T ? (int)n : T;
+    return P;
+  };
+  if (tiles_per_cu(D, 16, 5) == 1) return tile(16, 5);
+  if (n >= 4 && tiles_per_cu(D, 24, 5) == 1) return tile(24, 5);
+  int T = 5;
+  int64_t q = tiles_per_cu(D, 32, 5);
+  const int64_t q4 = tiles_per_cu(D, 32, 4);
+  if (tile32_us(4, q4) / 4 < tile32_us(5, q) / 5) {
+    T = 4;
+    q = q4;
+  }
+  const double single = single_us(D);
+  const bool tiles = n >= 4 && (q == 1 || ((D.elem == 4 || D.nx >= 128) &&
+                                           tile32_us(T, q) / T < 1.1 * single));
+  if (D.walls || forced)
+    return tiles && q <= (forced ? 2 : (D.elem == 4 ? 6 : 4)) ? tile(32, T) : M;
+  if (tiles && q == 1) return tile(32, T);
+  if ((int64_t)D.nx * D.ny < (n >= 4 ? 200000 : 400000)) return tiles ? tile(32, T) : M;
+  // marching: windows of equal width, in multiples of 8 nodes
+  const int windows = (D.nx + kMarchOut - 1) / kMarchOut;
+  int out = ((D.nx + windows - 1) / windows + 7) / 8 * 8;
+  if (out > kMarchOut) out = kMarchOut;
+  const int nw = (D.nx + out - 1) / out;
+  MultiPlan W{};
+  W.out = out;
+  W.wx = nw >= 3 ? 4 : nw;
+  W.groups_x = (nw + W.wx - 1) / W.wx;
+  const int64_t strips = 4 / W.wx;  // strips per workgroup
+  double best = 0.0;
+  for (int k = 1; k <= 16; ++k) {
+    const int64_t groups_y = kCUs * k / W.groups_x > 0 ? kCUs * k / W.groups_x : 1;
+    int rows = (int)((D.ny + groups_y * strips - 1) / (groups_y * strips));
+    if (rows < 3) rows = 3;
+    const int64_t wgs = W.groups_x * ((D.ny + rows * strips - 1) / (rows * strips));
+    const double us = march_us((double)wgs / kCUs, rows);
+    if (W.rows == 0 || us < best) {
+      best = us;
+      W.rows = rows;
+    }
+  }
+  if (tiles && tile32_us(T, q) / T < best / 4) return tile(32, T);
+  if (best / 4 > 1.1 * single) return M;
+  W.steps = n < 4 ? (int)n : 4;
+  return W;
+}
+
+hipError_t launch_multi(const MultiPlan &M, int storage, const Domain &D, const void *src,
+                        void *dst, hipStream_t st) {
+  if (storage != kF16)
+    multi_t<CodecF32>(M, D, src, dst, st);
+  else if (D.s == 1.0f)
+    multi_t<CodecF16U>(M, D, src, dst, st);
+  else
+    multi_t<CodecF16>(M, D, src, dst, st);
+  return hipGetLastError();
+}
+
+}  // namespace rr

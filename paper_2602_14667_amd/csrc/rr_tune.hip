@@ -24,11 +24,12 @@ constexpr double kMargin = 0.98;
 
 struct Entry {
   int bx = 0, by = 0, xcd = 0, grid = 0, fetch = 0, nt = 1;
+  int multi = 0;  // the default launch: several steps per pass where a form applies
   double ms = 0.0;
 };
 
 // ---- cache file: {"key": {"bx": 128, "by": 2, "xcd": 2, "grid": 0, "fetch": 0, "nt": 1,
-// "ms": 1.7}, ...}
+// "multi": 0, "ms": 1.7}, ...}
 // The cache file: the caller's path, else RRMHD_AUTOTUNE_CACHE, else none.
 const char *cache_file(const char *path) {
   if (path) return path;
@@ -65,7 +66,7 @@ std::map<std::string, Entry> read_cache(const char *path) {
       if (t == std::string::npos) return;
       *out = std::strtod(body.c_str() + t + 1, nullptr);
     };
-    double v[7] = {0, 0, 0, 0, 0, 0, 1};
+    double v[8] = {0, 0, 0, 0, 0, 0, 1, 0};
     num("bx", &v[0]);
     num("by", &v[1]);
     num("xcd", &v[2]);
@@ -73,6 +74,7 @@ std::map<std::string, Entry> read_cache(const char *path) {
     num("ms", &v[4]);
     num("fetch", &v[5]);
     num("nt", &v[6]);
+    num("multi", &v[7]);
     e.bx = (int)v[0];
     e.by = (int)v[1];
     e.xcd = (int)v[2];
@@ -80,6 +82,7 @@ std::map<std::string, Entry> read_cache(const char *path) {
     e.ms = v[4];
     e.fetch = (int)v[5];
     e.nt = (int)v[6];
+    e.multi = (int)v[7];
     if (e.bx > 0 && e.by > 0) m[key] = e;
     p = cb + 1;
   }
@@ -96,9 +99,9 @@ void write_cache(const char *path, const std::map<std::string, Entry> &m) {
   for (const auto &kv : m) {
     std::fprintf(f,
                  "  \"%s\": {\"bx\": %d, \"by\": %d, \"xcd\": %d, \"grid\": %d, \"fetch\": %d, "
-                 "\"nt\": %d, \"ms\": %.6f}%s\n",
+                 "\"nt\": %d, \"multi\": %d, \"ms\": %.6f}%s\n",
                  kv.first.c_str(), kv.second.bx, kv.second.by, kv.second.xcd, kv.second.grid,
-                 kv.second.fetch, kv.second.nt, kv.second.ms, (++i < m.size()) ? "," : "");
+                 kv.second.fetch, kv.second.nt, kv.second.multi, kv.second.ms, (++i < m.size()) ? "," : "");
   }
   std::fprintf(f, "}\n");
   std::fclose(f);
@@ -199,6 +202,15 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
         (storage == RRMHD_STORE_F16 || rows) && nx % 2 == 0 && !rr_handle_walls(h);
     const bool quad_ok = storage == RRMHD_STORE_F16 && nx % 4 == 0 && !rr_handle_walls(h);
     best.ms = 1e30;
+    // the default launch first, with several steps per pass; the candidates
+    // below are shapes of the one-step kernels
+    if (rc == RRMHD_OK) {
+      rr_handle_default_launch(h);
+      rc = rrmhd_get_launch(h, &best.bx, &best.by, nullptr, &best.xcd, &best.nt);
+      if (rc == RRMHD_OK)
+        rc = time_steps([&](int n) { return rrmhd_step(h, n); }, st, trials, &best.ms);
+      best.multi = 1;
+    }
     for (const Shape &c : cands) {
       if (rc != RRMHD_OK) break;
       if ((c.nt & 4) && !pair_ok) continue;
@@ -214,6 +226,7 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
         best.by = c.by;
         best.xcd = c.xcd;
         best.nt = c.nt;
+        best.multi = 0;
         best.ms = ms;
       }
     }
@@ -226,7 +239,10 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
     cache[key] = best;
     write_cache(cache_path, cache);
   }
-  rc = rrmhd_set_launch(h, best.bx, best.by, 1, best.xcd, best.nt > 0 ? best.nt : 1);
+  if (best.multi)
+    rr_handle_default_launch(h);
+  else
+    rc = rrmhd_set_launch(h, best.bx, best.by, 1, best.xcd, best.nt > 0 ? best.nt : 1);
   if (out_bx) *out_bx = best.bx;
   if (out_by) *out_by = best.by;
   if (out_xcd) *out_xcd = best.xcd;

@@ -1,0 +1,107 @@
+"""Several steps per launch (LDS tiles and marching strips) against the one-step
+kernels, bit for bit: a handle whose launch shape was set explicitly takes one
+step per launch.  Sizes sit at the edges of the launch rule's forms: tiles of
+16, 24 and 32 nodes, one and several tiles per CU, windows and strips with
+remainders, grids narrower than a window and strips that end inside one.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_14667_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def state(s):
+    torch.cuda.synchronize()
+    out = torch.empty(s.state_bytes(), dtype=torch.uint8, device="cuda")
+    s.save_state(out)
+    torch.cuda.synchronize()
+    return out
+
+
+def pair(nx, ny, storage, **kw):
+    from paper_2602_14667_amd import rrmhd
+    print(f"[gpu] multi-step {nx}x{ny} {storage} {kw}", flush=True)
+    rng = np.random.default_rng(nx * 7919 + ny)
+    u = torch.from_numpy(0.03 * rng.standard_normal((2, ny, nx))).cuda()
+    b = torch.from_numpy(0.03 * rng.standard_normal((2, ny, nx))).cuda()
+    got, ref = (rrmhd.Solver(nx, ny, 0.56, 0.61, storage=storage, **kw) for _ in range(2))
+    ref.set_launch(64, 1, 1, 0, 1)
+    for s in (got, ref):
+        s.init(u, b)
+    return got, ref
+
+
+def check(got, ref, counts):
+    for n in counts:
+        got.step(n)
+        ref.step(n)
+        assert got.step_count == ref.step_count
+        assert torch.equal(state(got), state(ref)), n
+    got.close()
+    ref.close()
+
+
+TILES = [(1, 1), (2, 3), (7, 5), (8, 9), (64, 64), (127, 129), (128, 128), (129, 120), (203, 180),
+         (224, 224), (225, 224), (300, 290), (352, 384), (400, 416), (512, 500), (33, 6001)]
+MARCH = [(800, 700), (1001, 777), (56, 9000), (57, 9000), (112, 4001), (113, 6000), (224, 2500),
+         (225, 2500), (6000, 200), (2048, 1024)]
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("shape", TILES + MARCH)
+def test_periodic_grids_equal_single_steps(shape, storage):
+    check(*pair(*shape, storage), [1, 2, 3, 4, 5, 6, 9, 11])
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("force", [(0.0, 0.0), (1e-6, 2e-6)])
+@pytest.mark.parametrize("shape", [(1, 2), (5, 3), (64, 64), (130, 33), (200, 190), (512, 256),
+                                   (700, 640)])
+def test_walls_and_force_equal_single_steps(shape, storage, force):
+    check(*pair(*shape, storage, walls=True, force=force, b_wall=(0.001, 0.02)),
+          [2, 3, 5, 7, 10])
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("shape", [(64, 64), (200, 200), (300, 300)])
+def test_periodic_force_equals_single_steps(shape, storage):
+    check(*pair(*shape, storage, force=(1e-6, -1e-6)), [2, 4, 5, 9])
+
+
+@pytest.mark.parametrize("shape", [(100, 90), (1001, 640)])
+def test_planar_layout_scale_and_graph(shape):
+    check(*pair(*shape, "f32", layout="planar"), [5, 6])
+    check(*pair(*shape, "f16", codec_scale=4.0), [5, 6])
+    got, ref = pair(*shape, "f32")
+    got.set_graph_chunk(7)  # two launches or three, so replays may end in either buffer
+    for k in range(3):
+        check_graph(got, ref, 23 + k)
+    got.close()
+    ref.close()
+
+
+def check_graph(got, ref, n):
+    got.step(n)
+    ref.step(n)
+    assert torch.equal(state(got), state(ref)), n
+
+
+def test_nonfinite_values_spread_as_in_single_steps():
+    """A NaN and an infinity in the state reach the same nodes either way."""
+    for shape in ((96, 80), (900, 800)):
+        got, ref = pair(*shape, "f32")
+        s = state(ref).view(torch.float32).clone()
+        s[5 * shape[0] * shape[1] + 37] = float("nan")
+        s[2 * shape[0] * shape[1] + 20 * shape[0] + 11] = float("inf")
+        for h in (got, ref):
+            h.load_state(s.view(torch.uint8), 0)
+            h.step(5)
+        a, b = state(got).view(torch.int32), state(ref).view(torch.int32)
+        fa, fb = a.view(torch.float32), b.view(torch.float32)
+        assert torch.equal(torch.isnan(fa), torch.isnan(fb))
+        assert torch.equal(a[~torch.isnan(fa)], b[~torch.isnan(fb)])
+        got.close()
+        ref.close()
