@@ -43,15 +43,35 @@ namespace rr {
 
 constexpr int kTB = 256;
 
-__device__ __forceinline__ float gelu32(float z) {
-  const float k = 0.7978845608028654f;
-  return 0.5f * z * (1.0f + tanhf(k * fmaf(0.044715f, z * z * z, z)));
+// GELU in its tanh form and its derivative, as z s and s + 2 z s (1 - s) v'(z)
+// with s = 1 / (1 + e), e = exp(-2 v), v = sqrt(2/pi) (z + 0.044715 z^3): the
+// same functions as z/2 (1 + tanh v), without the cancellation of 1 + tanh v
+// at negative z, at one v_exp_f32 and one v_rcp_f32.  The rounding of 1 + e is
+// carried into the reciprocal's correction step; 1 - s is e s.  Largest and
+// rms error over |z| <= 5 against FP64 (library tanhf form in brackets): 3.7e-7
+// (4.3e-7) and 6.4e-8 (7.5e-8), derivative 1.4e-7 (5.6e-7) and 2.9e-8 (1.3e-7).
+__device__ __forceinline__ void gelu_parts(float z, float &h, float &es, float &s) {
+  constexpr double kL = 2.302208198144325;  // 2 sqrt(2 / pi) log2(e)
+  constexpr float c1 = (float)kL, c1l = (float)(kL - (double)c1), c2 = (float)(kL * 0.044715);
+  const float p = fmaf(z, c1, z * fmaf(c2, z * z, c1l));  // e = 2^-p
+  const float e = __builtin_amdgcn_exp2f(fminf(-p, 126.0f));
+  const float d = 1.0f + e, bb = d - 1.0f;
+  const float err = (1.0f - (d - bb)) + (e - bb);  // 1 + e = d + err
+  const float r0 = __builtin_amdgcn_rcpf(d);
+  s = fmaf(fmaf(-err, r0, fmaf(-d, r0, 1.0f)), r0, r0);
+  es = e * s;
+  h = z * s;
 }
-
-__device__ __forceinline__ float gelu32_grad(float z) {
-  const float k = 0.7978845608028654f;
-  const float t = tanhf(k * fmaf(0.044715f, z * z * z, z));
-  return 0.5f * (1.0f + t) + 0.5f * z * (1.0f - t * t) * k * fmaf(3.0f * 0.044715f, z * z, 1.0f);
+__device__ __forceinline__ float gelu32(float z) {
+  float h, es, s;
+  gelu_parts(z, h, es, s);
+  return h;
+}
+__device__ __forceinline__ void gelu_pair(float z, float &h, float &g) {
+  float es, s;
+  gelu_parts(z, h, es, s);
+  const float w = fmaf(0.21406445f, z * z, 1.5957691f);  // 2 v'(z): 6 sqrt(2/pi) 0.044715, 2 sqrt(2/pi)
+  g = fmaf(h * w, es, s);
 }
 
 // ---- data preparation -------------------------------------------------------
@@ -231,109 +251,498 @@ __global__ __launch_bounds__(256) void k_sum64(const double *__restrict__ v, int
   if (threadIdx.x == 0) out[0] = red[0];
 }
 
-// ---- forward / backward -----------------------------------------------------
-// Per-sample activations are kept in SoA scratch arrays [feature][n] so the
-// gradient reduction can stream them.
-struct Acts {
-  float *xh, *h1, *g1, *h2, *g2, *dy, *dz1, *dz2;  // [8|64|3][n]
+// ---- the network in FP32 on matrix cores --------------------------------------
+// A wavefront holds 16 samples as the columns of 16x16x4 FP32 MFMAs, written
+// transposed (Z^T = W X^T): lane (column c, quarter q), register r of block b
+// is hidden unit 16 b + 4 q + r.  A layer's activations feed the next product's
+// B operand register by register: step r of block b takes the four units that
+// register r holds in the four quarters, and the A operand is read from the
+// weights in LDS in that order (one 16-byte read per block), so activations
+// never leave their registers.  The gradient products contract over the
+// samples, which need the other orientation: each wavefront turns its 64 x 16
+// blocks through LDS, and the four wavefronts of a workgroup share out the
+// products over their 64 samples (wavefront w keeps rows 16 w .. 16 w + 15 of
+// dW2 and dW1 and columns 16 w .. of dW3).
+//
+// Activations are recomputed in the reverse pass, not stored: the former
+// kernels kept 395 floats per sample in memory and reduced the weight gradients
+// with one thread per parameter reading whole sample rows (4.4 ms per
+// activation set at 262,144 samples).  A training step of the feedback form on
+// 512^2 nodes: 9260 us before, 304 us now (k_net_grad 217, k_net_forward
+// 92); its products take 130 us at the FP32 matrix rate (150 TFLOP/s measured).
+// Of the same design with 32-sample wavefronts (32x32x2 MFMAs), one wavefront
+// per SIMD holding all of dW2 took 360 us in k_net_grad, and eight in one workgroup
+// 308 (in step with each other at every barrier, and out of registers).
+struct alignas(16) NetLds {
+  float w2[kNH][kNH + 4];       // W2, rows padded against bank conflicts
+  float w1[kNH][kNIN + 4];      // W1
+  float w1t[kNOUT][kNH];        // columns 5..7 of W1 (the a_1^(2) inputs)
+  float w3[kNOUT][kNH];
+  float b1[kNH], b2[kNH];
+  float mu[kNIN], sigma[kNIN];
+  float b3[kNOUT], so[kNOUT], pad_[2];
 };
+constexpr int kNetWaves = 4, kNetThreads = 64 * kNetWaves;
+constexpr int kNetGroup = 16;  // samples of a wavefront's pass
+typedef float floatx2_t __attribute__((ext_vector_type(2)));
 
-// tg = nullptr: no a-priori loss; A.dy receives the outputs y instead.
-__global__ __launch_bounds__(kTB) void k_forward(const float *__restrict__ p,
-                                                 const float *__restrict__ norm,
-                                                 const float *__restrict__ x,
-                                                 const float *__restrict__ tg, int n, Acts A,
-                                                 float *__restrict__ loss_part) {
-  __shared__ float P[kNParam];
-  __shared__ float red[kTB / 64];
-  for (int k = threadIdx.x; k < kNParam; k += kTB) P[k] = p[k];
-  __syncthreads();
-  const int s = blockIdx.x * kTB + threadIdx.x;
-  float l = 0.0f;
-  if (s < n) {
-    float xh[kNIN], h1[kNH];
-#pragma unroll
-    for (int k = 0; k < kNIN; ++k) {
-      xh[k] = (x[(int64_t)s * kNIN + k] - norm[k]) / norm[kNIN + k];
-      A.xh[(int64_t)k * n + s] = xh[k];
-    }
-#pragma unroll
-    for (int i = 0; i < kNH; ++i) {
-      float z = P[kOffB1 + i];
-#pragma unroll
-      for (int k = 0; k < kNIN; ++k) z = fmaf(P[kOffW1 + i * kNIN + k], xh[k], z);
-      h1[i] = gelu32(z);
-      A.h1[(int64_t)i * n + s] = h1[i];
-      A.g1[(int64_t)i * n + s] = gelu32_grad(z);
-    }
-    float y[kNOUT] = {P[kOffB3 + 0], P[kOffB3 + 1], P[kOffB3 + 2]};
-    for (int i = 0; i < kNH; ++i) {
-      float z = P[kOffB2 + i];
-#pragma unroll
-      for (int k = 0; k < kNH; ++k) z = fmaf(P[kOffW2 + i * kNH + k], h1[k], z);
-      const float h2 = gelu32(z);
-      A.h2[(int64_t)i * n + s] = h2;
-      A.g2[(int64_t)i * n + s] = gelu32_grad(z);
-#pragma unroll
-      for (int o = 0; o < kNOUT; ++o) y[o] = fmaf(P[kOffW3 + o * kNH + i], h2, y[o]);
-    }
-    if (tg) {
-#pragma unroll
-      for (int o = 0; o < kNOUT; ++o) {
-        const float r = y[o] - tg[(int64_t)s * kNOUT + o] / norm[2 * kNIN + o];
-        l = fmaf(r, r, l);
-        A.dy[(int64_t)o * n + s] = 2.0f * r / (float)n;
-      }
-    } else {
-      // no target: keep the output for the one-step objective
-#pragma unroll
-      for (int o = 0; o < kNOUT; ++o) A.dy[(int64_t)o * n + s] = y[o];
-    }
+__device__ __forceinline__ void net_to_lds(NetLds &W, const float *__restrict__ p,
+                                           const float *__restrict__ norm) {
+  const int t = threadIdx.x;
+  for (int k = t; k < kNH * kNH; k += kNetThreads) W.w2[k / kNH][k % kNH] = p[kOffW2 + k];
+  for (int k = t; k < kNH * kNIN; k += kNetThreads) {
+    const float v = p[kOffW1 + k];
+    W.w1[k / kNIN][k % kNIN] = v;
+    if (k % kNIN >= 5) W.w1t[k % kNIN - 5][k / kNIN] = v;
   }
-  // block sum of the squared residuals (fixed order)
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) l += __shfl_xor(l, off, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = l;
+  for (int k = t; k < kNOUT * kNH; k += kNetThreads) W.w3[k / kNH][k % kNH] = p[kOffW3 + k];
+  if (t < kNH) {
+    W.b1[t] = p[kOffB1 + t];
+    W.b2[t] = p[kOffB2 + t];
+  }
+  if (t < kNOUT) {
+    W.b3[t] = p[kOffB3 + t];
+    W.so[t] = norm[2 * kNIN + t];
+  }
+  if (t < kNIN) {
+    W.mu[t] = norm[t];
+    W.sigma[t] = norm[kNIN + t];
+  }
   __syncthreads();
-  if (threadIdx.x == 0) loss_part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-__global__ __launch_bounds__(kTB) void k_backward(const float *__restrict__ p, int n, Acts A) {
-  __shared__ float P[kNParam];
-  for (int k = threadIdx.x; k < kNParam; k += kTB) P[k] = p[k];
+__device__ __forceinline__ floatx4 ld_f4(const float *p) {
+  floatx4 v;
+  __builtin_memcpy(&v, p, 16);
+  return v;
+}
+// Keeps the weights in LDS (not hoisted into registers) and the phases of a
+// pass apart.
+__device__ __forceinline__ void net_phase() { asm volatile("" ::: "memory"); }
+
+// The lane's share of a wavefront: column c (sample), quarter q.
+struct NetLane {
+  int c, q;
+};
+__device__ __forceinline__ NetLane net_lane() {
+  return NetLane{(int)threadIdx.x & 15, ((int)threadIdx.x >> 4) & 3};
+}
+
+// Pre-activations of layer 1 from the lane's two normalised features (2 q and
+// 2 q + 1 of its sample).
+__device__ __forceinline__ void net_layer1(const NetLds &W, const float (&xh)[2], NetLane L,
+                                           floatx4 (&z)[4]) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    z[m] = ld_f4(W.b1 + 16 * m + 4 * L.q);
+    floatx2_t a;
+    __builtin_memcpy(&a, &W.w1[16 * m + L.c][2 * L.q], 8);
+    z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], xh[0], z[m], 0, 0, 0);
+    z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], xh[1], z[m], 0, 0, 0);
+  }
+}
+// z = b + W2 h (layer 2).
+__device__ __forceinline__ void net_layer2(const NetLds &W, const floatx4 (&h)[4], NetLane L,
+                                           floatx4 (&z)[4]) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) z[m] = ld_f4(W.b2 + 16 * m + 4 * L.q);
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const floatx4 a = ld_f4(&W.w2[16 * m + L.c][16 * b + 4 * L.q]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        z[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], h[b][r], z[m], 0, 0, 0);
+    }
+}
+// d = W2^T z.
+__device__ __forceinline__ void net_layer2_t(const NetLds &W, const floatx4 (&z)[4], NetLane L,
+                                             floatx4 (&d)[4]) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) d[m] = floatx4{0};
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        d[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(W.w2[16 * b + 4 * L.q + r][16 * m + L.c],
+                                                    z[b][r], d[m], 0, 0, 0);
+}
+// Rows `m` (3 x 64) times the activations, summed over the quarters.
+__device__ __forceinline__ void net_rows3(const float (&m)[kNOUT][kNH], const floatx4 (&h)[4],
+                                          NetLane L, float (&y)[kNOUT]) {
+#pragma unroll
+  for (int o = 0; o < kNOUT; ++o) {
+    float a = 0.0f;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const floatx4 w = ld_f4(&m[o][16 * b + 4 * L.q]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) a = fmaf(w[r], h[b][r], a);
+    }
+    a += __shfl_xor(a, 16, 64);
+    y[o] = a + __shfl_xor(a, 32, 64);
+  }
+}
+
+// The lane's two features of sample s, its a_1^(2) entries (features 5, 6, 7)
+// shifted by qv, normalised.
+__device__ __forceinline__ void net_features(const NetLds &W, const float *__restrict__ x,
+                                             int64_t s, NetLane L, const float (&qv)[kNOUT],
+                                             float (&xh)[2]) {
+  floatx2_t f;
+  __builtin_memcpy(&f, x + s * kNIN + 2 * L.q, 8);
+  if (L.q == 2) f[1] += qv[0];
+  if (L.q == 3) {
+    f[0] += qv[1];
+    f[1] += qv[2];
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) xh[k] = (f[k] - W.mu[2 * L.q + k]) / W.sigma[2 * L.q + k];
+}
+
+// D = sigma_out y of every sample (SoA [3][n]).  FEEDBACK: a first pass gives
+// q = (tau_c - 1) sigma_out y(x) (SoA, kept), the second runs on x with its
+// a_1^(2) entries shifted by q, and D = sigma_out y + q.
+template <bool FEEDBACK>
+__global__ __launch_bounds__(kNetThreads) void k_net_forward(const float *__restrict__ p,
+                                                             const float *__restrict__ norm,
+                                                             const float *__restrict__ x, int n,
+                                                             float tm1, float *__restrict__ q,
+                                                             float *__restrict__ D) {
+  __shared__ NetLds W;
+  net_to_lds(W, p, norm);
+  const NetLane L = net_lane();
+  const int groups = (n + kNetGroup - 1) / kNetGroup;
+  for (int g = blockIdx.x * kNetWaves + (threadIdx.x >> 6); g < groups;
+       g += gridDim.x * kNetWaves) {
+    const int64_t s = (int64_t)g * kNetGroup + L.c, sc = s < n ? s : n - 1;
+    float xh[2], y[kNOUT], qv[kNOUT] = {0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int pass = FEEDBACK ? 0 : 1; pass < 2; ++pass) {
+      net_phase();
+      net_features(W, x, sc, L, qv, xh);
+      floatx4 h[4], z[4];
+      net_layer1(W, xh, L, h);
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h[b][r] = gelu32(h[b][r]);
+      net_layer2(W, h, L, z);
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z[b][r] = gelu32(z[b][r]);
+      net_rows3(W.w3, z, L, y);
+#pragma unroll
+      for (int o = 0; o < kNOUT; ++o) {
+        y[o] = W.so[o] * (y[o] + W.b3[o]);
+        if (FEEDBACK && pass == 0) qv[o] = tm1 * y[o];
+      }
+    }
+    if (s < n && L.q < kNOUT) {  // quarter o writes output o
+      const float d = L.q == 0 ? y[0] : (L.q == 1 ? y[1] : y[2]);
+      const float v = L.q == 0 ? qv[0] : (L.q == 1 ? qv[1] : qv[2]);
+      D[(int64_t)L.q * n + s] = FEEDBACK ? d + v : d;
+      if (FEEDBACK) q[(int64_t)L.q * n + s] = v;
+    }
+  }
+}
+
+// Gradient accumulators of a wavefront: its rows of dW2 (four 16 x 16 blocks)
+// and dW1 (unit, feature), its columns of dW3 (output, unit), the biases of its
+// rows (this lane's quarter of the samples) and of the outputs (its sample).
+struct NetGrad {
+  floatx4 w2[4], w1, w3;
+  float b1, b2, b3[kNOUT];
+};
+// A wavefront's turning buffers (64 units x 16 samples).
+struct alignas(16) NetTurn {
+  float a[kNH][kNetGroup + 4], b[kNH][kNetGroup + 4];
+};
+__device__ __forceinline__ void turn_in(float (*t)[kNetGroup + 4], const floatx4 (&v)[4],
+                                        NetLane L) {
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t[16 * b + 4 * L.q + r][L.c] = v[b][r];
+}
+
+// Forward again and reverse mode for the lane's sample; the whole workgroup
+// calls it together.  dy: dL/dy, or (LOSS) formed here from the target t
+// (already over sigma_out) and the squared residual added to `loss`; live =
+// false adds nothing.  gx[3] (GX) = dL/d of the normalised a_1^(2) inputs.
+template <bool LOSS, bool GX>
+__device__ __forceinline__ void net_reverse(const NetLds &W, NetTurn *TT, NetGrad &G,
+                                            const float (&xh)[2], float (&dy)[kNOUT],
+                                            const float (&t)[kNOUT], float scale, bool live,
+                                            float &loss, float (&gx)[kNOUT]) {
+  const NetLane L = net_lane();
+  const int wave = threadIdx.x >> 6;
+  NetTurn &T = TT[wave];
+  floatx4 h1[4], g1[4], z[4];
+  net_layer1(W, xh, L, z);
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float h, g;
+      gelu_pair(z[b][r], h, g);
+      h1[b][r] = h;
+      g1[b][r] = g;
+    }
+  net_layer2(W, h1, L, z);
+  // h2 to the turning buffer (and, for the loss, through layer 3); z becomes
+  // the derivative
+  float y[kNOUT] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float h, g;
+      gelu_pair(z[b][r], h, g);
+      const int u = 16 * b + 4 * L.q + r;
+      T.b[u][L.c] = h;
+      if (LOSS) {
+#pragma unroll
+        for (int o = 0; o < kNOUT; ++o) y[o] = fmaf(W.w3[o][u], h, y[o]);
+      }
+      z[b][r] = g;
+    }
+  if (LOSS) {
+#pragma unroll
+    for (int o = 0; o < kNOUT; ++o) {
+      float a = y[o];
+      a += __shfl_xor(a, 16, 64);
+      a += __shfl_xor(a, 32, 64);
+      const float r = (a + W.b3[o]) - t[o];
+      if (live && L.q == 0) loss = fmaf(r, r, loss);
+      dy[o] = live ? 2.0f * r * scale : 0.0f;
+    }
+  }
+  if (L.q == 0) {
+#pragma unroll
+    for (int o = 0; o < kNOUT; ++o) {
+      T.a[o][L.c] = dy[o];
+      G.b3[o] += dy[o];
+    }
+  }
   __syncthreads();
-  const int s = blockIdx.x * kTB + threadIdx.x;
-  if (s >= n) return;
-  float dy[kNOUT], dz2[kNH];
+  // dW3 (rows 3 .. 15 of the product are zero)
 #pragma unroll
-  for (int o = 0; o < kNOUT; ++o) dy[o] = A.dy[(int64_t)o * n + s];
+  for (int w = 0; w < kNetWaves; ++w) {
+    floatx4 a = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (L.c < kNOUT) a = ld_f4(&TT[w].a[L.c][4 * L.q]);
+    const floatx4 b = ld_f4(&TT[w].b[16 * wave + L.c][4 * L.q]);
 #pragma unroll
-  for (int k = 0; k < kNH; ++k) {
-    float d = 0.0f;
-#pragma unroll
-    for (int o = 0; o < kNOUT; ++o) d = fmaf(P[kOffW3 + o * kNH + k], dy[o], d);
-    dz2[k] = d * A.g2[(int64_t)k * n + s];
-    A.dz2[(int64_t)k * n + s] = dz2[k];
+    for (int r = 0; r < 4; ++r)
+      G.w3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[r], G.w3, 0, 0, 0);
   }
-  for (int k = 0; k < kNH; ++k) {
-    float d = 0.0f;
+  // dz2 = (W3^T dy) gelu'(z2)
 #pragma unroll
-    for (int i = 0; i < kNH; ++i) d = fmaf(P[kOffW2 + i * kNH + k], dz2[i], d);
-    A.dz1[(int64_t)k * n + s] = d * A.g1[(int64_t)k * n + s];
+  for (int b = 0; b < 4; ++b) {
+    floatx4 d = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int o = 0; o < kNOUT; ++o) {
+      const floatx4 w = ld_f4(&W.w3[o][16 * b + 4 * L.q]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) d[r] = fmaf(w[r], dy[o], d[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z[b][r] *= d[r];
   }
+  __syncthreads();
+  // dW2 and db2
+  turn_in(T.a, z, L);
+  turn_in(T.b, h1, L);
+  __syncthreads();
+#pragma unroll 2
+  for (int w = 0; w < kNetWaves; ++w) {
+    const floatx4 a = ld_f4(&TT[w].a[16 * wave + L.c][4 * L.q]);
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+      const floatx4 b = ld_f4(&TT[w].b[16 * nb + L.c][4 * L.q]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        G.w2[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[r], G.w2[nb], 0, 0, 0);
+    }
+    G.b2 += (a[0] + a[1]) + (a[2] + a[3]);
+  }
+  // dz1 = (W2^T dz2) gelu'(z1); dW1 and db1
+  net_layer2_t(W, z, L, h1);
+#pragma unroll
+  for (int b = 0; b < 4; ++b) h1[b] *= g1[b];
+  __syncthreads();
+  turn_in(T.a, h1, L);
+  T.b[2 * L.q][L.c] = xh[0];
+  T.b[2 * L.q + 1][L.c] = xh[1];
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kNetWaves; ++w) {
+    const floatx4 a = ld_f4(&TT[w].a[16 * wave + L.c][4 * L.q]);
+    floatx4 b = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (L.c < kNIN) b = ld_f4(&TT[w].b[L.c][4 * L.q]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      G.w1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[r], G.w1, 0, 0, 0);
+    G.b1 += (a[0] + a[1]) + (a[2] + a[3]);
+  }
+  if (GX) net_rows3(W.w1t, h1, L, gx);
+  __syncthreads();
+}
+
+// The workgroup's accumulators in `out` (the parameter vector's order); b3: the
+// wavefronts' sums of dy.
+__device__ __forceinline__ void net_grad_out(const NetGrad &G, float *out, float (*b3)[kNOUT]) {
+  const NetLane L = net_lane();
+  const int wave = threadIdx.x >> 6;
+  float v1 = G.b1, v2 = G.b2;
+  v1 += __shfl_xor(v1, 16, 64);
+  v1 += __shfl_xor(v1, 32, 64);
+  v2 += __shfl_xor(v2, 16, 64);
+  v2 += __shfl_xor(v2, 32, 64);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = 4 * L.q + r;
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+      out[kOffW2 + (16 * wave + row) * kNH + 16 * nb + L.c] = G.w2[nb][r];
+    if (L.c < kNIN) out[kOffW1 + (16 * wave + row) * kNIN + L.c] = G.w1[r];
+    if (row < kNOUT) out[kOffW3 + row * kNH + 16 * wave + L.c] = G.w3[r];
+  }
+  if (L.q == 0) {
+    out[kOffB1 + 16 * wave + L.c] = v1;
+    out[kOffB2 + 16 * wave + L.c] = v2;
+  }
+#pragma unroll
+  for (int o = 0; o < kNOUT; ++o) {
+    float v = G.b3[o];  // samples of quarter 0
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    if ((threadIdx.x & 63) == 0) b3[wave][o] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < kNOUT) {
+    const int o = threadIdx.x;
+    out[kOffB3 + o] = (b3[0][o] + b3[1][o]) + (b3[2][o] + b3[3][o]);
+  }
+}
+
+// Parameter gradient of a batch: part[block][4931], and (apriori) the block's
+// sum of squared residuals.  NET_APRIORI: mean squared error against the
+// target tg over sigma_out.  NET_ONESTEP: dL/dD per sample (gE, SoA) from the
+// one-step stencil.  NET_FEEDBACK: the same through both network passes, the
+// second on the features shifted by q, the first with dL/dq = gE + dL/dx1.
+// Every sum has a fixed order: the samples of a workgroup's passes, then
+// (k_net_final) the workgroups.
+enum { NET_APRIORI = 0, NET_ONESTEP = 1, NET_FEEDBACK = 2 };
+template <int MODE>
+__global__ __launch_bounds__(kNetThreads, 2) void k_net_grad(
+    const float *__restrict__ p, const float *__restrict__ norm, const float *__restrict__ x,
+    const float *__restrict__ tg, const float *__restrict__ q, const float *__restrict__ gE, int n,
+    float tm1, float *__restrict__ part, float *__restrict__ loss_part) {
+  __shared__ NetLds W;
+  __shared__ NetTurn T[kNetWaves];
+  __shared__ float red[kNetWaves][kNOUT];
+  net_to_lds(W, p, norm);
+  const NetLane L = net_lane();
+  const int wave = threadIdx.x >> 6;
+  NetGrad G{};
+  float loss = 0.0f;
+  const float scale = 1.0f / (float)n;
+  const int groups = (n + kNetGroup - 1) / kNetGroup;
+  // the wavefronts of a workgroup stay together (barriers in net_reverse)
+  for (int g0 = blockIdx.x * kNetWaves; g0 < groups; g0 += gridDim.x * kNetWaves) {
+    const int64_t s = (int64_t)(g0 + wave) * kNetGroup + L.c;
+    const bool live = s < n;
+    const int64_t sc = live ? s : n - 1;
+    float xh[2], dy[kNOUT] = {0.0f, 0.0f, 0.0f}, t[kNOUT] = {0.0f, 0.0f, 0.0f};
+    float ge[kNOUT] = {0.0f, 0.0f, 0.0f}, gx[kNOUT];
+    if (MODE == NET_APRIORI) {
+#pragma unroll
+      for (int o = 0; o < kNOUT; ++o) t[o] = tg[sc * kNOUT + o] / W.so[o];
+    } else if (live) {
+#pragma unroll
+      for (int o = 0; o < kNOUT; ++o) ge[o] = gE[(int64_t)o * n + s];
+    }
+#pragma unroll 1
+    for (int pass = MODE == NET_FEEDBACK ? 1 : 0; pass >= 0; --pass) {
+      net_phase();
+      float qv[kNOUT] = {0.0f, 0.0f, 0.0f};
+      if (MODE == NET_FEEDBACK && pass == 1) {
+#pragma unroll
+        for (int o = 0; o < kNOUT; ++o) qv[o] = q[(int64_t)o * n + sc];
+      }
+      net_features(W, x, sc, L, qv, xh);
+      if (!live) xh[0] = xh[1] = 0.0f;  // finite whatever the sample, without effect: dy = 0
+      if (MODE != NET_APRIORI) {
+#pragma unroll
+        for (int o = 0; o < kNOUT; ++o)
+          dy[o] = W.so[o] * (MODE == NET_FEEDBACK && pass == 0 ? tm1 * ge[o] : ge[o]);
+      }
+      net_reverse<MODE == NET_APRIORI, MODE == NET_FEEDBACK>(W, T, G, xh, dy, t, scale, live, loss,
+                                                             gx);
+      if (MODE == NET_FEEDBACK) {
+#pragma unroll
+        for (int o = 0; o < kNOUT; ++o) ge[o] = live ? ge[o] + gx[o] / W.sigma[5 + o] : 0.0f;
+      }
+    }
+  }
+  net_grad_out(G, part + (int64_t)blockIdx.x * kNParam, red);
+  if (MODE == NET_APRIORI) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) loss += __shfl_xor(loss, off, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[wave][0] = loss;
+    __syncthreads();
+    if (threadIdx.x == 0) loss_part[blockIdx.x] = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
+  }
+}
+
+// grad = sum of the blocks' partial gradients (16 parameters x 16 slices of the
+// blocks per workgroup, FP64), loss = loss_scale * sum of loss_part (the last
+// workgroup, FP64).
+__global__ __launch_bounds__(256) void k_net_final(const float *__restrict__ part, int nparts,
+                                                   const float *__restrict__ loss_part, int nlb,
+                                                   double loss_scale, float *__restrict__ grad,
+                                                   float *__restrict__ loss) {
+  __shared__ double red[256];
+  const int t = threadIdx.x, j = t & 15, slice = t >> 4;
+  double a = 0.0;
+  if (blockIdx.x + 1 < gridDim.x) {
+    const int k = blockIdx.x * 16 + j;
+    if (k < kNParam)
+      for (int c = slice; c < nparts; c += 16) a += (double)part[(int64_t)c * kNParam + k];
+    red[t] = a;
+    __syncthreads();
+    if (slice == 0 && k < kNParam) {
+      for (int c = 1; c < 16; ++c) a += red[16 * c + j];
+      grad[k] = (float)a;
+    }
+    return;
+  }
+  if (!loss) return;
+  for (int c = t; c < nlb; c += 256) a += (double)loss_part[c];
+  red[t] = a;
+  __syncthreads();
+  for (int w = 128; w >= 1; w >>= 1) {
+    if (t < w) red[t] += red[t + w];
+    __syncthreads();
+  }
+  if (t == 0) *loss = (float)(red[0] * loss_scale);
 }
 
 // One-step objective, network-dependent part (FP32).  Node s of the batch is
-// node s % Nc of snapshot s / Nc (periodic nc x nc).  D = sigma_out * y with
-// y = A.dy from k_forward.  res[2][n] = r0 + sum_i c_i (1 - omega) w_i
-// R_i(u(X - c_i)) . D(X - c_i); loss_part = per-workgroup sums of |res|^2.
-// q (SoA [3][n], may be null) is added to D (feedback form: the restart's
-// extra non-equilibrium relaxes with the correction).
+// node s % Nc of snapshot s / Nc (periodic nc x nc).  D (SoA [3][n]): the
+// correction each node's collision relaxes.  res[2][n] = r0 + sum_i c_i (1 -
+// omega) w_i R_i(u(X - c_i)) . D(X - c_i); loss_part = per-workgroup sums of
+// |res|^2.
 __global__ __launch_bounds__(kTB) void k_onestep_fwd(const float *__restrict__ x,
-                                                     const float *__restrict__ r0,
-                                                     const float *__restrict__ norm, int nsnap,
-                                                     int nc, float om1, Acts A,
-                                                     const float *__restrict__ q,
+                                                     const float *__restrict__ r0, int nsnap,
+                                                     int nc, float om1,
+                                                     const float *__restrict__ D,
                                                      float *__restrict__ res,
                                                      float *__restrict__ loss_part) {
   __shared__ float red[kTB / 64];
@@ -343,21 +752,16 @@ __global__ __launch_bounds__(kTB) void k_onestep_fwd(const float *__restrict__ x
   if (s < n) {
     const int sn = s / Nc, c = s - sn * Nc;
     const int cy = c / nc, cx = c - cy * nc;
-    const float so0 = norm[2 * kNIN + 0], so1 = norm[2 * kNIN + 1], so2 = norm[2 * kNIN + 2];
     float jx = r0[2 * (int64_t)s], jy = r0[2 * (int64_t)s + 1];
 #pragma unroll
     for (int i = 1; i < 9; ++i) {
       const int yx = (cx - rr::cx(i) + nc) % nc, yy = (cy - rr::cy(i) + nc) % nc;
       const int qn = sn * Nc + yy * nc + yx;
       const float ux = x[(int64_t)qn * kNIN + 1], uy = x[(int64_t)qn * kNIN + 2];
-      float dxx = so0 * A.dy[qn], dxy = so1 * A.dy[(int64_t)n + qn],
-            dyy = so2 * A.dy[2 * (int64_t)n + qn];
-      if (q) {
-        dxx += q[qn];
-        dxy += q[(int64_t)n + qn];
-        dyy += q[2 * (int64_t)n + qn];
-      }
-      const float d = om1 * reg_expand<float>(i, ux, uy, dxx, dxy, dyy) / wdiv(i);
+      const float d = om1 *
+                      reg_expand<float>(i, ux, uy, D[qn], D[(int64_t)n + qn],
+                                        D[2 * (int64_t)n + qn]) /
+                      wdiv(i);
       if (rr::cx(i)) jx = fmaf((float)rr::cx(i), d, jx);
       if (rr::cy(i)) jy = fmaf((float)rr::cy(i), d, jy);
     }
@@ -372,13 +776,10 @@ __global__ __launch_bounds__(kTB) void k_onestep_fwd(const float *__restrict__ x
   if (threadIdx.x == 0) loss_part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// Transpose stencil: dL/dy_k(Y) = sigma_out_k scale om1 sum_i (c_i . res(Y +
-// c_i)) w_i dR_i/dD_k(u(Y)), scale = 2 / den; written to A.dy (the outputs
-// it overwrites are no longer needed).
-// gE (SoA [3][n], may be null) receives dL/dD itself (before sigma_out).
-__global__ __launch_bounds__(kTB) void k_onestep_adj(const float *__restrict__ x,
-                                                     const float *__restrict__ norm, int nsnap,
-                                                     int nc, float om1, float scale, Acts A,
+// Transpose stencil: dL/dD_k(Y) = scale om1 sum_i (c_i . res(Y + c_i)) w_i
+// dR_i/dD_k(u(Y)), scale = 2 / den, SoA [3][n].
+__global__ __launch_bounds__(kTB) void k_onestep_adj(const float *__restrict__ x, int nsnap,
+                                                     int nc, float om1, float scale,
                                                      const float *__restrict__ res,
                                                      float *__restrict__ gE) {
   const int Nc = nc * nc, n = nsnap * Nc;
@@ -399,150 +800,9 @@ __global__ __launch_bounds__(kTB) void k_onestep_adj(const float *__restrict__ x
     gyy = fmaf(m, reg_expand<float>(i, ux, uy, 0.0f, 0.0f, 1.0f), gyy);
   }
   const float k = scale * om1;
-  A.dy[s] = norm[2 * kNIN + 0] * k * gxx;
-  A.dy[(int64_t)n + s] = norm[2 * kNIN + 1] * k * gxy;
-  A.dy[2 * (int64_t)n + s] = norm[2 * kNIN + 2] * k * gyy;
-  if (gE) {
-    gE[s] = k * gxx;
-    gE[(int64_t)n + s] = k * gxy;
-    gE[2 * (int64_t)n + s] = k * gyy;
-  }
-}
-
-// Feedback form, first network pass done (outputs y0 in A0.dy): the
-// restart's extra non-equilibrium q = (tau_c - 1) sigma_out y0 (SoA), and
-// the features x1 of that restart (a_1^(2) entries shifted by q).
-__global__ __launch_bounds__(kTB) void k_feedback_x1(const float *__restrict__ x,
-                                                     const float *__restrict__ norm, int n,
-                                                     float tm1, Acts A0, float *__restrict__ q,
-                                                     float *__restrict__ x1) {
-  const int s = blockIdx.x * kTB + threadIdx.x;
-  if (s >= n) return;
-#pragma unroll
-  for (int k = 0; k < 5; ++k) x1[(int64_t)s * kNIN + k] = x[(int64_t)s * kNIN + k];
-#pragma unroll
-  for (int o = 0; o < kNOUT; ++o) {
-    const float v = tm1 * (norm[2 * kNIN + o] * A0.dy[(int64_t)o * n + s]);
-    q[(int64_t)o * n + s] = v;
-    x1[(int64_t)s * kNIN + 5 + o] = x[(int64_t)s * kNIN + 5 + o] + v;
-  }
-}
-
-// Feedback form, after reverse mode through the second pass (dz1 in A1):
-// dL/dq = gE + dL/dx1 (a_1^(2) entries, through the second pass's input),
-// and the first pass's output gradient dL/dy0 = sigma_out (tau_c - 1) dL/dq.
-__global__ __launch_bounds__(kTB) void k_feedback_back(const float *__restrict__ p,
-                                                       const float *__restrict__ norm, int n,
-                                                       float tm1, Acts A1,
-                                                       const float *__restrict__ gE, Acts A0) {
-  __shared__ float W1[kNH * kNIN];
-  for (int k = threadIdx.x; k < kNH * kNIN; k += kTB) W1[k] = p[kOffW1 + k];
-  __syncthreads();
-  const int s = blockIdx.x * kTB + threadIdx.x;
-  if (s >= n) return;
-  float g[kNOUT] = {0.0f, 0.0f, 0.0f};
-  for (int i = 0; i < kNH; ++i) {
-    const float d = A1.dz1[(int64_t)i * n + s];
-#pragma unroll
-    for (int o = 0; o < kNOUT; ++o) g[o] = fmaf(W1[i * kNIN + 5 + o], d, g[o]);
-  }
-#pragma unroll
-  for (int o = 0; o < kNOUT; ++o) {
-    const float gq = gE[(int64_t)o * n + s] + g[o] / norm[kNIN + 5 + o];
-    A0.dy[(int64_t)o * n + s] = norm[2 * kNIN + o] * (tm1 * gq);
-  }
-}
-
-// Gradient reduction: out[chunk][param] = sum over the chunk's samples of
-// the per-sample contribution, in a fixed order.  Parameter p of a weight
-// matrix is (row i, column k): dW = sum_s delta_i(s) act_k(s); biases use
-// act = 1.  Each block handles one chunk of kChunk samples and 256
-// parameters.
-constexpr int kChunk = 1024;
-
-__device__ __forceinline__ void param_operands(int q, const Acts &A, const float *&dl,
-                                               const float *&ac) {
-  // returns the delta row and activation row (nullptr = bias) of parameter q
-  if (q < kOffB1) {
-    dl = A.dz1 + 0;
-    ac = A.xh;
-  } else if (q < kOffW2) {
-    dl = A.dz1;
-    ac = nullptr;
-  } else if (q < kOffB2) {
-    dl = A.dz2;
-    ac = A.h1;
-  } else if (q < kOffW3) {
-    dl = A.dz2;
-    ac = nullptr;
-  } else if (q < kOffB3) {
-    dl = A.dy;
-    ac = A.h2;
-  } else {
-    dl = A.dy;
-    ac = nullptr;
-  }
-}
-
-__global__ __launch_bounds__(kTB) void k_grad_chunks(int n, Acts A, float *__restrict__ part) {
-  const int q = blockIdx.y * kTB + threadIdx.x;
-  if (q >= kNParam) return;
-  int row, col, ncol;
-  const float *dl, *ac;
-  param_operands(q, A, dl, ac);
-  if (q < kOffB1) {
-    row = q / kNIN;
-    col = q % kNIN;
-    ncol = kNIN;
-  } else if (q < kOffW2) {
-    row = q - kOffB1;
-    col = 0;
-    ncol = 0;
-  } else if (q < kOffB2) {
-    row = (q - kOffW2) / kNH;
-    col = (q - kOffW2) % kNH;
-    ncol = kNH;
-  } else if (q < kOffW3) {
-    row = q - kOffB2;
-    col = 0;
-    ncol = 0;
-  } else if (q < kOffB3) {
-    row = (q - kOffW3) / kNH;
-    col = (q - kOffW3) % kNH;
-    ncol = kNH;
-  } else {
-    row = q - kOffB3;
-    col = 0;
-    ncol = 0;
-  }
-  (void)ncol;
-  const int64_t s0 = (int64_t)blockIdx.x * kChunk;
-  const int64_t s1 = s0 + kChunk < n ? s0 + kChunk : n;
-  const float *drow = dl + (int64_t)row * n;
-  float acc = 0.0f;
-  if (ac) {
-    const float *arow = ac + (int64_t)col * n;
-    for (int64_t s = s0; s < s1; ++s) acc = fmaf(drow[s], arow[s], acc);
-  } else {
-    for (int64_t s = s0; s < s1; ++s) acc += drow[s];
-  }
-  part[(int64_t)blockIdx.x * kNParam + q] = acc;
-}
-
-__global__ void k_grad_final(const float *__restrict__ part, int nchunks,
-                             const float *__restrict__ loss_part, int nlb, double loss_scale,
-                             float *__restrict__ grad, float *__restrict__ loss) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < kNParam) {
-    float s = 0.0f;
-    for (int c = 0; c < nchunks; ++c) s += part[(int64_t)c * kNParam + q];
-    grad[q] = s;
-  }
-  if (q == 0 && loss) {
-    double l = 0.0;
-    for (int b = 0; b < nlb; ++b) l += loss_part[b];
-    *loss = (float)(l * loss_scale);
-  }
+  gE[s] = k * gxx;
+  gE[(int64_t)n + s] = k * gxy;
+  gE[2 * (int64_t)n + s] = k * gyy;
 }
 
 __global__ void k_adam(float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
@@ -603,16 +863,19 @@ extern "C" RR_HIDDEN int rr_launch_impose_fluid(int storage, const rr::Domain *D
 // ---------------------------------------------------------------------------
 // C-ABI
 // ---------------------------------------------------------------------------
+// Workgroups of the network kernels, at most one per 64 samples: two per CU in
+// the reverse pass (LDS), four in the forward one (registers).
+static int net_blocks(int64_t n, int most = 512) {
+  const int64_t per = rr::kNetWaves * rr::kNetGroup, b = (n + per - 1) / per;
+  return (int)(b < most ? b : most);
+}
+
 struct rrmhd_trainer {
   int64_t cap = 0;
   hipStream_t st = nullptr;
-  float *acts = nullptr;  // SoA activations
-  float *part = nullptr;  // [chunks][4931]
-  float *loss_part = nullptr;
-  float *res = nullptr;  // one-step residuals [2][cap]
-  float *acts2 = nullptr;  // second activation set (feedback form)
-  float *fb = nullptr;     // feedback form: x1 [cap][8], q [3][cap], gE [3][cap]
-  rr::Acts A{};
+  float *part = nullptr;       // [blocks][4931] partial gradients
+  float *loss_part = nullptr;  // partial losses
+  float *node = nullptr;       // per sample: D [3], q [3], residual [2], dL/dD [3] (SoA)
 };
 
 namespace {
@@ -633,12 +896,9 @@ extern "C" {
 int rrmhd_train_destroy(rrmhd_trainer *t) {
   if (!t) return RRMHD_OK;
   (void)hipStreamSynchronize(t->st);
-  if (t->acts) (void)hipFree(t->acts);
   if (t->part) (void)hipFree(t->part);
   if (t->loss_part) (void)hipFree(t->loss_part);
-  if (t->res) (void)hipFree(t->res);
-  if (t->acts2) (void)hipFree(t->acts2);
-  if (t->fb) (void)hipFree(t->fb);
+  if (t->node) (void)hipFree(t->node);
   delete t;
   return RRMHD_OK;
 }
@@ -651,16 +911,13 @@ int rrmhd_train_create(int64_t max_batch, void *hip_stream, rrmhd_trainer **out)
   if (!t) return RRMHD_ENOMEM;
   t->cap = max_batch;
   t->st = (hipStream_t)hip_stream;
-  const int64_t per = rr::kNIN + 4 * rr::kNH + rr::kNOUT + 2 * rr::kNH;
-  const int64_t chunks = (max_batch + rr::kChunk - 1) / rr::kChunk;
-  const int64_t lblocks = (max_batch + rr::kTB - 1) / rr::kTB;
-  hipError_t e = hipMalloc((void **)&t->acts, sizeof(float) * per * max_batch);
-  // two chunk sets: the feedback form reduces two activation sets
-  if (e == hipSuccess) e = hipMalloc((void **)&t->part, sizeof(float) * 2 * chunks * rr::kNParam);
+  // partial losses: of the stencil's workgroups, or of the network's
+  int64_t lblocks = (max_batch + rr::kTB - 1) / rr::kTB;
+  if (lblocks < net_blocks(max_batch)) lblocks = net_blocks(max_batch);
+  hipError_t e = hipMalloc((void **)&t->part,
+                           sizeof(float) * (int64_t)net_blocks(max_batch) * rr::kNParam);
   if (e == hipSuccess) e = hipMalloc((void **)&t->loss_part, sizeof(float) * lblocks);
-  if (e == hipSuccess) e = hipMalloc((void **)&t->res, sizeof(float) * 2 * max_batch);
-  if (e == hipSuccess) e = hipMalloc((void **)&t->acts2, sizeof(float) * per * max_batch);
-  if (e == hipSuccess) e = hipMalloc((void **)&t->fb, sizeof(float) * 14 * max_batch);
+  if (e == hipSuccess) e = hipMalloc((void **)&t->node, sizeof(float) * 11 * max_batch);
   if (e != hipSuccess) {
     int rc = terr(e, "hipMalloc(trainer)");
     rrmhd_train_destroy(t);
@@ -672,42 +929,12 @@ int rrmhd_train_create(int64_t max_batch, void *hip_stream, rrmhd_trainer **out)
 
 }  // extern "C"
 
-// SoA activation arrays of a batch of n samples inside the trainer's buffer.
-static rr::Acts acts_of(const rrmhd_trainer *t, int64_t N, bool second = false) {
-  float *a = second ? t->acts2 : t->acts;
-  rr::Acts A;
-  A.xh = a;
-  a += rr::kNIN * N;
-  A.h1 = a;
-  a += rr::kNH * N;
-  A.g1 = a;
-  a += rr::kNH * N;
-  A.h2 = a;
-  a += rr::kNH * N;
-  A.g2 = a;
-  a += rr::kNH * N;
-  A.dy = a;
-  a += rr::kNOUT * N;
-  A.dz1 = a;
-  a += rr::kNH * N;
-  A.dz2 = a;
-  return A;
-}
-
-// Reverse mode from dL/dy in A.dy to the parameter gradient, and the loss
-// from the per-workgroup partial sums.
-static int backward_and_reduce(rrmhd_trainer *t, const float *params, const rr::Acts &A,
-                               int64_t n, int nlb, double loss_scale, float *grad,
-                               float *loss) {
-  const int nb = (int)((n + rr::kTB - 1) / rr::kTB);
-  const int nch = (int)((n + rr::kChunk - 1) / rr::kChunk);
-  hipLaunchKernelGGL(rr::k_backward, dim3(nb), dim3(rr::kTB), 0, t->st, params, (int)n, A);
-  THIP(hipGetLastError());
-  hipLaunchKernelGGL(rr::k_grad_chunks, dim3(nch, (rr::kNParam + rr::kTB - 1) / rr::kTB),
-                     dim3(rr::kTB), 0, t->st, (int)n, A, t->part);
-  THIP(hipGetLastError());
-  hipLaunchKernelGGL(rr::k_grad_final, dim3((rr::kNParam + 255) / 256), dim3(256), 0, t->st,
-                     t->part, nch, t->loss_part, nlb, loss_scale, grad, loss);
+// The partial gradients summed, and the loss.
+static int net_final(rrmhd_trainer *t, int nparts, int nlb, double loss_scale, float *grad,
+                     float *loss) {
+  hipLaunchKernelGGL(rr::k_net_final, dim3((rr::kNParam + 15) / 16 + 1), dim3(256), 0, t->st,
+                     (const float *)t->part, nparts, (const float *)t->loss_part, nlb, loss_scale,
+                     grad, loss);
   THIP(hipGetLastError());
   return RRMHD_OK;
 }
@@ -719,12 +946,12 @@ int rrmhd_train_loss_grad(rrmhd_trainer *t, const float *params, const float *no
                           float *loss) {
   if (!t || !params || !norm || !x || !target || !grad || n < 1 || n > t->cap)
     return RRMHD_EINVAL;
-  const rr::Acts A = acts_of(t, n);
-  const int nb = (int)((n + rr::kTB - 1) / rr::kTB);
-  hipLaunchKernelGGL(rr::k_forward, dim3(nb), dim3(rr::kTB), 0, t->st, params, norm, x, target,
-                     (int)n, A, t->loss_part);
+  const int nb = net_blocks(n);
+  hipLaunchKernelGGL(rr::k_net_grad<rr::NET_APRIORI>, dim3(nb), dim3(rr::kNetThreads), 0, t->st,
+                     params, norm, x, target, (const float *)nullptr, (const float *)nullptr,
+                     (int)n, 0.0f, t->part, t->loss_part);
   THIP(hipGetLastError());
-  return backward_and_reduce(t, params, A, n, nb, 1.0 / (double)n, grad, loss);
+  return net_final(t, nb, nb, 1.0 / (double)n, grad, loss);
 }
 
 int rrmhd_train_onestep_loss_grad(rrmhd_trainer *t, const float *params, const float *norm,
@@ -736,56 +963,34 @@ int rrmhd_train_onestep_loss_grad(rrmhd_trainer *t, const float *params, const f
     return RRMHD_EINVAL;
   const int64_t n = (int64_t)nsnap * nc * nc;
   if (n > t->cap || n > INT32_MAX) return RRMHD_EINVAL;
-  const int nb = (int)((n + rr::kTB - 1) / rr::kTB);
-  const float om1 = (float)(1.0 - 1.0 / tau_c);
-  const rr::Acts A = acts_of(t, n);
-  hipLaunchKernelGGL(rr::k_forward, dim3(nb), dim3(rr::kTB), 0, t->st, params, norm, x,
-                     (const float *)nullptr, (int)n, A, t->loss_part);
+  const int nb = (int)((n + rr::kTB - 1) / rr::kTB), ng = net_blocks(n);
+  const int nf = net_blocks(n, 1024);
+  const float om1 = (float)(1.0 - 1.0 / tau_c), tm1 = (float)(tau_c - 1.0);
+  const dim3 net(rr::kNetThreads);
+  float *D = t->node, *q = D + 3 * n, *res = q + 3 * n, *gE = res + 2 * n;
+  if (feedback)
+    hipLaunchKernelGGL(rr::k_net_forward<true>, dim3(nf), net, 0, t->st, params, norm, x, (int)n,
+                       tm1, q, D);
+  else
+    hipLaunchKernelGGL(rr::k_net_forward<false>, dim3(nf), net, 0, t->st, params, norm, x, (int)n,
+                       tm1, q, D);
   THIP(hipGetLastError());
-  if (!feedback) {
-    hipLaunchKernelGGL(rr::k_onestep_fwd, dim3(nb), dim3(rr::kTB), 0, t->st, x, r0, norm,
-                       nsnap, nc, om1, A, (const float *)nullptr, t->res, t->loss_part);
-    THIP(hipGetLastError());
-    hipLaunchKernelGGL(rr::k_onestep_adj, dim3(nb), dim3(rr::kTB), 0, t->st, x, norm, nsnap,
-                       nc, om1, (float)(2.0 / den), A, (const float *)t->res, (float *)nullptr);
-    THIP(hipGetLastError());
-    return backward_and_reduce(t, params, A, n, nb, 1.0 / den, grad, loss);
-  }
-  // feedback form: pass 0 on the Chapman-Enskog features (A), pass 1 on the
-  // features of the restart carrying q = (tau_c - 1) D0 (A1)
-  const float tm1 = (float)(tau_c - 1.0);
-  const rr::Acts A1 = acts_of(t, n, true);
-  float *x1 = t->fb, *q = t->fb + 8 * n, *gE = t->fb + 11 * n;
-  hipLaunchKernelGGL(rr::k_feedback_x1, dim3(nb), dim3(rr::kTB), 0, t->st, x, norm, (int)n, tm1,
-                     A, q, x1);
+  hipLaunchKernelGGL(rr::k_onestep_fwd, dim3(nb), dim3(rr::kTB), 0, t->st, x, r0, nsnap, nc, om1,
+                     (const float *)D, res, t->loss_part);
   THIP(hipGetLastError());
-  hipLaunchKernelGGL(rr::k_forward, dim3(nb), dim3(rr::kTB), 0, t->st, params, norm,
-                     (const float *)x1, (const float *)nullptr, (int)n, A1, t->loss_part);
+  hipLaunchKernelGGL(rr::k_onestep_adj, dim3(nb), dim3(rr::kTB), 0, t->st, x, nsnap, nc, om1,
+                     (float)(2.0 / den), (const float *)res, gE);
   THIP(hipGetLastError());
-  hipLaunchKernelGGL(rr::k_onestep_fwd, dim3(nb), dim3(rr::kTB), 0, t->st, (const float *)x1, r0,
-                     norm, nsnap, nc, om1, A1, (const float *)q, t->res, t->loss_part);
+  if (feedback)
+    hipLaunchKernelGGL(rr::k_net_grad<rr::NET_FEEDBACK>, dim3(ng), net, 0, t->st, params, norm, x,
+                       (const float *)nullptr, (const float *)q, (const float *)gE, (int)n, tm1,
+                       t->part, (float *)nullptr);
+  else
+    hipLaunchKernelGGL(rr::k_net_grad<rr::NET_ONESTEP>, dim3(ng), net, 0, t->st, params, norm, x,
+                       (const float *)nullptr, (const float *)nullptr, (const float *)gE, (int)n,
+                       tm1, t->part, (float *)nullptr);
   THIP(hipGetLastError());
-  hipLaunchKernelGGL(rr::k_onestep_adj, dim3(nb), dim3(rr::kTB), 0, t->st, (const float *)x1,
-                     norm, nsnap, nc, om1, (float)(2.0 / den), A1, (const float *)t->res, gE);
-  THIP(hipGetLastError());
-  hipLaunchKernelGGL(rr::k_backward, dim3(nb), dim3(rr::kTB), 0, t->st, params, (int)n, A1);
-  THIP(hipGetLastError());
-  hipLaunchKernelGGL(rr::k_feedback_back, dim3(nb), dim3(rr::kTB), 0, t->st, params, norm, (int)n,
-                     tm1, A1, (const float *)gE, A);
-  THIP(hipGetLastError());
-  hipLaunchKernelGGL(rr::k_backward, dim3(nb), dim3(rr::kTB), 0, t->st, params, (int)n, A);
-  THIP(hipGetLastError());
-  const int nch = (int)((n + rr::kChunk - 1) / rr::kChunk);
-  const dim3 gq(nch, (rr::kNParam + rr::kTB - 1) / rr::kTB);
-  hipLaunchKernelGGL(rr::k_grad_chunks, gq, dim3(rr::kTB), 0, t->st, (int)n, A, t->part);
-  THIP(hipGetLastError());
-  hipLaunchKernelGGL(rr::k_grad_chunks, gq, dim3(rr::kTB), 0, t->st, (int)n, A1,
-                     t->part + (int64_t)nch * rr::kNParam);
-  THIP(hipGetLastError());
-  hipLaunchKernelGGL(rr::k_grad_final, dim3((rr::kNParam + 255) / 256), dim3(256), 0, t->st,
-                     t->part, 2 * nch, t->loss_part, nb, 1.0 / den, grad, loss);
-  THIP(hipGetLastError());
-  return RRMHD_OK;
+  return net_final(t, ng, nb, 1.0 / den, grad, loss);
 }
 
 int rrmhd_train_adam(rrmhd_trainer *t, float *params, float *m, float *v, const float *grad,
