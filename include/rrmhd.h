@@ -354,7 +354,11 @@ int rrmhd_batch_create(int n, const rrmhd_grid *grids, const double *tau_f,
                        rrmhd_batch **out);
 /* Equilibrium initial state of domain d (as rrmhd_init). */
 int rrmhd_batch_init(rrmhd_batch *b, int d, const double *u, const double *bf);
-/* Advance every domain n steps (all domains must have been initialised). */
+/* Advance every domain n steps (all domains must have been initialised).  With
+ * the default launch a pass over the ensemble takes two to five steps where
+ * there is a form for it, bit for bit the same as one step per pass; after
+ * rrmhd_batch_set_shape or _set_fetch a pass is one step of the kernel whose
+ * shape and schedule they choose. */
 int rrmhd_batch_step(rrmhd_batch *b, int64_t n);
 /* Steps per captured hipGraph (0: plain launches, the default). */
 int rrmhd_batch_set_graph_chunk(rrmhd_batch *b, int chunk);
@@ -516,7 +520,7 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
 /* Ensemble version: a tile width for every distinct domain size (timed on a
  * standalone grid of that size) and then the work distribution (workgroup
  * count and static or dynamic schedule, timed on the ensemble, state
- * preserved); same cache file. */
+ * preserved), and that against the default launch; same cache file. */
 int rrmhd_batch_autotune(rrmhd_batch *b, const char *cache_path, int trials);
 
 /* Measurement helper, not part of the method: copies `bytes` (a multiple of

@@ -13,6 +13,7 @@
 // into one hipGraph and launched at once.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -22,6 +23,7 @@
 #include "../../include/rrmhd.h"
 #include "rr_internal.h"
 #include "rr_kernels.h"
+#include "rr_multi.h"
 #include "rr_node.h"
 #include "rr_pull.h"
 
@@ -35,6 +37,10 @@ struct BatchDom {
   int bx, by;  // tile shape, bx * by = 256
   int tiles_x;
   int tile_first;
+  // several steps per pass: marching windows of `out` nodes (nw per row) times
+  // strips of `rows` rows, or square tiles (mt_x per row); workgroups from wg_first
+  int nw, out, rows, mt_x;
+  int wg_first;
 };
 
 // One step of the whole ensemble.  Static schedule (per_fetch = 0): workgroup
@@ -114,6 +120,50 @@ __global__ __launch_bounds__(256) void k_batch_step(const BatchDom *__restrict__
   }
 }
 
+// Several steps of the whole ensemble in one pass (rr_multi.h): workgroup L
+// belongs to domain wg_dom[L].  Marching: its four wavefronts take four
+// consecutive (strip, window) units of the domain, all with the domain's rows
+// per strip (the march holds barriers); units past the domain's last store
+// nothing.
+template <class C, int T>
+__global__ __launch_bounds__(256) void k_batch_march(const BatchDom *__restrict__ doms,
+                                                     const int *__restrict__ wg_dom, float s,
+                                                     float inv_s,
+                                                     const typename C::T *__restrict__ src,
+                                                     typename C::T *__restrict__ dst) {
+  const int L = xcd_local(blockIdx.x, gridDim.x);
+  const BatchDom D = doms[__builtin_amdgcn_readfirstlane(wg_dom[L])];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int unit = (L - D.wg_first) * 4 + wave;
+  const int ts = unit / D.nw, tx = unit - ts * D.nw;
+  const int x0 = tx * D.out - kMarchHalo + lane;
+  const bool live = lane >= kMarchHalo && lane < kMarchHalo + D.out && x0 < D.nx;
+  const CollideParams P{D.om_c, D.omm_c, 0.0f, 0.0f, 0.0f};
+  const PlaneGeom G{D.plane, D.nx, D.ny, s, inv_s, 0u, (int64_t)D.nx};  // planes of [ny][nx]
+  march_strip<C, T>(G, P, src + D.base, dst + D.base, x0, live, ts * D.rows, D.rows);
+}
+
+template <class C, int B>
+__global__ __launch_bounds__(B *B) void k_batch_tiles(const BatchDom *__restrict__ doms,
+                                                      const int *__restrict__ wg_dom, int T,
+                                                      float s, float inv_s,
+                                                      const typename C::T *__restrict__ src,
+                                                      typename C::T *__restrict__ dst) {
+  __shared__ float ex[2][kMoving][B * B];
+  const BatchDom W = doms[__builtin_amdgcn_readfirstlane(wg_dom[blockIdx.x])];
+  Domain D{};
+  D.nx = W.nx;
+  D.ny = W.ny;
+  D.plane = W.plane;
+  D.row = W.nx;
+  D.om_c = W.om_c;
+  D.omm_c = W.omm_c;
+  D.s = s;
+  D.inv_s = inv_s;
+  const int t = (int)blockIdx.x - W.wg_first, ty = t / W.mt_x, tx = t - ty * W.mt_x;
+  tile_steps<C, B, false, false>(D, ex, tx, ty, T, src + W.base, dst + W.base);
+}
+
 }  // namespace rr
 
 namespace {
@@ -155,8 +205,15 @@ struct rrmhd_batch {
   hipStream_t user = nullptr;  // caller's stream
   hipStream_t own = nullptr;   // internal stream for graph launches
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
+  // several steps per pass (off once a shape or schedule of the one-step
+  // kernel was chosen): multi_steps per pass (1: no form), in square tiles of
+  // side multi_tile or (0) marching, multi_wgs workgroups in d_wg_dom
+  bool multi = true;
+  int multi_steps = 1, multi_tile = 0, multi_wgs = 0;
+  int *d_wg_dom = nullptr;
   int graph_chunk = 0;
-  hipGraphExec_t graph[2] = {nullptr, nullptr};  // by starting parity
+  hipGraphExec_t graph[2] = {nullptr, nullptr};  // by starting buffer
+  int graph_flip[2] = {0, 0};  // whether a replay of it ends in the other buffer
   void *diag_work = nullptr;
   size_t diag_bytes = 0;
   double *diag_out = nullptr, *diag_host = nullptr;
@@ -233,6 +290,114 @@ static hipError_t launch_one(rrmhd_batch *b, hipStream_t st) {
   return hipGetLastError();
 }
 
+// The multi-step form of the ensemble (fills the domains' fields and the
+// workgroup list): the smallest square tiles that are at most one per CU (bound
+// by latency), else the faster estimate of 32 x 32 tiles and marching strips,
+// if that beats one step per launch.  21 domains of sides 64 .. 1024 (7.5 M
+// nodes, FP32): 91 us per step marching against 218 one step at a time; 256
+// domains (90.9 M nodes): 873 against 2450.
+static int plan_multi(rrmhd_batch *b) {
+  auto tiles = [&](int B, int T) {
+    const int64_t out = B - 2 * (T - 1);
+    int64_t k = 0;
+    for (const rr::BatchDom &D : b->doms) k += (D.nx + out - 1) / out * ((D.ny + out - 1) / out);
+    return k;
+  };
+  double bytes = 0.0;
+  bool fits = true;  // indices of a window or tile stay far from 2^31
+  for (const rr::BatchDom &D : b->doms) {
+    bytes += (double)D.nx * D.ny * b->elem * rr::kStatePlanes;
+    fits = fits && D.nx <= (1 << 30) && D.ny <= (1 << 30);
+  }
+  b->multi_steps = 1;
+  if (!fits) return RRMHD_OK;
+  const double single = rr::single_us(bytes);
+  int tile = 0, T = 5, rows = 0;
+  if (tiles(16, 5) <= rr::kCUs) {
+    tile = 16;
+  } else if (tiles(24, 5) <= rr::kCUs) {
+    tile = 24;
+  } else {
+    const double q5 = std::ceil((double)tiles(32, 5) / rr::kCUs);
+    const double q4 = std::ceil((double)tiles(32, 4) / rr::kCUs);
+    double best = rr::tile32_us(5, q5) / 5;
+    tile = 32;
+    if (rr::tile32_us(4, q4) / 4 < best) {
+      best = rr::tile32_us(4, q4) / 4;
+      T = 4;
+    }
+    for (int r : {4, 6, 8, 11, 16, 23, 32, 45, 64, 91, 128}) {
+      int64_t wgs = 0;
+      for (const rr::BatchDom &D : b->doms)
+        wgs += ((int64_t)rr::march_windows(D.nx).n * ((D.ny + r - 1) / r) + 3) / 4;
+      const double us = rr::march_us((double)wgs / rr::kCUs, r) / 4;
+      if (us < best) {
+        best = us;
+        tile = 0;
+        T = 4;
+        rows = r;
+      }
+    }
+    if (best > 1.1 * single) return RRMHD_OK;
+  }
+  std::vector<int> wg;
+  for (int d = 0; d < b->n; ++d) {
+    rr::BatchDom &D = b->doms[d];
+    D.wg_first = (int)wg.size();
+    int64_t k;
+    if (tile) {
+      const int out = tile - 2 * (T - 1);
+      D.mt_x = (D.nx + out - 1) / out;
+      k = (int64_t)D.mt_x * ((D.ny + out - 1) / out);
+    } else {
+      const rr::MarchWindows w = rr::march_windows(D.nx);
+      const int strips = (D.ny + rows - 1) / rows;
+      D.nw = w.n;
+      D.out = w.out;
+      D.rows = (D.ny + strips - 1) / strips;
+      k = ((int64_t)w.n * strips + 3) / 4;
+    }
+    wg.insert(wg.end(), (size_t)k, d);
+  }
+  b->multi_steps = T;
+  b->multi_tile = tile;
+  b->multi_wgs = (int)wg.size();
+  BHIP(hipMalloc((void **)&b->d_wg_dom, sizeof(int) * wg.size()));
+  BHIP(hipMemcpy(b->d_wg_dom, wg.data(), sizeof(int) * wg.size(), hipMemcpyHostToDevice));
+  return RRMHD_OK;
+}
+
+template <class C>
+static void launch_multi_t(const rrmhd_batch *b, int T, hipStream_t st) {
+  using E = typename C::T;
+  auto src = (const E *)b->buf[b->cur];
+  auto dst = (E *)b->buf[b->cur ^ 1];
+  const dim3 grid(b->multi_wgs);
+#define RR_LAUNCH(kernel, block, ...) \
+  hipLaunchKernelGGL((kernel), grid, dim3(block), 0, st, b->d_doms, b->d_wg_dom, __VA_ARGS__)
+  if (b->multi_tile == 16)
+    RR_LAUNCH((rr::k_batch_tiles<C, 16>), 256, T, b->s, b->inv_s, src, dst);
+  else if (b->multi_tile == 24)
+    RR_LAUNCH((rr::k_batch_tiles<C, 24>), 576, T, b->s, b->inv_s, src, dst);
+  else if (b->multi_tile == 32)
+    RR_LAUNCH((rr::k_batch_tiles<C, 32>), 1024, T, b->s, b->inv_s, src, dst);
+  else if (T == 4)
+    RR_LAUNCH((rr::k_batch_march<C, 4>), 256, b->s, b->inv_s, src, dst);
+  else if (T == 3)
+    RR_LAUNCH((rr::k_batch_march<C, 3>), 256, b->s, b->inv_s, src, dst);
+  else
+    RR_LAUNCH((rr::k_batch_march<C, 2>), 256, b->s, b->inv_s, src, dst);
+#undef RR_LAUNCH
+}
+
+static hipError_t launch_multi(const rrmhd_batch *b, int T, hipStream_t st) {
+  if (b->storage == RRMHD_STORE_F16)
+    launch_multi_t<rr::CodecF16U>(b, T, st);
+  else
+    launch_multi_t<rr::CodecF32>(b, T, st);
+  return hipGetLastError();
+}
+
 static rr::Domain domain_of(const rrmhd_batch *b, int d) {
   const rr::BatchDom &B = b->doms[d];
   rr::Domain D{};
@@ -260,6 +425,7 @@ int rrmhd_batch_destroy(rrmhd_batch *b) {
     if (p) (void)hipFree(p), p = nullptr;
   if (b->d_doms) (void)hipFree(b->d_doms);
   if (b->d_tile_dom) (void)hipFree(b->d_tile_dom);
+  if (b->d_wg_dom) (void)hipFree(b->d_wg_dom);
   if (b->d_ctr) (void)hipFree(b->d_ctr);
   if (b->diag_work) (void)hipFree(b->diag_work);
   if (b->diag_out) (void)hipFree(b->diag_out);
@@ -333,6 +499,7 @@ int rrmhd_batch_create(int n, const rrmhd_grid *grids, const double *tau_f,
   chk(hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming), "hipEventCreate");
   chk(hipEventCreateWithFlags(&b->ev_out, hipEventDisableTiming), "hipEventCreate");
   b->grid = -1;  // one workgroup per tile
+  if (rc == RRMHD_OK) rc = plan_multi(b);
   if (rc == RRMHD_OK) rc = upload_tiles(b);
   if (rc != RRMHD_OK) {
     rrmhd_batch_destroy(b);
@@ -363,21 +530,30 @@ int rrmhd_batch_set_shape(rrmhd_batch *b, int d, int bx, int grid, int nt) {
   }
   if (grid) b->grid = grid;
   if (nt >= 0) b->nt = nt ? 1 : 0;
+  b->multi = false;
   return upload_tiles(b);
 }
 
 int rrmhd_batch_set_fetch(rrmhd_batch *b, int tiles_per_fetch) {
   if (!b || tiles_per_fetch < 0 || tiles_per_fetch > 64) return RRMHD_EINVAL;
   b->per_fetch = tiles_per_fetch;
+  b->multi = false;
   free_graphs(b);
   return RRMHD_OK;
 }
 
 static int plain_steps(rrmhd_batch *b, int64_t n, hipStream_t st) {
-  for (int64_t k = 0; k < n; ++k) {
-    BHIP(launch_one(b, st));
+  while (n > 0) {
+    int64_t T = b->multi && b->multi_steps > 1 ? std::min<int64_t>(n, b->multi_steps) : 1;
+    // short remainders in tiles larger than 16 nodes: as for a single grid
+    if (T < 4 && b->multi_tile > 16) T = 1;
+    if (T > 1)
+      BHIP(launch_multi(b, (int)T, st));
+    else
+      BHIP(launch_one(b, st));
     b->cur ^= 1;
-    b->steps++;
+    b->steps += T;
+    n -= T;
   }
   return RRMHD_OK;
 }
@@ -401,6 +577,7 @@ int rrmhd_batch_step(rrmhd_batch *b, int64_t n) {
       BHIP(hipStreamBeginCapture(b->own, hipStreamCaptureModeThreadLocal));
       int rc = plain_steps(b, chunk, b->own);
       hipError_t ee = hipStreamEndCapture(b->own, &graph);
+      b->graph_flip[c0] = b->cur ^ c0;
       b->cur = c0;  // capture recorded the launches; nothing ran yet
       b->steps = s0;
       if (rc != RRMHD_OK) return rc;
@@ -410,7 +587,7 @@ int rrmhd_batch_step(rrmhd_batch *b, int64_t n) {
       if (ei != hipSuccess) return bdev_err(ei, "hipGraphInstantiate");
     }
     BHIP(hipGraphLaunch(g, b->own));
-    if (chunk & 1) b->cur ^= 1;
+    b->cur ^= b->graph_flip[b->cur];
     b->steps += chunk;
     left -= chunk;
   }
@@ -506,6 +683,11 @@ int rr_batch_restore(rrmhd_batch *b, void *copy, int64_t steps) {
   b->cur = 0;
   b->steps = steps;
   return RRMHD_OK;
+}
+
+void rr_batch_set_multi(rrmhd_batch *b) {
+  free_graphs(b);
+  b->multi = true;
 }
 
 hipStream_t rr_batch_stream(const rrmhd_batch *b) { return b ? b->user : nullptr; }

@@ -48,6 +48,9 @@ RR_HIDDEN int rr_batch_domains(const rrmhd_batch *b, int *n, int *storage, int *
 // batch: copy of the whole current state / restore it (frees the copy)
 RR_HIDDEN int rr_batch_save(rrmhd_batch *b, void **copy);
 RR_HIDDEN int rr_batch_restore(rrmhd_batch *b, void *copy, int64_t steps);
+// batch: several steps per pass again (rrmhd_batch_set_shape and _set_fetch
+// choose the one-step kernel)
+RR_HIDDEN void rr_batch_set_multi(rrmhd_batch *b);
 RR_HIDDEN hipStream_t rr_batch_stream(const rrmhd_batch *b);
 }
 

@@ -23,6 +23,7 @@
 
 #include "rr_node.h"
 #include "rr_pull.h"
+#include "rr_walls.h"
 
 namespace rr {
 
@@ -49,6 +50,10 @@ __device__ __forceinline__ float through_storage(float v, float s, float inv_s) 
 }
 
 // ---- marching strips -----------------------------------------------------------
+// Nodes of a window lost to the halo on each side (one per step, four at most),
+// and those stored.
+constexpr int kMarchHalo = 4, kMarchOut = 64 - 2 * kMarchHalo;
+
 // Lane i takes the value of lane i - 1 (c_x = +1) or i + 1 (c_x = -1).  The
 // window's end lanes get zero: their values are lost to the halo anyway.
 template <int CX>
@@ -174,5 +179,101 @@ __host__ __device__ constexpr int moving_slot(int p) {
   return n;
 }
 constexpr int kMoving = moving_slot(kPlanes);
+
+// A B x B tile of the grid D, one node per thread, through T steps: the first
+// pulls from memory, the later ones from the neighbours through LDS (two
+// buffers, so one barrier per step).  After T steps the inner B - 2 (T - 1)
+// square is valid and stored; tile (tx, ty) stores the square at (tx, ty) times
+// that side.  With walls the tiles cover [0, ny) in y, threads beyond a wall
+// idle, and bounce-back reads the node's own values as the one-step kernel does.
+template <class C, int B, bool WALLS, bool FORCED>
+__device__ __forceinline__ void tile_steps(const Domain &D, float (&ex)[2][kMoving][B * B], int tx,
+                                           int ty, int T, const typename C::T *__restrict__ src,
+                                           typename C::T *__restrict__ dst) {
+  constexpr int N = B * B;
+  const int halo = T - 1, out = B - 2 * halo;
+  const int t = threadIdx.x, ly = t / B, lx = t - ly * B;
+  const int xr = tx * out - halo + lx, yr = ty * out - halo + ly;
+  int x = xr % D.nx;
+  x += x < 0 ? D.nx : 0;
+  int y = yr;
+  bool inside = true;
+  if constexpr (WALLS) {
+    inside = yr >= 0 && yr < D.ny;
+    y = inside ? yr : 0;
+  } else {
+    y %= D.ny;
+    y += y < 0 ? D.ny : 0;
+  }
+  const bool lo = WALLS && y == 0, hi = WALLS && y == D.ny - 1;
+  const CollideParams P{D.om_c, D.omm_c, D.Gx, D.Gy, D.src_c};
+  const PlaneGeom G{D.plane, D.nx, D.ny, D.s, D.inv_s, 0u, D.row};
+  float v[kPlanes];
+  float(&d)[kQ] = *reinterpret_cast<float(*)[kQ]>(v);
+  float(&g)[2 * kQm] = *reinterpret_cast<float(*)[2 * kQm]>(v + kQ);
+  if constexpr (WALLS)
+    pull_node<C, true>(D, src, x, y, d, g);
+  else
+    pull_node_per<C, false>(G, row_addr<RM_LANE>(G, src, y), x, d, g);
+#pragma unroll 1
+  for (int s = 1;; ++s) {
+    collide<FORCED>(d, g, P);
+    if (s == T) break;
+    float(&b)[kMoving][N] = ex[s & 1];
+#pragma unroll
+    for (int p = 0; p < kPlanes; ++p) {
+      v[p] = through_storage<C>(v[p], D.s, D.inv_s);
+      if (plane_moves(p)) b[moving_slot(p)][t] = v[p];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < kPlanes; ++p) {
+      if (!plane_moves(p)) continue;
+      // the upstream neighbour; cells past the tile's edge (whose values the
+      // halo discards) stay in bounds
+      const int o = t - plane_cx(p) - plane_cy(p) * B;
+      float w = b[moving_slot(p)][min(max(o, 0), N - 1)];
+      if constexpr (WALLS) {
+        if (plane_cy(p) != 0 && (plane_cy(p) > 0 ? lo : hi)) {
+          w = b[moving_slot(plane_opp(p))][t];
+          if (p >= kQ) w = ((p - kQ) & 1 ? D.bw2y : D.bw2x) - w;
+        }
+      }
+      v[p] = w;
+    }
+  }
+  if (inside && lx >= halo && lx < B - halo && ly >= halo && ly < B - halo && xr < D.nx &&
+      yr < D.ny)
+    store_node<C, false, RM_LANE>(G, dst, x, y, d, g);
+}
+
+// ---- what a pass costs (launch rules) -----------------------------------------------
+constexpr int kCUs = 256;
+
+// Estimated time (us) of one pass of four marching steps with w workgroups per
+// CU and strips of `rows` rows: per row each wavefront on a SIMD issues four
+// collisions (1.8 us), each strip adds its halo rows, plus the launch.  Fits
+// the measured passes of 20 grids from 320^2 to 5000^2, 1 to 16 workgroups
+// per CU, to 4 % on average.
+inline double march_us(double w, int rows) {
+  return 6.0 + (1.1 + 1.75 * (w > 1.0 ? w : 1.0)) * (rows + 2.5);
+}
+// The same for a pass of T steps in 32 x 32 tiles, one workgroup per CU at a
+// time (131 KB of LDS), q tiles per CU.
+inline double tile32_us(int T, double q) { return T == 5 ? 1.5 + 13.0 * q : 2.0 + 11.5 * q; }
+// One step of the one-step kernels, `bytes` of state: a launch, or the state
+// read and written through HBM.
+inline double single_us(double bytes) { return 3.0 + 2.0 * bytes / 5.4e6; }
+
+// Windows of equal width covering a row of nx nodes, in multiples of 8.
+struct MarchWindows {
+  int n, out;
+};
+inline MarchWindows march_windows(int nx) {
+  const int w = (nx + kMarchOut - 1) / kMarchOut;
+  int out = ((nx + w - 1) / w + 7) / 8 * 8;
+  if (out > kMarchOut) out = kMarchOut;
+  return MarchWindows{(nx + out - 1) / out, out};
+}
 
 }  // namespace rr

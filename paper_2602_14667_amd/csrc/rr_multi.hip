@@ -22,7 +22,6 @@ namespace rr {
 // 625 us per step (six lose 12 of 64 lanes to the halo); two nodes per lane
 // need twice the delay registers and measured 694 us at three steps.  Four
 // neighbouring windows of 56 nodes are 7 x 128 B lines in FP32.
-constexpr int kMarchHalo = 4, kMarchOut = 64 - 2 * kMarchHalo;
 
 template <class C, int T>
 __global__ __launch_bounds__(256) void k_march(PlaneGeom G, CollideParams P, int groups_x, int wx,
@@ -40,73 +39,13 @@ __global__ __launch_bounds__(256) void k_march(PlaneGeom G, CollideParams P, int
 }
 
 // ---- tiles with LDS exchange ---------------------------------------------------
-// A workgroup holds a B x B tile, one node per thread, and takes T steps: the
-// first pulls from memory, the later ones from the neighbours through LDS
-// (two buffers, so one barrier per step).  After T steps the inner B - 2 (T -
-// 1) square is valid and stored.  With walls the tiles cover [0, ny) in y,
-// threads beyond a wall idle, and bounce-back reads the node's own values as
-// the one-step kernel does.
 template <class C, int B, bool WALLS, bool FORCED>
 __global__ __launch_bounds__(B *B) void k_tile_steps(Domain D, int tiles_x, int T,
                                                      const typename C::T *__restrict__ src,
                                                      typename C::T *__restrict__ dst) {
-  constexpr int N = B * B;
-  __shared__ float ex[2][kMoving][N];
-  const int halo = T - 1, out = B - 2 * halo;
+  __shared__ float ex[2][kMoving][B * B];
   const int ty = blockIdx.x / tiles_x, tx = blockIdx.x - ty * tiles_x;
-  const int t = threadIdx.x, ly = t / B, lx = t - ly * B;
-  const int xr = tx * out - halo + lx, yr = ty * out - halo + ly;
-  int x = xr % D.nx;
-  x += x < 0 ? D.nx : 0;
-  int y = yr;
-  bool inside = true;
-  if constexpr (WALLS) {
-    inside = yr >= 0 && yr < D.ny;
-    y = inside ? yr : 0;
-  } else {
-    y %= D.ny;
-    y += y < 0 ? D.ny : 0;
-  }
-  const bool lo = WALLS && y == 0, hi = WALLS && y == D.ny - 1;
-  const CollideParams P{D.om_c, D.omm_c, D.Gx, D.Gy, D.src_c};
-  const PlaneGeom G{D.plane, D.nx, D.ny, D.s, D.inv_s, 0u, D.row};
-  float v[kPlanes];
-  float(&d)[kQ] = *reinterpret_cast<float(*)[kQ]>(v);
-  float(&g)[2 * kQm] = *reinterpret_cast<float(*)[2 * kQm]>(v + kQ);
-  if constexpr (WALLS)
-    pull_node<C, true>(D, src, x, y, d, g);
-  else
-    pull_node_per<C, false>(G, row_addr<RM_LANE>(G, src, y), x, d, g);
-#pragma unroll 1
-  for (int s = 1;; ++s) {
-    collide<FORCED>(d, g, P);
-    if (s == T) break;
-    float(&b)[kMoving][N] = ex[s & 1];
-#pragma unroll
-    for (int p = 0; p < kPlanes; ++p) {
-      v[p] = through_storage<C>(v[p], D.s, D.inv_s);
-      if (plane_moves(p)) b[moving_slot(p)][t] = v[p];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < kPlanes; ++p) {
-      if (!plane_moves(p)) continue;
-      // the upstream neighbour; cells past the tile's edge (whose values the
-      // halo discards) stay in bounds
-      const int o = t - plane_cx(p) - plane_cy(p) * B;
-      float w = b[moving_slot(p)][min(max(o, 0), N - 1)];
-      if constexpr (WALLS) {
-        if (plane_cy(p) != 0 && (plane_cy(p) > 0 ? lo : hi)) {
-          w = b[moving_slot(plane_opp(p))][t];
-          if (p >= kQ) w = ((p - kQ) & 1 ? D.bw2y : D.bw2x) - w;
-        }
-      }
-      v[p] = w;
-    }
-  }
-  if (inside && lx >= halo && lx < B - halo && ly >= halo && ly < B - halo && xr < D.nx &&
-      yr < D.ny)
-    store_node<C, false, RM_LANE>(G, dst, x, y, d, g);
+  tile_steps<C, B, WALLS, FORCED>(D, ex, tx, ty, T, src, dst);
 }
 
 // ---- launch rules ------------------------------------------------------------------
@@ -162,24 +101,6 @@ static void multi_t(const MultiPlan &M, const Domain &D, const void *src, void *
     tile_b<C, 32>(M, D, src, dst, st);
 }
 
-constexpr int kCUs = 256;
-
-// Estimated time (us) of one pass of four marching steps with w workgroups per
-// CU and strips of `rows` rows: per row each wavefront on a SIMD issues four
-// collisions (1.8 us), each strip adds its halo rows, plus the launch.  Fits
-// the measured passes of 20 grids from 320^2 to 5000^2, 1 to 16 workgroups
-// per CU, to 4 % on average.
-static double march_us(double w, int rows) {
-  return 6.0 + (1.1 + 1.75 * (w > 1.0 ? w : 1.0)) * (rows + 2.5);
-}
-// The same for a pass of T steps in 32 x 32 tiles, one workgroup per CU at a
-// time (131 KB of LDS), q tiles per CU.
-static double tile32_us(int T, double q) { return T == 5 ? 1.5 + 13.0 * q : 2.0 + 11.5 * q; }
-// One step of the one-step kernels: a launch, or the state through HBM.
-static double single_us(const Domain &D) {
-  return 3.0 + (double)D.nx * D.ny * D.elem * 2 * kStatePlanes / 5.4e6;
-}
-
 // Tiles per CU of a pass of T steps in B x B tiles.
 static int64_t tiles_per_cu(const Domain &D, int B, int T) {
   const int64_t out = B - 2 * (T - 1);
@@ -221,22 +142,18 @@ MultiPlan multi_plan(const Domain &D, int64_t n) {
     T = 4;
     q = q4;
   }
-  const double single = single_us(D);
+  const double single = single_us((double)D.nx * D.ny * D.elem * kStatePlanes);
   const bool tiles = n >= 4 && (q == 1 || ((D.elem == 4 || D.nx >= 128) &&
                                            tile32_us(T, q) / T < 1.1 * single));
   if (D.walls || forced)
     return tiles && q <= (forced ? 2 : (D.elem == 4 ? 6 : 4)) ? tile(32, T) : M;
   if (tiles && q == 1) return tile(32, T);
   if ((int64_t)D.nx * D.ny < (n >= 4 ? 200000 : 400000)) return tiles ? tile(32, T) : M;
-  // marching: windows of equal width, in multiples of 8 nodes
-  const int windows = (D.nx + kMarchOut - 1) / kMarchOut;
-  int out = ((D.nx + windows - 1) / windows + 7) / 8 * 8;
-  if (out > kMarchOut) out = kMarchOut;
-  const int nw = (D.nx + out - 1) / out;
+  const MarchWindows mw = march_windows(D.nx);
   MultiPlan W{};
-  W.out = out;
-  W.wx = nw >= 3 ? 4 : nw;
-  W.groups_x = (nw + W.wx - 1) / W.wx;
+  W.out = mw.out;
+  W.wx = mw.n >= 3 ? 4 : mw.n;
+  W.groups_x = (mw.n + W.wx - 1) / W.wx;
   const int64_t strips = 4 / W.wx;  // strips per workgroup
   double best = 0.0;
   for (int k = 1; k <= 16; ++k) {

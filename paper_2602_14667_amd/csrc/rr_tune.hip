@@ -412,13 +412,42 @@ int rrmhd_batch_autotune(rrmhd_batch *b, const char *cache_path, int trials) {
     e.ms = best_ms;
     cache[ukey] = e;
   }
-  write_cache(cache_path, cache);
   for (int d = 0; d < n; ++d) {
     rc = rrmhd_batch_set_shape(b, d, uniform > 0 ? uniform : width[std::make_pair(nxs[d], nys[d])],
                                0, -1);
     if (rc != RRMHD_OK) return rc;
   }
-  return RRMHD_OK;
+  // 4) the tuned one-step kernel against the default launch, several steps per
+  // pass where the ensemble has a form for it (state preserved)
+  const std::string mkey = key_of(kb, 2, 0, storage);
+  auto mit = cache.find(mkey);
+  int multi = 0;
+  if (mit != cache.end()) {
+    multi = mit->second.multi;
+  } else {
+    void *save = nullptr;
+    rc = rr_batch_save(b, &save);
+    if (rc != RRMHD_OK) return rc;
+    auto step = [&](int k) { return rrmhd_batch_step(b, k); };
+    double one = 0.0, many = 0.0;
+    rc = time_steps(step, rr_batch_stream(b), trials, &one);
+    rr_batch_set_multi(b);
+    if (rc == RRMHD_OK) rc = time_steps(step, rr_batch_stream(b), trials, &many);
+    multi = many < one;
+    int rc2 = rr_batch_restore(b, save, steps0);
+    if (rc == RRMHD_OK) rc = rc2;
+    if (rc != RRMHD_OK) return rc;
+    if (!multi) rc = rrmhd_batch_set_shape(b, -1, 0, 0, -1);  // one step per pass again
+    Entry e;
+    e.bx = 1;
+    e.by = 1;
+    e.multi = multi;
+    e.ms = multi ? many : one;
+    cache[mkey] = e;
+  }
+  if (multi) rr_batch_set_multi(b);
+  write_cache(cache_path, cache);
+  return rc;
 }
 
 }  // extern "C"

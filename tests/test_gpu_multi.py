@@ -105,3 +105,36 @@ def test_nonfinite_values_spread_as_in_single_steps():
         assert torch.equal(a[~torch.isnan(fa)], b[~torch.isnan(fb)])
         got.close()
         ref.close()
+
+
+ENSEMBLES = [[(1, 1), (2, 3), (64, 64)], [(96, 64), (33, 70), (160, 96)],
+             [(224, 225), (130, 64), (64, 190)], [(400, 300), (96, 96), (57, 211)],
+             [(1024, 640), (64, 64), (113, 700), (56, 40), (7, 900)],
+             [(448, 448)] * 9 + [(225, 31)]]
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("shapes", ENSEMBLES)
+def test_ensembles_equal_single_steps(shapes, storage):
+    from paper_2602_14667_amd import rrmhd
+    print(f"[gpu] multi-step ensemble {shapes[:3]} x {len(shapes)} {storage}", flush=True)
+    tf = [0.55 + 0.005 * k for k in range(len(shapes))]
+    tm = [0.6 - 0.004 * k for k in range(len(shapes))]
+    got, ref = (rrmhd.Batch(shapes, tf, tm, storage=storage) for _ in range(2))
+    ref.set_shape(-1, 32, 0, -1)  # one step per launch
+    rng = np.random.default_rng(len(shapes))
+    for d, (nx, ny) in enumerate(shapes):
+        u, b = (torch.from_numpy(0.03 * rng.standard_normal((2, ny, nx))).cuda() for _ in range(2))
+        for h in (got, ref):
+            h.init(d, u, b)
+    for k, n in enumerate([1, 2, 3, 4, 5, 9, 23, 24]):
+        if k == 6:
+            got.set_graph_chunk(7)
+        got.step(n)
+        ref.step(n)
+        assert got.info()["steps"] == ref.info()["steps"]
+        for d in range(len(shapes)):
+            for a, c in zip(got.moments(d), ref.moments(d)):
+                assert torch.equal(a, c), (n, d)
+    got.close()
+    ref.close()
