@@ -58,3 +58,38 @@ def test_loss_gradient_at_group_edges(n, gain):
     assert e < TOL, e
     assert abs(loss.item() - loss_ref) < TOL * abs(loss_ref)
     tr.close()
+
+
+@pytest.mark.parametrize("nc,factor", [(1, 2), (15, 2), (16, 4), (17, 4), (16, 8), (33, 8),
+                                       (16, 3), (5, 6)])
+@pytest.mark.parametrize("skew", [0, 1])
+def test_box_filter_factors_and_alignment(nc, factor, skew):
+    """Compiled and general factors, fields at 16-byte and at 8-byte bases;
+    and den, summed per workgroup first.  FP64 sums of at most 64 values
+    (1089 for den): 1e-13 relative to the largest value is over ten times
+    their rounding."""
+    from paper_2602_14667_amd import rrmhd
+    print(f"[gpu] box filter nc={nc} factor={factor} skew={skew}", flush=True)
+    n = nc * factor
+    g = np.random.default_rng(10 * nc + factor)
+
+    def field(*shape):
+        a = 0.05 * g.standard_normal(shape) + (1.0 if len(shape) == 2 else 0.0)
+        t = torch.empty(a.size + skew, dtype=torch.float64, device="cuda")[skew:].view(shape)
+        t.copy_(torch.from_numpy(a))
+        return a, t
+
+    def mean(a):
+        return a.reshape(nc, factor, nc, factor).mean(axis=(1, 3))
+
+    (r0, tr0), (u0, tu0), (b0, tb0) = field(n, n), field(2, n, n), field(2, n, n)
+    (r1, tr1), (u1, tu1), (b1, tb1) = field(n, n), field(2, n, n), field(2, n, n)
+    out = rrmhd.train_box_filter(tr0, tu0, tb0, factor).cpu().numpy()
+    want = [r0, r0 * u0[0], r0 * u0[1], b0[0], b0[1], r0 * u0[0] ** 2, r0 * u0[0] * u0[1],
+            r0 * u0[1] ** 2, 0.5 * (b0[1] ** 2 - b0[0] ** 2), -b0[0] * b0[1]]
+    for k, w in enumerate(want):
+        assert np.abs(out[k] - mean(w)).max() <= 1e-13 * np.abs(w).max(), k
+    _, _, den = rrmhd.train_onestep_samples((tr0, tu0, tb0), (tr1, tu1, tb1), factor, 0.55)
+    dj = [mean(r1 * u1[a]) - mean(r0 * u0[a]) for a in range(2)]
+    ref = (dj[0] ** 2 + dj[1] ** 2).sum()
+    assert abs(den.item() - ref) <= 1e-12 * ref
