@@ -285,11 +285,11 @@ __device__ __forceinline__ void load_all(const typename C::T *__restrict__ s, co
   ((v[P] = ld_plane<C, P>(s, D, S)), ...);
 }
 
-template <class C, int... P>
+template <class C, bool NT, int... P>
 __device__ __forceinline__ void store_all(typename C::T *__restrict__ dst, const Dom3 &D,
                                           uint32_t o, const float *v,
                                           std::integer_sequence<int, P...>) {
-  ((rr::st_at<typename C::T, true>(dst + (int64_t)P * D.plane, o, C::enc(v[P], 1.0f))), ...);
+  ((rr::st_at<typename C::T, NT>(dst + (int64_t)P * D.plane, o, C::enc(v[P], 1.0f))), ...);
 }
 
 __device__ __forceinline__ Src3 sources(const Dom3 &D, int x, int y, int z, uint32_t E) {
@@ -326,24 +326,41 @@ __device__ __forceinline__ Tile3 tile3(int xcd) {
   return Tile3{L % (int)gridDim.x, L / (int)gridDim.x};
 }
 
-template <class C>
+// The node of a thread.  LIN: the nodes in memory order, x and y and z from
+// the node number; a workgroup's stores then are whole aligned lines and no
+// lane idles, whatever the box.  Otherwise (bx, by) tiles of a z plane.
+struct Node3 {
+  int x, y, z;
+  bool in;
+};
+template <bool LIN>
+__device__ __forceinline__ Node3 node3(const Dom3 &D, int tiles_x, int xcd) {
+  const Tile3 T = tile3(xcd);
+  if constexpr (LIN) {
+    const uint32_t n = (uint32_t)T.t * blockDim.x + threadIdx.x;
+    const uint32_t row = n / (uint32_t)D.nx, z = row / (uint32_t)D.ny;
+    return Node3{(int)(n - row * (uint32_t)D.nx), (int)(row - z * (uint32_t)D.ny), (int)z,
+                 z < (uint32_t)D.nz};
+  }
+  const int tx = T.t % tiles_x, ty = T.t / tiles_x;
+  const int x = tx * blockDim.x + threadIdx.x, y = ty * blockDim.y + threadIdx.y;
+  return Node3{x, y, T.z, x < D.nx && y < D.ny};
+}
+
+template <class C, bool LIN, bool NT>
 __global__ __launch_bounds__(256) void k_step3(Dom3 D, int tiles_x, int xcd,
                                                const typename C::T *__restrict__ src,
                                                typename C::T *__restrict__ dst) {
-  const Tile3 T = tile3(xcd);
-  const int tx = T.t % tiles_x, ty = T.t / tiles_x;
-  const int x = tx * blockDim.x + threadIdx.x;
-  const int y = ty * blockDim.y + threadIdx.y;
-  const int z = T.z;
-  if (x >= D.nx || y >= D.ny) return;
+  const Node3 P = node3<LIN>(D, tiles_x, xcd);
+  if (!P.in) return;
   constexpr uint32_t E = sizeof(typename C::T);
-  const Src3 S = sources(D, x, y, z, E);
+  const Src3 S = sources(D, P.x, P.y, P.z, E);
   float v[kPlanes];
   load_all<C>(src, D, S, v, std::make_integer_sequence<int, kPlanes>{});
   float(&d)[kQ] = *reinterpret_cast<float(*)[kQ]>(v);
   float(&g)[3 * kQm] = *reinterpret_cast<float(*)[3 * kQm]>(v + kQ);
   collide3(d, g, D.om_c, D.omm_c);
-  store_all<C>(dst, D, S.slab[1] + S.row[1] + S.col[1], v,
+  store_all<C, NT>(dst, D, S.slab[1] + S.row[1] + S.col[1], v,
                std::make_integer_sequence<int, kPlanes>{});
 }
 
@@ -377,7 +394,7 @@ __device__ __forceinline__ void st_push(typename C::T *buf, const Dom3 &D, const
   }
   // the source entry of -c is the node x + c
   const uint32_t off = S.slab[1 - c] + S.row[1 - b] + S.col[1 - a];
-  rr::st_at<typename C::T, true>(buf + (int64_t)opp_plane(P) * D.plane, off, C::enc(v[P], 1.0f));
+  rr::st_at<typename C::T, false>(buf + (int64_t)opp_plane(P) * D.plane, off, C::enc(v[P], 1.0f));
 }
 template <class C, int... P>
 __device__ __forceinline__ void push_all(typename C::T *buf, const Dom3 &D, const Src3 &S,
@@ -393,17 +410,13 @@ __device__ __forceinline__ void load_own(const typename C::T *buf, const Dom3 &D
    ...);
 }
 
-template <class C, int PHASE>
+template <class C, int PHASE, bool LIN>
 __global__ __launch_bounds__(256) void k_step3_inplace(Dom3 D, int tiles_x, int xcd,
                                                        typename C::T *buf) {
-  const Tile3 T = tile3(xcd);
-  const int tx = T.t % tiles_x, ty = T.t / tiles_x;
-  const int x = tx * blockDim.x + threadIdx.x;
-  const int y = ty * blockDim.y + threadIdx.y;
-  const int z = T.z;
-  if (x >= D.nx || y >= D.ny) return;
+  const Node3 P = node3<LIN>(D, tiles_x, xcd);
+  if (!P.in) return;
   constexpr uint32_t E = sizeof(typename C::T);
-  const Src3 S = sources(D, x, y, z, E);
+  const Src3 S = sources(D, P.x, P.y, P.z, E);
   const uint32_t own = S.slab[1] + S.row[1] + S.col[1];
   float v[kPlanes];
   if constexpr (PHASE == 0)
@@ -416,7 +429,7 @@ __global__ __launch_bounds__(256) void k_step3_inplace(Dom3 D, int tiles_x, int 
   if constexpr (PHASE == 0)
     push_all<C>(buf, D, S, v, std::make_integer_sequence<int, kPlanes>{});
   else
-    store_all<C>(buf, D, own, v, std::make_integer_sequence<int, kPlanes>{});
+    store_all<C, false>(buf, D, own, v, std::make_integer_sequence<int, kPlanes>{});
 }
 
 // Debug fill of a population buffer with a NaN pattern (32-bit words).
@@ -459,7 +472,7 @@ __global__ void k_swapped_to_pull3(Dom3 D, const T *__restrict__ buf, T *__restr
 // Each node evaluates its own equilibria once, from factors shared by all
 // populations, and writes population p to the slot x - c_p it is pulled from
 // (the former kernel evaluated, per slot, the equilibrium of the node upstream:
-// 34 field reads and full evaluations per node).  256^3 FP32: 797 us (2406),
+// 34 field reads and full evaluations per node).  256^3 FP32: 845 us (2406),
 // bound by its writes.
 struct EqD3 {
   double f[3][3];  // f[a][c + 1]: D1Q3 factor, direction a, speed c
@@ -525,11 +538,10 @@ template <class C>
 __global__ __launch_bounds__(256) void k_init3(Dom3 D, const double *__restrict__ u,
                                                const double *__restrict__ b,
                                                typename C::T *__restrict__ dst) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y, z = blockIdx.z;
-  if (x >= D.nx || y >= D.ny) return;
+  const Node3 P = node3<true>(D, 1, 1);
+  if (!P.in) return;
   const int64_t N = (int64_t)D.nx * D.ny * D.nz;
-  const int64_t o = ((int64_t)z * D.ny + y) * D.nx + x;
+  const int64_t o = ((int64_t)P.z * D.ny + P.y) * D.nx + P.x;
   EqD3 E;
   double bh = 0.0;
 #pragma unroll
@@ -547,7 +559,7 @@ __global__ __launch_bounds__(256) void k_init3(Dom3 D, const double *__restrict_
     E.f[a][2] = 1.0 + (3.0 * v + 3.0 * v * v);
     E.md[a] = 1.5 * (bh - E.b[a] * E.b[a]);
   }
-  const Src3 S = sources(D, x, y, z, sizeof(typename C::T));
+  const Src3 S = sources(D, P.x, P.y, P.z, sizeof(typename C::T));
   init_all<C>(dst, D, S, E, std::make_integer_sequence<int, kPlanes>{});
 }
 
@@ -588,13 +600,13 @@ __device__ Mom3 moments3(const Dom3 &D, const typename C::T *__restrict__ s, int
 }
 
 template <class C, bool SW>
-__global__ void k_moments3(Dom3 D, const typename C::T *__restrict__ src, double *rho, double *u,
-                           double *b) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-  if (x >= D.nx) return;
-  const Mom3 m = moments3<C, SW>(D, src, x, y, z);
+__global__ __launch_bounds__(256) void k_moments3(Dom3 D, const typename C::T *__restrict__ src,
+                                                  double *rho, double *u, double *b) {
+  const Node3 P = node3<true>(D, 1, 1);
+  if (!P.in) return;
+  const Mom3 m = moments3<C, SW>(D, src, P.x, P.y, P.z);
   const int64_t N = (int64_t)D.nx * D.ny * D.nz;
-  const int64_t o = ((int64_t)z * D.ny + y) * D.nx + x;
+  const int64_t o = ((int64_t)P.z * D.ny + P.y) * D.nx + P.x;
   if (rho) rho[o] = m.rho;
   for (int a = 0; a < 3; ++a) {
     if (u) u[a * N + o] = m.u[a];
@@ -717,6 +729,8 @@ struct rrmhd3d {
   int phase = 0;         // in-place: 0 pull layout, 1 swapped layout
   bool poison = false;   // debug: NaN-fill the destination buffer before each step
   int bx = 64, by = 4;
+  int linear = 0;  // threads of a workgroup over the nodes in memory order, or 0: tiles
+  bool nt = true;  // streaming stores
   int xcd = 0;  // XCD-local tile order
   double *diag_work = nullptr;
   double *diag_out = nullptr;
@@ -729,13 +743,45 @@ struct rrmhd3d {
     if (e_ != hipSuccess) return rr_device_error(e_, #x); \
   } while (0)
 
-template <class C>
-static void launch_inplace3(rrmhd3d *h, dim3 grid, dim3 block, int tiles_x) {
-  auto b = (typename C::T *)h->buf[0];
-  if (h->phase == 0)
-    hipLaunchKernelGGL((rr3::k_step3_inplace<C, 0>), grid, block, 0, h->stream, h->D, tiles_x, h->xcd, b);
+static unsigned node_blocks(const rr3::Dom3 &D, int threads = 256) {
+  return (unsigned)(((int64_t)D.nx * D.ny * D.nz + threads - 1) / threads);
+}
+
+template <class C, bool LIN>
+static void launch_step3(rrmhd3d *h, dim3 grid, dim3 block, int tiles_x, const void *src,
+                         void *dst) {
+  using T = typename C::T;
+  if (!h->inplace && h->nt)
+    hipLaunchKernelGGL((rr3::k_step3<C, LIN, true>), grid, block, 0, h->stream, h->D, tiles_x,
+                       h->xcd, (const T *)src, (T *)dst);
+  else if (!h->inplace)
+    hipLaunchKernelGGL((rr3::k_step3<C, LIN, false>), grid, block, 0, h->stream, h->D, tiles_x,
+                       h->xcd, (const T *)src, (T *)dst);
+  else if (h->phase == 0)
+    hipLaunchKernelGGL((rr3::k_step3_inplace<C, 0, LIN>), grid, block, 0, h->stream, h->D,
+                       tiles_x, h->xcd, (T *)h->buf[0]);
   else
-    hipLaunchKernelGGL((rr3::k_step3_inplace<C, 1>), grid, block, 0, h->stream, h->D, tiles_x, h->xcd, b);
+    hipLaunchKernelGGL((rr3::k_step3_inplace<C, 1, LIN>), grid, block, 0, h->stream, h->D,
+                       tiles_x, h->xcd, (T *)h->buf[0]);
+}
+
+// One step from src to dst (in place: of the one buffer, whatever they are).
+static void launch_step3(rrmhd3d *h, const void *src, void *dst) {
+  const rr3::Dom3 &D = h->D;
+  if (h->linear) {
+    const dim3 grid(node_blocks(D, h->linear)), block(h->linear);
+    if (h->storage == RRMHD_STORE_F16)
+      launch_step3<rr3::CodecF16U, true>(h, grid, block, 0, src, dst);
+    else
+      launch_step3<rr3::CodecF32, true>(h, grid, block, 0, src, dst);
+    return;
+  }
+  const int tiles_x = (D.nx + h->bx - 1) / h->bx, tiles_y = (D.ny + h->by - 1) / h->by;
+  const dim3 grid(tiles_x * tiles_y, D.nz), block(h->bx, h->by);
+  if (h->storage == RRMHD_STORE_F16)
+    launch_step3<rr3::CodecF16U, false>(h, grid, block, tiles_x, src, dst);
+  else
+    launch_step3<rr3::CodecF32, false>(h, grid, block, tiles_x, src, dst);
 }
 
 template <class C>
@@ -803,22 +849,27 @@ int rrmhd3d_create(int32_t nx, int32_t ny, int32_t nz, int32_t storage, double t
   h->tau_m = tau_m;
   h->D.om_c = (float)(1.0 - 1.0 / tau_f);
   h->D.omm_c = (float)(1.0 - 1.0 / tau_m);
-  // measured at 256^3: one row of 128 threads is the best or within 1 % of
-  // it (FP16 +6 % over 64 x 4); narrow boxes stack rows to fill 128 threads
-  h->bx = nx >= 128 ? 128 : ((nx + 15) / 16) * 16;
-  h->by = 128 / h->bx;
-  if (h->inplace && nx >= 256) {
-    // the alternating single-buffer steps: one row of 256 threads measured
-    // best at 256^3 (FP32 61 %, FP16 64 % of 8 TB/s against 56 %, 60 % at 128)
-    h->bx = 256;
-    h->by = 1;
-  }
-  // measured at 256^3: the XCD-local order gains about one point of 8 TB/s
-  // for FP16 storage (67.6 % against 66.7 %) and for one buffer (FP32 61.5 %
-  // against 60.5 %, FP16 65.2 % against 64.2 %); FP32 with two buffers is the
-  // same either way and keeps the plain order
-  h->xcd = (h->storage == RRMHD_STORE_F16 || h->inplace) ? 1 : 0;
+  // Nodes in memory order, XCD-local: a workgroup of tiles cuts the lines of
+  // rows that do not start on one, and both halves are then written on their
+  // own.  317 x 247 x 186, tiles of 128 -> memory order, in us per step: FP32
+  // 1918 -> 1063, FP16 1202 -> 545, one buffer FP32 1413 -> 1146, FP16 820 ->
+  // 577; 43 x 299 x 83: 115 -> 74, 61 -> 36, 86 -> 63, 46 -> 37.  Rows of
+  // whole waves keep one row of 64 as the tile with two buffers (a wave's rows
+  // are then scalar, 256^3 FP32 1114 against 1148 in memory order and 1130 in
+  // rows of 128, FP16 584, 582 and 608); with one buffer memory order is the
+  // faster there too (256^3 FP32 1260 against 1338 in rows of 256).
+  h->linear = !h->inplace && nx % 64 == 0 ? 0 : (elem == 4 && !h->inplace ? 128 : 256);
+  h->bx = 64;
+  h->by = 1;
+  h->xcd = 1;
   const size_t bytes = (size_t)h->D.plane * rr3::kPlanes * elem;
+  // Streaming stores keep the source of a step in the caches where the two
+  // buffers do not fit the 256 MiB last-level cache (256^3 FP32 1114 against
+  // 1153 us, 43 x 299 x 83 FP32 at 410 MB 74 against 79); buffers that do are
+  // read back from it by the next step (128 x 170 x 57 FP16 at 238 MB 41
+  // against 48, 71 x 61 x 59 FP32 at 98 MB 16 against 20).  One buffer is
+  // written where it was just read and takes plain stores.
+  h->nt = 2 * bytes > ((size_t)256 << 20);
   int rc = RRMHD_OK;
   for (int k = 0; k < (h->inplace ? 1 : 2) && rc == RRMHD_OK; ++k)
     if (hipMalloc(&h->buf[k], bytes) != hipSuccess) rc = RRMHD_ENOMEM;
@@ -837,6 +888,7 @@ int rrmhd3d_create(int32_t nx, int32_t ny, int32_t nz, int32_t storage, double t
 
 int rrmhd3d_set_launch(rrmhd3d *h, int bx, int by, int xcd) {
   if (!h || bx < 1 || by < 1 || bx * by > 256 || xcd < -1 || xcd > 1) return RRMHD_EINVAL;
+  h->linear = 0;
   h->bx = bx;
   h->by = by;
   if (xcd >= 0) h->xcd = xcd;
@@ -845,9 +897,7 @@ int rrmhd3d_set_launch(rrmhd3d *h, int bx, int by, int xcd) {
 
 int rrmhd3d_init(rrmhd3d *h, const double *u, const double *b) {
   if (!h || !u || !b) return RRMHD_EINVAL;
-  // whole rows where they fit, so that a row's shifted stores meet in one L2
-  const unsigned bx = h->D.nx > 128 ? 256 : (h->D.nx > 64 ? 128 : 64), by = 256 / bx;
-  const dim3 block(bx, by), grid((h->D.nx + bx - 1) / bx, (h->D.ny + by - 1) / by, h->D.nz);
+  const dim3 block(256), grid(node_blocks(h->D));
   if (h->storage == RRMHD_STORE_F16)
     hipLaunchKernelGGL(rr3::k_init3<rr3::CodecF16U>, grid, block, 0, h->stream, h->D, u, b,
                        (uint16_t *)h->buf[0]);
@@ -865,34 +915,20 @@ int rrmhd3d_init(rrmhd3d *h, const double *u, const double *b) {
 int rrmhd3d_step(rrmhd3d *h, int64_t n) {
   if (!h || n < 0) return RRMHD_EINVAL;
   if (!h->ready) return RRMHD_ESTATE;
-  const int tiles_x = (h->D.nx + h->bx - 1) / h->bx, tiles_y = (h->D.ny + h->by - 1) / h->by;
-  const dim3 grid(tiles_x * tiles_y, h->D.nz), block(h->bx, h->by);
-  for (int64_t k = 0; k < n && h->inplace; ++k) {
-    if (h->storage == RRMHD_STORE_F16)
-      launch_inplace3<rr3::CodecF16U>(h, grid, block, tiles_x);
-    else
-      launch_inplace3<rr3::CodecF32>(h, grid, block, tiles_x);
-    HIP3(hipGetLastError());
-    h->phase ^= 1;
-    h->steps++;
-  }
-  if (h->inplace) return RRMHD_OK;
   for (int64_t k = 0; k < n; ++k) {
-    const void *s = h->buf[h->cur];
-    void *d = h->buf[h->cur ^ 1];
+    const void *src = h->buf[h->cur];
+    void *dst = h->inplace ? h->buf[0] : h->buf[h->cur ^ 1];
     if (h->poison) {
       const int64_t words = h->D.plane * rr3::kPlanes * h->elem / 4;
-      hipLaunchKernelGGL(rr3::k_poison3, dim3(2048), dim3(256), 0, h->stream, (uint32_t *)d, words,
-                         h->elem == 4 ? 0x7fc00000u : 0x7e007e00u);
+      hipLaunchKernelGGL(rr3::k_poison3, dim3(2048), dim3(256), 0, h->stream, (uint32_t *)dst,
+                         words, h->elem == 4 ? 0x7fc00000u : 0x7e007e00u);
     }
-    if (h->storage == RRMHD_STORE_F16)
-      hipLaunchKernelGGL(rr3::k_step3<rr3::CodecF16U>, grid, block, 0, h->stream, h->D, tiles_x,
-                         h->xcd, (const uint16_t *)s, (uint16_t *)d);
-    else
-      hipLaunchKernelGGL(rr3::k_step3<rr3::CodecF32>, grid, block, 0, h->stream, h->D, tiles_x,
-                         h->xcd, (const float *)s, (float *)d);
+    launch_step3(h, src, dst);
     HIP3(hipGetLastError());
-    h->cur ^= 1;
+    if (h->inplace)
+      h->phase ^= 1;
+    else
+      h->cur ^= 1;
     h->steps++;
   }
   return RRMHD_OK;
@@ -914,7 +950,7 @@ int rrmhd3d_moments(rrmhd3d *h, double *rho, double *u, double *b) {
   if (!h) return RRMHD_EINVAL;
   if (!h->ready) return RRMHD_ESTATE;
   if (!rho && !u && !b) return RRMHD_OK;
-  const dim3 block(64), grid((h->D.nx + 63) / 64, h->D.ny, h->D.nz);
+  const dim3 block(256), grid(node_blocks(h->D));
   const bool sw = h->inplace && h->phase;
   if (h->storage == RRMHD_STORE_F16)
     launch_moments3<rr3::CodecF16U>(h, sw, grid, block, rho, u, b);

@@ -141,6 +141,31 @@ def test_3d_launch_shapes_bitwise(storage, shape, inplace):
             assert np.array_equal(g[k], out[0][k]), k
 
 
+@pytest.mark.parametrize("inplace", [False, True])
+@pytest.mark.parametrize("storage,shape", [
+    ("f32", (1, 1, 1)), ("f32", (5, 3, 2)), ("f32", (2, 1, 64)), ("f32", (63, 3, 3)),
+    ("f32", (64, 3, 2)), ("f32", (65, 5, 3)), ("f16", (257, 2, 1)), ("f16", (128, 2, 2)),
+    ("f16", (31, 33, 1)), ("f32", (97, 91, 89)), ("f32", (128, 80, 77))])
+def test_3d_memory_order_bitwise(storage, shape, inplace):
+    """The default launch (memory order, or rows of 64) against explicit
+    tiles, bit for bit: boxes below, at and past a wavefront or a workgroup,
+    and two whose buffers exceed the size above which stores stream."""
+    note(f"3D memory order {storage} {shape} inplace={inplace}")
+    R = rrmhd()
+    u, b = inputs.random_modes3d(*shape, 0.03, seed=4)
+    out = []
+    for tiles in (False, True):
+        s = R.Solver3D(*shape, 0.54, 0.58, storage=storage, inplace=inplace)
+        if tiles:
+            s.set_launch(32, 4, 0)
+        s.init(dev(u), dev(b))
+        s.step(3)
+        out.append(gpu_fields(s))
+        s.close()
+    for k in FIELDS:
+        assert np.array_equal(out[0][k], out[1][k]), k
+
+
 def test_3d_uniform_state_is_fixed():
     R = rrmhd()
     shape = (8, 6, 4)
