@@ -84,6 +84,30 @@ def test_zero_network_is_bitwise_plain():
     a.close(); c.close()
 
 
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (64, 1), (65, 17), (300, 37), (1067, 400), (130, 3001),
+                                   (512, 512), (2048, 128)])
+def test_zero_network_covers_every_node(nx, ny, storage):
+    """Work dealt out in rows (fewer rows than blocks, ragged last bands, a
+    last round that is part full) or in whole tiles (the last two grids): a
+    zero network is the plain step bit for bit."""
+    note(f"zero closure {nx}x{ny} {storage}")
+    rr = R()
+    u, b = inputs.random_modes(nx, ny, 0.05, seed=5)
+    out = []
+    for on in (False, True):
+        s = rr.Solver(nx, ny, 0.55, 0.6, storage=storage)
+        s.init(torch.from_numpy(u).cuda(), torch.from_numpy(b).cuda())
+        if on:
+            s.closure_set(dev32(np.zeros(oracle.NPARAM)), dev32(np.ones(19)))
+            s.closure_enable(True)
+        s.step(3)
+        out.append([a.cpu().numpy() for a in s.moments()])
+        s.close()
+    for a, c in zip(*out):
+        assert np.array_equal(a, c)
+
+
 @pytest.mark.parametrize("shape", [(64, 64), (100, 37)])
 def test_fused_closure_step_vs_oracle(shape):
     """A network whose correction is of the order of a_1^(2) itself; after 10
