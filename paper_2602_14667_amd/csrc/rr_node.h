@@ -263,41 +263,18 @@ struct NoCorrection {
 // it stores; the unforced method keeps FP32 arithmetic.  Constants enter as
 // FP64 products with correctly rounded FP64 reciprocals (their rounding is
 // far below the FP32 storage's).
-template <int CX, int CY>
-__device__ __forceinline__ double reg_bracket64(const double (&A)[6]) {
-  constexpr double hx = CX ? 2.0 : -1.0;
-  constexpr double hy = CY ? 2.0 : -1.0;
-  double r = 1.5 * fma(hx, A[0], hy * A[2]);
-  if constexpr (CX != 0 && CY != 0) r = fma(9.0 * CX * CY, A[1], r);
-  if constexpr (CY != 0) r = fma(4.5 * CY * hx, A[3], r);
-  if constexpr (CX != 0) r = fma(4.5 * CX * hy, A[4], r);
-  return fma(2.25 * hx * hy, A[5], r);
-}
-
-template <int I, bool FULLM>
-__device__ __forceinline__ float post_f64(double rho, double dr, const double (&ex)[3],
-                                          const double (&ey)[3], double mq, double mxy,
-                                          const double (&A)[6], double a1c, double a1x,
-                                          double a1y, double sc, double Fx, double Fy,
-                                          double ux, double uy) {
-  constexpr int CX = cx(I), CY = cy(I);
-  constexpr double hx = CX ? 2.0 : -1.0;
-  constexpr double hy = CY ? 2.0 : -1.0;
-  // equilibrium bracket (D1Q3 product, Maxwell stress at second order)
-  const double exv = ex[CX + 1], eyv = ey[CY + 1];
-  double B = fma(rho, fma(exv, eyv, exv + eyv), dr);
-  if constexpr (CX != 0 && CY == 0) B = B + mq;
-  if constexpr (CX == 0 && CY != 0) B = B - mq;
-  if constexpr (CX != 0 && CY != 0) B = fma(-(double)(CX * CY), mxy, B);
-  // forcing: (1 - omega) 3 c.a1 + (1 - omega/2)[3 c.F + 3 (hx ux Fx + hy uy Fy)
-  // + 9 cx cy (ux Fy + uy Fx)]
-  double ca1 = 0.0, cF = 0.0;
-  if constexpr (CX != 0) { ca1 = CX * a1x; cF = CX * Fx; }
-  if constexpr (CY != 0) { ca1 = ca1 + CY * a1y; cF = cF + CY * Fy; }
-  double fs = 3.0 * fma(hx * ux, Fx, hy * uy * Fy) + 3.0 * cF;
-  if constexpr (CX != 0 && CY != 0) fs = fma(9.0 * CX * CY, fma(ux, Fy, uy * Fx), fs);
-  const double v = B + reg_bracket64<CX, CY>(A) + fma(a1c, ca1, sc * fs);
-  return (float)(v * (1.0 / (double)wdiv(I)));
+//
+// All of equilibrium, regularised part and force is one Hermite series, w_i
+// sum a_mn F_m(c_x) F_n(c_y) over m, n = 0, 1, 2 with F_0 = 1, F_1 = 3c, F_2 =
+// 1.5 (3c^2 - 1): the coefficients are added up first and the nine values
+// follow in two passes of three lines, one per direction (223 FP64
+// instructions per node against 338 velocity by velocity; 200 forced steps at
+// 512 x 256 in 690 us against 838).
+__device__ __forceinline__ void hermite_line64(double &a0, double &a1, double &a2) {
+  const double p = fma(3.0, a2, a0), o = a1;
+  a1 = fma(-1.5, a2, a0);
+  a0 = fma(-3.0, o, p);
+  a2 = fma(3.0, o, p);
 }
 
 template <bool FULLM>
@@ -315,8 +292,9 @@ __device__ __forceinline__ void collide_forced64(float (&d)[kQ], float (&g)[2 * 
   const double jy = ((f[1] + f[7]) + f[8]) - ((f[3] + f[4]) + f[5]);
   const double Gx = P.Gx, Gy = P.Gy;
   const double Fx = rho * Gx, Fy = rho * Gy;
-  const double ux = fma(0.5, Fx, jx) / rho;
-  const double uy = fma(0.5, Fy, jy) / rho;
+  const double nx = fma(0.5, Fx, jx), ny = fma(0.5, Fy, jy), rr = 1.0 / rho;
+  const double qx = nx * rr, qy = ny * rr;
+  const double ux = fma(fma(-qx, rho, nx), rr, qx), uy = fma(fma(-qy, rho, ny), rr, qy);
   const double bx = ((m[0] + m[2]) + (m[4] + m[6])) + m[8];
   const double by = ((m[1] + m[3]) + (m[5] + m[7])) + m[9];
   // task 3: exact Hermite moments of f_eq, projection, recursion
@@ -344,23 +322,30 @@ __device__ __forceinline__ void collide_forced64(float (&d)[kQ], float (&g)[2 * 
     A[4] += fma(-ux, mxx, -2.0 * (uy * bxy));
     A[5] += fma(fma(uy, uy, -ux * ux), mxx, -4.0 * (ux * (uy * bxy)));
   }
-  // task 2: D1Q3 factors minus one, indexed by c + 1
-  const double ux2 = ux * ux, uy2 = uy * uy;
-  const double ex[3] = {fma(-3.0, ux, 3.0 * ux2), -1.5 * ux2, fma(3.0, ux, 3.0 * ux2)};
-  const double ey[3] = {fma(-3.0, uy, 3.0 * uy2), -1.5 * uy2, fma(3.0, uy, 3.0 * uy2)};
-  const double mq = 4.5 * mxx, mxy = 9.0 * bxy;
-  const double a1c = 3.0 * om, a1x = -0.5 * Fx, a1y = -0.5 * Fy;
-  const double sc = P.src_c;
-  // tasks 4-5 per velocity, rounded once to FP32
-  d[0] = post_f64<0, FULLM>(rho, dr, ex, ey, mq, mxy, A, a1c, a1x, a1y, sc, Fx, Fy, ux, uy);
-  d[1] = post_f64<1, FULLM>(rho, dr, ex, ey, mq, mxy, A, a1c, a1x, a1y, sc, Fx, Fy, ux, uy);
-  d[2] = post_f64<2, FULLM>(rho, dr, ex, ey, mq, mxy, A, a1c, a1x, a1y, sc, Fx, Fy, ux, uy);
-  d[3] = post_f64<3, FULLM>(rho, dr, ex, ey, mq, mxy, A, a1c, a1x, a1y, sc, Fx, Fy, ux, uy);
-  d[4] = post_f64<4, FULLM>(rho, dr, ex, ey, mq, mxy, A, a1c, a1x, a1y, sc, Fx, Fy, ux, uy);
-  d[5] = post_f64<5, FULLM>(rho, dr, ex, ey, mq, mxy, A, a1c, a1x, a1y, sc, Fx, Fy, ux, uy);
-  d[6] = post_f64<6, FULLM>(rho, dr, ex, ey, mq, mxy, A, a1c, a1x, a1y, sc, Fx, Fy, ux, uy);
-  d[7] = post_f64<7, FULLM>(rho, dr, ex, ey, mq, mxy, A, a1c, a1x, a1y, sc, Fx, Fy, ux, uy);
-  d[8] = post_f64<8, FULLM>(rho, dr, ex, ey, mq, mxy, A, a1c, a1x, a1y, sc, Fx, Fy, ux, uy);
+  // tasks 2, 4, 5: the series' coefficients.  Equilibrium rho u_x^m u_y^n (less
+  // 1 at m = n = 0) and M at second order; force (1 - omega) a1 and
+  // (1 - omega/2) F at first, (1 - omega/2) (u F + F u) at second order
+  const double sc = P.src_c, kf = fma(-0.5, om, sc);
+  const double sx = sc * Fx, sy = sc * Fy;
+  const double rxx = rux * ux, rxy = rux * uy, rxxy = rxx * uy;
+  double a[9];  // a[m + 3 n]
+  a[0] = dr;
+  a[1] = fma(kf, Fx, rux);
+  a[3] = fma(kf, Fy, ruy);
+  a[2] = fma(2.0 * ux, sx, (rxx + mxx) + A[0]);
+  a[6] = fma(2.0 * uy, sy, fma(ruy, uy, -mxx) + A[2]);
+  a[4] = fma(ux, sy, fma(uy, sx, (rxy - bxy) + A[1]));
+  a[5] = rxxy + A[3];
+  a[7] = fma(rxy, uy, A[4]);
+  a[8] = fma(rxxy, uy, A[5]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) hermite_line64(a[k], a[k + 3], a[k + 6]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) hermite_line64(a[3 * k], a[3 * k + 1], a[3 * k + 2]);
+  // rounded once to FP32
+#pragma unroll
+  for (int i = 0; i < kQ; ++i)
+    d[i] = (float)(a[cx(i) + 1 + 3 * (cy(i) + 1)] * (1.0 / (double)wdiv(i)));
   // magnetic BGK with E = u_x b_y - u_y b_x; the rest population from the
   // conservation of b, as in the FP32 collision
   const double E3 = 3.0 * fma(ux, by, -uy * bx);
