@@ -95,8 +95,6 @@ static void multi_t(const MultiPlan &M, const Domain &D, const void *src, void *
     march_t<C>(M, D, src, dst, st);
   else if (M.tile == 16)
     tile_b<C, 16>(M, D, src, dst, st);
-  else if (M.tile == 24)
-    tile_b<C, 24>(M, D, src, dst, st);
   else
     tile_b<C, 32>(M, D, src, dst, st);
 }
@@ -109,20 +107,30 @@ static int64_t tiles_per_cu(const Domain &D, int B, int T) {
 
 // The form and the number of steps of the next pass with n steps to go.
 //
-// Tiles of the smallest size whose workgroups are at most one per CU: a pass
-// is then one round, bound by latency (64^2 FP32: 16 x 16 tiles, 5 steps, 1.27
-// us per step against 3.12 one at a time; 128^2 1.64 / 3.26; 256^2 with 24 x
-// 24 2.55 / 3.92; 320^2 with 32 x 32 2.9 / 4.5; 400^2, 4 steps, 3.6 / 7.3; FP16 within
-// 15 % of these).  Above that the estimates decide between 32 x 32 tiles and
-// marching strips (512^2 FP32 5.7 / 9.6 in tiles, 768^2 9.8 / 20.0, 1024^2 14.9
-// / 30.5, 2048^2 45 / 108, 8192^2 586 / 1652 marching; FP16 1024^2 15.8 / 19.6,
-// 4096^2 155 / 222).  Short remainders stay one step at a time where the halo
-// costs more than the launches saved, and grids so narrow or short that the
-// estimate exceeds the one-step kernel's: two steps in 24 x 24 tiles at 256^2
-// measured 5.0 us per step against 3.9, three 3.9; FP16 grids narrower than
-// 128 nodes with more than one tile per CU 5.3 against 4.75.  Walls and forces
-// exist as tiles only: unforced up to six tiles per CU (FP16 four), forced (FP64
-// arithmetic) up to two: 512 x 256 4.5 / 5.9 us, but 1000 x 600 18.7 / 18.6.
+// Where the workgroups are at most one per CU, a pass is one round of tiles,
+// bound by latency: 16 x 16 tiles if they can take five steps or more (up to
+// seven), else 32 x 32 (up to nine), with as many steps as still give one
+// round (us per step, one at a time in brackets: 64^2 FP32 7 steps 1.17 (3.12),
+// 5 steps 1.28; 96^2 6 steps 1.40 (3.20); 128^2 5 steps 1.64 (3.26); 192^2, 32 x
+// 32, 9 steps 2.01 (3.50), 5 steps 2.41; 256^2 9 steps 2.26 (3.90), 5 steps 2.73;
+// 320^2 7 steps 2.53 (4.35); FP16 within 15 % of these; 24 x 24 tiles were
+// between the two or level with them everywhere).  The steps to go are shared
+// out evenly among the passes.  Above that the estimates decide between 32 x
+// 32 tiles and marching strips (512^2 FP32 5.7 / 9.6 in tiles, 768^2 9.8 / 20.0,
+// 1024^2 14.9 / 30.5, 2048^2 45 / 108, 8192^2 586 / 1652 marching; FP16 1024^2
+// 15.8 / 19.6, 4096^2 155 / 222).  Short remainders stay one step at a time
+// where the halo costs more than the launches saved, and grids so narrow or
+// short that the estimate exceeds the one-step kernel's: two steps in tiles at
+// 256^2 measured 5.0 us per step against 3.9, three 3.9; FP16 grids narrower
+// than 128 nodes with more than one tile per CU 5.3 against 4.75.
+//
+// Walls and forces exist as tiles only.  FP32 takes them at any size (tiles /
+// one step at a time, walls: 1000 x 600 13.2 / 17.6, 2048^2 73 / 124, 4001 x 2000
+// 137 / 312; walls and force 14.9 / 17.3, 86 / 118, 165 / 305); with FP16, half
+// the bytes, the one-step kernel is ahead beyond three tiles per CU (walls:
+// 700 x 500 8.2 / 8.5, 1000 x 600 12.4 / 11.4, 2048^2 70 / 59), forced beyond two
+// (700 x 500 9.8 / 9.9, 2048^2 86 / 76).  From nine tiles per CU on five steps
+// beat four (1500 x 1000 28.0 / 29.0, 2048^2 73 / 82).
 MultiPlan multi_plan(const Domain &D, int64_t n) {
   MultiPlan M{};
   if (n < 2 || D.feq || D.sr || D.nx > (1 << 30) || D.ny > (1 << 30)) return M;
@@ -130,15 +138,19 @@ MultiPlan multi_plan(const Domain &D, int64_t n) {
   auto tile = [&](int B, int T) {
     MultiPlan P{};
     P.tile = B;
-    P.steps = n < T ? (int)n : T;
+    const int64_t passes = (n + T - 1) / T;
+    P.steps = (int)((n + passes - 1) / passes);
     return P;
   };
-  if (tiles_per_cu(D, 16, 5) == 1) return tile(16, 5);
-  if (n >= 4 && tiles_per_cu(D, 24, 5) == 1) return tile(24, 5);
+  for (int T = 7; T >= 5; --T)
+    if (tiles_per_cu(D, 16, T) == 1) return tile(16, T);
+  if (n >= 4)
+    for (int T = 9; T >= 6; --T)
+      if (tiles_per_cu(D, 32, T) == 1) return tile(32, T);
   int T = 5;
   int64_t q = tiles_per_cu(D, 32, 5);
   const int64_t q4 = tiles_per_cu(D, 32, 4);
-  if (tile32_us(4, q4) / 4 < tile32_us(5, q) / 5) {
+  if (q <= 8 && tile32_us(4, q4) / 4 < tile32_us(5, q) / 5) {
     T = 4;
     q = q4;
   }
@@ -146,7 +158,7 @@ MultiPlan multi_plan(const Domain &D, int64_t n) {
   const bool tiles = n >= 4 && (q == 1 || ((D.elem == 4 || D.nx >= 128) &&
                                            tile32_us(T, q) / T < 1.1 * single));
   if (D.walls || forced)
-    return tiles && q <= (forced ? 2 : (D.elem == 4 ? 6 : 4)) ? tile(32, T) : M;
+    return tiles && (D.elem == 4 || q <= (forced ? 2 : 3)) ? tile(32, T) : M;
   if (tiles && q == 1) return tile(32, T);
   if ((int64_t)D.nx * D.ny < (n >= 4 ? 200000 : 400000)) return tiles ? tile(32, T) : M;
   const MarchWindows mw = march_windows(D.nx);

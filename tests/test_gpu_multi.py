@@ -71,6 +71,23 @@ def test_periodic_force_equals_single_steps(shape, storage):
     check(*pair(*shape, storage, force=(1e-6, -1e-6)), [2, 4, 5, 9])
 
 
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("shape", [(64, 64), (65, 64), (96, 97), (256, 256), (257, 256), (353, 351),
+                                   (416, 400)])
+def test_step_counts_of_one_round_tiles(shape, walls, storage):
+    """Grids on either side of where a pass of 5 .. 9 steps stops being one
+    round of tiles, with step counts that leave uneven passes."""
+    check(*pair(*shape, storage, walls=walls), [7, 8, 9, 10, 17, 19])
+
+
+@pytest.mark.parametrize("force", [(0.0, 0.0), (1e-6, 2e-6)])
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("shape", [(1300, 1111), (3001, 700)])
+def test_many_tiles_per_cu(shape, walls, force):
+    check(*pair(*shape, "f32", walls=walls, force=force), [4, 5, 9])
+
+
 @pytest.mark.parametrize("shape", [(100, 90), (1001, 640)])
 def test_planar_layout_scale_and_graph(shape):
     check(*pair(*shape, "f32", layout="planar"), [5, 6])
