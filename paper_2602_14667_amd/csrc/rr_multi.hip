@@ -15,10 +15,12 @@ namespace rr {
 // nodes each, times 4 / wx strips of `rows` rows (wx = 4 unless the grid is
 // narrower than that).  Eight neighbouring workgroups of every 64 share an XCD.
 //
-// Bound by the vector ALU: 8192^2 FP32, 4 steps per pass, 586 us per step
-// (114 GLUPS, 88 % of the issue rate at ~265 instructions per node and 56 of
-// 64 lanes storing) against 1652 us one step at a time, which HBM bounds.
-// Four steps and not more: 2 / 3 / 4 / 6 steps measured 1076 / 725 / 586 /
+// Bound by the vector ALU, and at sizes far past the caches by HBM as well:
+// 8192^2 FP32, 4 steps per pass, 572 us per step (117 GLUPS; 82 % of the issue
+// rate at ~240 instructions per node with 56 of 64 lanes storing, and 4.8 TB/s,
+// what a copy reaches) against 1652 us one step at a time; 4096^2 FP16 148 us
+// (90 % of the issue rate) against 222.
+// Four steps and not more: 2 / 3 / 4 / 6 steps measured, when four took 586, 1076 / 725 / 586 /
 // 625 us per step (six lose 12 of 64 lanes to the halo); two nodes per lane
 // need twice the delay registers and measured 694 us at three steps.  Four
 // neighbouring windows of 56 nodes are 7 x 128 B lines in FP32.
@@ -117,8 +119,8 @@ static int64_t tiles_per_cu(const Domain &D, int B, int T) {
 // between the two or level with them everywhere).  The steps to go are shared
 // out evenly among the passes.  Above that the estimates decide between 32 x
 // 32 tiles and marching strips (512^2 FP32 5.7 / 9.6 in tiles, 768^2 9.8 / 20.0,
-// 1024^2 14.9 / 30.5, 2048^2 45 / 108, 8192^2 586 / 1652 marching; FP16 1024^2
-// 15.8 / 19.6, 4096^2 155 / 222).  Short remainders stay one step at a time
+// 1024^2 14.9 / 30.5, 2048^2 45 / 108, 8192^2 572 / 1652 marching; FP16 1024^2
+// 15.8 / 19.6, 4096^2 148 / 222).  Short remainders stay one step at a time
 // where the halo costs more than the launches saved, and grids so narrow or
 // short that the estimate exceeds the one-step kernel's: two steps in tiles at
 // 256^2 measured 5.0 us per step against 3.9, three 3.9; FP16 grids narrower
