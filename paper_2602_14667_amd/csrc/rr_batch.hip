@@ -291,11 +291,11 @@ static hipError_t launch_one(rrmhd_batch *b, hipStream_t st) {
 }
 
 // The multi-step form of the ensemble (fills the domains' fields and the
-// workgroup list): the smallest square tiles that are at most one per CU (bound
-// by latency), else the faster estimate of 32 x 32 tiles and marching strips,
-// if that beats one step per launch.  21 domains of sides 64 .. 1024 (7.5 M
-// nodes, FP32): 91 us per step marching against 218 one step at a time; 256
-// domains (90.9 M nodes): 873 against 2450.
+// workgroup list): one round of square tiles with as many steps as that takes
+// (bound by latency; the sizes of multi_plan), else the faster estimate of 32 x
+// 32 tiles and marching strips, if that beats one step per launch.  21 domains
+// of sides 64 .. 1024 (7.5 M nodes, FP32): 85 us per step marching against 218
+// one step at a time; 256 domains (90.9 M nodes): 873 against 2450.
 static int plan_multi(rrmhd_batch *b) {
   auto tiles = [&](int B, int T) {
     const int64_t out = B - 2 * (T - 1);
@@ -313,11 +313,11 @@ static int plan_multi(rrmhd_batch *b) {
   if (!fits) return RRMHD_OK;
   const double single = rr::single_us(bytes);
   int tile = 0, T = 5, rows = 0;
-  if (tiles(16, 5) <= rr::kCUs) {
-    tile = 16;
-  } else if (tiles(24, 5) <= rr::kCUs) {
-    tile = 24;
-  } else {
+  for (int t = 7; t >= 5 && !tile; --t)
+    if (tiles(16, t) <= rr::kCUs) tile = 16, T = t;
+  for (int t = 9; t >= 6 && !tile; --t)
+    if (tiles(32, t) <= rr::kCUs) tile = 32, T = t;
+  if (!tile) {
     const double q5 = std::ceil((double)tiles(32, 5) / rr::kCUs);
     const double q4 = std::ceil((double)tiles(32, 4) / rr::kCUs);
     double best = rr::tile32_us(5, q5) / 5;
@@ -377,8 +377,6 @@ static void launch_multi_t(const rrmhd_batch *b, int T, hipStream_t st) {
   hipLaunchKernelGGL((kernel), grid, dim3(block), 0, st, b->d_doms, b->d_wg_dom, __VA_ARGS__)
   if (b->multi_tile == 16)
     RR_LAUNCH((rr::k_batch_tiles<C, 16>), 256, T, b->s, b->inv_s, src, dst);
-  else if (b->multi_tile == 24)
-    RR_LAUNCH((rr::k_batch_tiles<C, 24>), 576, T, b->s, b->inv_s, src, dst);
   else if (b->multi_tile == 32)
     RR_LAUNCH((rr::k_batch_tiles<C, 32>), 1024, T, b->s, b->inv_s, src, dst);
   else if (T == 4)
@@ -545,6 +543,10 @@ int rrmhd_batch_set_fetch(rrmhd_batch *b, int tiles_per_fetch) {
 static int plain_steps(rrmhd_batch *b, int64_t n, hipStream_t st) {
   while (n > 0) {
     int64_t T = b->multi && b->multi_steps > 1 ? std::min<int64_t>(n, b->multi_steps) : 1;
+    if (T > 1 && b->multi_tile) {  // the steps to go in even passes
+      const int64_t passes = (n + T - 1) / T;
+      T = (n + passes - 1) / passes;
+    }
     // short remainders in tiles larger than 16 nodes: as for a single grid
     if (T < 4 && b->multi_tile > 16) T = 1;
     if (T > 1)

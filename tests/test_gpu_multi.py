@@ -124,7 +124,8 @@ def test_nonfinite_values_spread_as_in_single_steps():
         ref.close()
 
 
-ENSEMBLES = [[(1, 1), (2, 3), (64, 64)], [(96, 64), (33, 70), (160, 96)],
+ENSEMBLES = [[(1, 1), (2, 3), (64, 64)], [(64, 40), (24, 24)], [(96, 96), (65, 80)],
+             [(256, 129), (96, 100)], [(96, 64), (33, 70), (160, 96)],
              [(224, 225), (130, 64), (64, 190)], [(400, 300), (96, 96), (57, 211)],
              [(1024, 640), (64, 64), (113, 700), (56, 40), (7, 900)],
              [(448, 448)] * 9 + [(225, 31)]]
