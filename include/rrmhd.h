@@ -187,6 +187,10 @@ int rrmhd_current_vorticity(rrmhd *h, double *jz, double *wz);
 /* Host out[5] = mass sum rho, momentum sum_i c_i f_i (x, y), total field
  * sum b (x, y), FP64, over the current state.  Synchronises the stream. */
 int rrmhd_invariants(rrmhd *h, double out[5]);
+/* Both at once, from one pass over the state: E_kin, E_mag, max|div b| as
+ * rrmhd_diagnostics gives them (RRMHD_ENONFINITE likewise), then the five
+ * invariants. */
+int rrmhd_record(rrmhd *h, double out[8]);
 
 /* Steps taken since rrmhd_init (host value, no synchronisation). */
 int rrmhd_step_count(const rrmhd *h, int64_t *out);

@@ -547,6 +547,15 @@ int rrmhd_invariants(rrmhd *h, double out[5]) {
   return RRMHD_OK;
 }
 
+int rrmhd_record(rrmhd *h, double out[8]) {
+  if (!h || !out) return RRMHD_EINVAL;
+  if (!h->ready) return RRMHD_ESTATE;
+  int rc = run_diag(h);
+  if (rc != RRMHD_OK) return rc;
+  for (int k = 3; k < 8; ++k) out[k] = h->diag_host[k];
+  return diag_results(h, &out[0], &out[1], &out[2]);
+}
+
 int rrmhd_step_count(const rrmhd *h, int64_t *out) {
   if (!h || !out) return RRMHD_EINVAL;
   *out = h->steps;

@@ -21,7 +21,8 @@ FEQ_ALGORITHM, FEQ_FULL_MAXWELL = 0, 1
 
 EXPORTED = [
     "rrmhd_create", "rrmhd_init", "rrmhd_step", "rrmhd_moments",
-    "rrmhd_diagnostics", "rrmhd_diagnostics_noalloc", "rrmhd_invariants", "rrmhd_step_count",
+    "rrmhd_diagnostics", "rrmhd_diagnostics_noalloc", "rrmhd_invariants", "rrmhd_record",
+    "rrmhd_step_count",
     "rrmhd_state_bytes", "rrmhd_save_state", "rrmhd_load_state", "rrmhd_save", "rrmhd_load",
     "rrmhd_set_launch", "rrmhd_get_launch", "rrmhd_set_stream", "rrmhd_set_equilibrium", "rrmhd_set_graph_chunk",
     "rrmhd_set_debug_poison",
@@ -91,6 +92,7 @@ def lib():
                                                 ctypes.POINTER(ctypes.c_double),
                                                 ctypes.POINTER(ctypes.c_double)]
         L.rrmhd_invariants.argtypes = [vp, ctypes.POINTER(ctypes.c_double)]
+        L.rrmhd_record.argtypes = [vp, ctypes.POINTER(ctypes.c_double)]
         L.rrmhd_step_count.argtypes = [vp, ctypes.POINTER(i64)]
         L.rrmhd_state_bytes.argtypes = [vp]
         L.rrmhd_state_bytes.restype = i64
@@ -443,8 +445,11 @@ class Solver:
                 k = min(int(every), left)
                 self.step(k)
                 left -= k
-                ek, em, dv = self.diagnostics(allow_nonfinite=True)
-                inv = self.invariants()
+                v = (ctypes.c_double * 8)()
+                rc = lib().rrmhd_record(self._h, v)
+                if rc != ENONFINITE:
+                    _check(rc, "rrmhd_record")
+                (ek, em, dv), inv = v[:3], v[3:]
                 rec = {"step": self.step_count, "E_kin": fin(ek), "E_mag": fin(em),
                        "max_div_b": fin(dv), "mass": fin(inv[0]),
                        "momentum": [fin(inv[1]), fin(inv[2])],

@@ -774,3 +774,24 @@ def test_stochastic_rounding_refusals():
     assert R.lib().rrmhd_set_graph_chunk(s._h, 4) == R.EINVAL
     assert R.lib().rrmhd_set_equilibrium(s._h, R.FEQ_FULL_MAXWELL) == R.EINVAL
     s.close()
+
+
+@pytest.mark.parametrize("walls,inplace", [(False, False), (True, False), (False, True)])
+def test_record_equals_diagnostics_and_invariants(walls, inplace):
+    """One pass gives what the two calls give, bit for bit, and the same
+    error for a state that is not finite."""
+    import ctypes
+    R = rrmhd()
+    s = R.Solver(70, 45, 0.55, 0.6, inplace=inplace, walls=walls)
+    u, b = inputs.random_modes(70, 45, 0.05, seed=2)
+    for bad in (False, True):
+        if bad:
+            u[0, 3, 5] = np.nan
+        s.init(dev(u), dev(b))
+        s.step(3)
+        v = (ctypes.c_double * 8)()
+        rc = R.lib().rrmhd_record(s._h, v)
+        assert rc == (R.ENONFINITE if bad else 0)
+        want = list(s.diagnostics(allow_nonfinite=True)) + s.invariants()
+        assert np.array_equal(np.array(v[:]), np.array(want), equal_nan=True)
+    s.close()
