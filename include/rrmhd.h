@@ -55,7 +55,9 @@ enum {
 /* Population storage.  Both store f_i - w_i for the fluid populations and
  * g_j for the magnetic ones, times the codec scale; arithmetic is FP32.
  * RRMHD_STORE_INPLACE may be OR-ed into rrmhd_grid.storage: the handle then
- * holds one population buffer instead of two (half the device memory).  Its
+ * holds one population buffer instead of two (half the device memory; a
+ * handle of up to 64 MiB of state keeps a second one all the same and steps
+ * as a two-buffer handle does, which for such grids is the faster).  Its
  * steps alternate between two forms that each write only the locations they
  * have just read: a pull of the upstream populations whose results go into
  * the slots just read for the opposite directions, then a read of the node's

@@ -79,6 +79,12 @@ int scratch_address(int *dev_out, void **out) {
 
 }  // namespace
 
+// Up to this state size a single-buffer handle keeps a second buffer all the
+// same, for passes of several steps: the memory saved would be negligible, and
+// such grids are bound by launches (256^2 FP32 2.26 us per step against 3.70,
+// 900 x 880 12.0 against 20.2).
+constexpr size_t kSmallState = (size_t)64 << 20;
+
 struct rrmhd {
   rr::Domain D{};
   int storage = 0;
@@ -111,8 +117,8 @@ struct rrmhd {
   // after the caller's stream with events
   int graph_chunk = 0;
   bool poison = false;  // debug: NaN-fill the destination buffer before each step
-  hipGraphExec_t graph[2] = {nullptr, nullptr};
-  int graph_flip[2] = {0, 0};  // whether a replay of it ends in the other buffer / phase
+  hipGraphExec_t graph[4] = {nullptr, nullptr, nullptr, nullptr};
+  int graph_flip[4] = {0, 0, 0, 0};  // whether a replay of it ends in the other buffer / phase
   hipStream_t own = nullptr;
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
 };
@@ -304,7 +310,7 @@ int rrmhd_create(const rrmhd_grid *grid, double tau_f, double tau_m,
     h->poison = !h->inplace && std::atoi(e) != 0;
   const size_t bytes = h->bytes;
   int rc = RRMHD_OK;
-  for (int k = 0; k < (h->inplace ? 1 : 2) && rc == RRMHD_OK; ++k) {
+  for (int k = 0; k < (h->inplace && bytes > kSmallState ? 1 : 2) && rc == RRMHD_OK; ++k) {
     hipError_t e = hipMalloc(&h->buf[k], bytes);
     if (e != hipSuccess) rc = dev_err(e, "hipMalloc(populations)");
   }
@@ -377,15 +383,19 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b) {
 }
 
 static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
-  const bool multi = h->multi && !h->inplace && !h->closure_on;
+  // a small single-buffer handle (kSmallState) takes the passes of a
+  // two-buffer one from its usual layout; its graphs keep to the phases
+  const bool multi =
+      h->multi && !h->closure_on && (!h->inplace || (h->buf[1] && h->graph_chunk <= 0));
   while (n > 0) {
     rr::MultiPlan M{};
-    if (multi) M = rr::multi_plan(h->D, n);
+    if (multi && !h->phase) M = rr::multi_plan(h->D, n);
     int64_t taken = 1;
     // random bits of the stochastic-rounding codec: keyed by the step count
     h->D.sr_key = rr::mix32((uint32_t)h->steps * 0x27d4eb2fu + 0x165667b1u);
-    if (h->inplace) {
-      HIP_OR_RETURN(rr::launch_step_inplace(h->storage, h->D, h->buf[0], h->phase, h->shape, st));
+    if (h->inplace && M.steps <= 1) {
+      HIP_OR_RETURN(
+          rr::launch_step_inplace(h->storage, h->D, h->buf[h->cur], h->phase, h->shape, st));
       h->phase ^= 1;
     } else {
       if (h->poison) HIP_OR_RETURN(poison_buffer(h, h->buf[h->cur ^ 1], st));
@@ -417,7 +427,7 @@ int rrmhd_step(rrmhd *h, int64_t n) {
   HIP_OR_RETURN(hipStreamWaitEvent(h->own, h->ev_in, 0));
   int64_t left = n;
   while (left >= chunk) {
-    const int state = h->inplace ? h->phase : h->cur;
+    const int state = h->inplace ? h->phase + 2 * h->cur : h->cur;
     hipGraphExec_t &g = h->graph[state];
     if (!g) {
       hipGraph_t graph = nullptr;
@@ -601,7 +611,7 @@ int rrmhd_save_state(rrmhd *h, void *dst, int64_t bytes) {
   if (!h || !dst || bytes < rrmhd_state_bytes(h)) return RRMHD_EINVAL;
   if (!h->ready) return RRMHD_ESTATE;
   if (h->inplace && h->phase) {
-    HIP_OR_RETURN(rr::launch_swapped_to_pull(h->storage, h->D, h->buf[0], dst, h->stream));
+    HIP_OR_RETURN(rr::launch_swapped_to_pull(h->storage, h->D, h->buf[h->cur], dst, h->stream));
     return RRMHD_OK;
   }
   HIP_OR_RETURN(copy_planes(h, dst, (const char *)h->buf[h->cur], false));
@@ -754,7 +764,7 @@ int rrmhd_save(rrmhd *h, const char *path) {
   if (h->inplace && h->phase) {
     // between the two step forms: gather the swapped layout first
     HIP_OR_RETURN(hipMalloc(&tmp, row * rr::kStatePlanes));
-    hipError_t e = rr::launch_swapped_to_pull(h->storage, h->D, h->buf[0], tmp, h->stream);
+    hipError_t e = rr::launch_swapped_to_pull(h->storage, h->D, h->buf[h->cur], tmp, h->stream);
     if (e != hipSuccess) {
       (void)hipFree(tmp);
       return dev_err(e, "launch_swapped_to_pull");

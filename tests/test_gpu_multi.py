@@ -88,6 +88,34 @@ def test_many_tiles_per_cu(shape, walls, force):
     check(*pair(*shape, "f32", walls=walls, force=force), [4, 5, 9])
 
 
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("shape", [(1, 3), (64, 64), (250, 130), (800, 700)])
+def test_small_single_buffer_handles(shape, walls, storage):
+    """Single-buffer handles below the size that keeps a second buffer, from
+    either phase, either buffer, after a load and around graph replays,
+    against the alternating one-step kernels."""
+    got, ref = pair(*shape, storage, walls=walls, inplace=True)
+    check_steps(got, ref, [1, 4, 5, 9, 1, 1, 3, 2, 7])
+    s = state(ref)
+    for h in (got, ref):
+        h.load_state(s, 40)
+    check_steps(got, ref, [5, 1])
+    for chunk in (3, 0, 3):
+        got.set_graph_chunk(chunk)
+        check_steps(got, ref, [7, 6, 5])
+    got.close()
+    ref.close()
+
+
+def check_steps(got, ref, counts):
+    for n in counts:
+        got.step(n)
+        ref.step(n)
+        assert got.step_count == ref.step_count
+        assert torch.equal(state(got), state(ref)), n
+
+
 @pytest.mark.parametrize("shape", [(100, 90), (1001, 640)])
 def test_planar_layout_scale_and_graph(shape):
     check(*pair(*shape, "f32", layout="planar"), [5, 6])
