@@ -392,7 +392,8 @@ static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
     if (multi && !h->phase) M = rr::multi_plan(h->D, n);
     int64_t taken = 1;
     // random bits of the stochastic-rounding codec: keyed by the step count
-    h->D.sr_key = rr::mix32((uint32_t)h->steps * 0x27d4eb2fu + 0x165667b1u);
+    h->D.sr_step = (uint32_t)h->steps;
+    h->D.sr_key = rr::sr_step_key(h->D.sr_step);
     if (h->inplace && M.steps <= 1) {
       HIP_OR_RETURN(
           rr::launch_step_inplace(h->storage, h->D, h->buf[h->cur], h->phase, h->shape, st));

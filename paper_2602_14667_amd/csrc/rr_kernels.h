@@ -25,6 +25,7 @@ struct Domain {
                      // cross terms of the third and fourth orders (ablation)
   int sr = 0;             // FP16 storage written with stochastic rounding
   uint32_t sr_key = 0;    // its per-step key (set before each step)
+  uint32_t sr_step = 0;   // the step's number, for passes of several steps
 };
 
 struct LaunchShape {

@@ -40,11 +40,15 @@ __host__ __device__ constexpr int delay_slot(int p, int cyv) {
 }
 constexpr int kDelayZero = delay_slot(kPlanes, 0), kDelayPlus = delay_slot(kPlanes, 1);
 
-// The value a step stores and the next one reads back.
+// The value a step stores and the next one reads back (seed, plane: the random
+// bits of the stochastic-rounding codec).
 template <class C>
-__device__ __forceinline__ float through_storage(float v, float s, float inv_s) {
+__device__ __forceinline__ float through_storage(float v, float s, float inv_s, uint32_t seed = 0,
+                                                 int plane = 0) {
   if constexpr (std::is_same_v<C, CodecF32>)
     return v;
+  else if constexpr (codec_sr<C>::value)
+    return C::dec(C::enc_sr(v, s, sr_plane(seed, plane)), inv_s);
   else
     return C::dec(C::enc(v, s), inv_s);
 }
@@ -221,7 +225,7 @@ __device__ __forceinline__ void tile_steps(const Domain &D, float (&ex)[2][kMovi
   }
   const bool lo = WALLS && y == 0, hi = WALLS && y == D.ny - 1;
   const CollideParams P{D.om_c, D.omm_c, D.Gx, D.Gy, D.src_c};
-  const PlaneGeom G{D.plane, D.nx, D.ny, D.s, D.inv_s, 0u, D.row};
+  PlaneGeom G{D.plane, D.nx, D.ny, D.s, D.inv_s, D.sr_key, D.row};
   float v[kPlanes];
   float(&d)[kQ] = *reinterpret_cast<float(*)[kQ]>(v);
   float(&g)[2 * kQm] = *reinterpret_cast<float(*)[2 * kQm]>(v + kQ);
@@ -234,9 +238,11 @@ __device__ __forceinline__ void tile_steps(const Domain &D, float (&ex)[2][kMovi
     collide<FORCED>(d, g, P);
     if (s == T) break;
     float(&b)[kMoving][N] = ex[s & 1];
+    const uint32_t seed = node_seed<C>(G, x, y);
+    if constexpr (codec_sr<C>::value) G.sr_key = sr_step_key(D.sr_step + s);  // of the next step
 #pragma unroll
     for (int p = 0; p < kPlanes; ++p) {
-      v[p] = through_storage<C>(v[p], D.s, D.inv_s);
+      v[p] = through_storage<C>(v[p], D.s, D.inv_s, seed, p);
       if (plane_moves(p)) b[moving_slot(p)][t] = v[p];
     }
     __syncthreads();

@@ -126,6 +126,11 @@ static int64_t tiles_per_cu(const Domain &D, int B, int T) {
 // 256^2 measured 5.0 us per step against 3.9, three 3.9; FP16 grids narrower
 // than 128 nodes with more than one tile per CU 5.3 against 4.75.
 //
+// Stochastic rounding draws its bits per step, node and plane, so a pass
+// reproduces them, at about half the collision's instructions again: it takes
+// the passes that are one round of tiles (64^2 1.51 us per step against 3.65,
+// 256^2 3.22 against 4.05), where launches and not instructions are what costs.
+//
 // Walls and forces exist as tiles only.  FP32 takes them at any size (tiles /
 // one step at a time, walls: 1000 x 600 13.2 / 17.6, 2048^2 73 / 124, 4001 x 2000
 // 137 / 312; walls and force 14.9 / 17.3, 86 / 118, 165 / 305); with FP16, half
@@ -135,7 +140,7 @@ static int64_t tiles_per_cu(const Domain &D, int B, int T) {
 // beat four (1500 x 1000 28.0 / 29.0, 2048^2 73 / 82).
 MultiPlan multi_plan(const Domain &D, int64_t n) {
   MultiPlan M{};
-  if (n < 2 || D.feq || D.sr || D.nx > (1 << 30) || D.ny > (1 << 30)) return M;
+  if (n < 2 || D.feq || D.nx > (1 << 30) || D.ny > (1 << 30)) return M;
   const bool forced = D.Gx != 0.0f || D.Gy != 0.0f;
   auto tile = [&](int B, int T) {
     MultiPlan P{};
@@ -149,6 +154,7 @@ MultiPlan multi_plan(const Domain &D, int64_t n) {
   if (n >= 4)
     for (int T = 9; T >= 6; --T)
       if (tiles_per_cu(D, 32, T) == 1) return tile(32, T);
+  if (D.sr) return M;
   int T = 5;
   int64_t q = tiles_per_cu(D, 32, 5);
   const int64_t q4 = tiles_per_cu(D, 32, 4);
@@ -189,7 +195,11 @@ MultiPlan multi_plan(const Domain &D, int64_t n) {
 
 hipError_t launch_multi(const MultiPlan &M, int storage, const Domain &D, const void *src,
                         void *dst, hipStream_t st) {
-  if (storage != kF16)
+  if (storage == kF16 && D.sr && M.tile == 16)
+    tile_b<CodecF16SR, 16>(M, D, src, dst, st);
+  else if (storage == kF16 && D.sr)
+    tile_b<CodecF16SR, 32>(M, D, src, dst, st);
+  else if (storage != kF16)
     multi_t<CodecF32>(M, D, src, dst, st);
   else if (D.s == 1.0f)
     multi_t<CodecF16U>(M, D, src, dst, st);

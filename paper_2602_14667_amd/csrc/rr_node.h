@@ -173,6 +173,10 @@ __host__ __device__ __forceinline__ uint32_t mix32(uint32_t h) {
   h ^= h >> 16;
   return h;
 }
+// The key of a step, from the number of steps taken before it.
+__host__ __device__ __forceinline__ uint32_t sr_step_key(uint32_t step) {
+  return mix32(step * 0x27d4eb2fu + 0x165667b1u);
+}
 // Random bits for the plane p of a node: a node seed from the step key k and
 // the node's in-plane byte offset o (computed once per node), then one
 // multiply-xorshift round over a Weyl sequence in the plane number.

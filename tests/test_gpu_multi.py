@@ -81,6 +81,14 @@ def test_step_counts_of_one_round_tiles(shape, walls, storage):
     check(*pair(*shape, storage, walls=walls), [7, 8, 9, 10, 17, 19])
 
 
+@pytest.mark.parametrize("kw", [{}, {"walls": True, "b_wall": (0.001, 0.02)}, {"inplace": True},
+                                {"force": (1e-6, 2e-6)}, {"codec_scale": 4.0}])
+@pytest.mark.parametrize("shape", [(1, 3), (64, 64), (97, 101), (256, 250), (353, 351)])
+def test_stochastic_rounding_equals_single_steps(shape, kw):
+    """The random bits of every step, node and plane inside a pass."""
+    check(*pair(*shape, "f16sr", **kw), [1, 2, 7, 9, 13])
+
+
 @pytest.mark.parametrize("force", [(0.0, 0.0), (1e-6, 2e-6)])
 @pytest.mark.parametrize("walls", [False, True])
 @pytest.mark.parametrize("shape", [(1300, 1111), (3001, 700)])
