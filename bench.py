@@ -7,13 +7,16 @@ tau_f = tau_m = 0.52 (the largest relaxation time of the stated range
 0.5005-0.52; at 0.51 and below the FP32 run turns non-finite within 2000
 steps, while at 0.52 it stays finite over 10,000), FP32 arithmetic, populations stored as FP32 offsets
 f - w (``--storage f16`` for the FP16-offset codec).  A step is one fused
-stream-and-collide launch over all 67,108,864 nodes; inputs are resident in
+stream-and-collide update of all 67,108,864 nodes; inputs are resident in
 HBM before timing starts.  By default 10,000 steps (the configuration's
 horizon) are timed after 100 warm-up steps.
 
 Prints one JSON line.  MLUPS = nodes x steps / seconds / 1e6.  The roofline
-object prices the step kernel's algorithmic traffic (19 reads + 19 writes
-per node: 152 B in FP32 storage, 76 B in FP16) per launch against 8 TB/s.
+object prices the algorithmic traffic of a launch (19 reads + 19 writes per
+node: 152 B in FP32 storage, 76 B in FP16) against 8 TB/s.  A launch of the
+default form takes several steps over the state (STEPS_PER_LAUNCH) and reads
+and writes it once; single-buffer handles, the equilibrium ablation and
+stochastic rounding take one.
 """
 import argparse
 import json
@@ -27,6 +30,11 @@ sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0
 BYTES_PER_NODE = {"f32": 152, "f16": 76, "f16sr": 76}
+# steps per launch of the default form on periodic grids of 1024^2 and more and
+# on the 256-domain ensemble (csrc/rr_multi.hip, csrc/rr_batch.hip)
+STEPS_PER_LAUNCH = 4
+
+
 def kernel_hash():
     from paper_2602_14667_amd import kernel_hash as kh
     return kh()
@@ -282,7 +290,7 @@ def time_batch_leg(torch, rrmhd, inputs, steps, autotune, sequential):
             seq_ms += f0.elapsed_time(f1) / 20
             s.close()
     b.close()
-    gbs = 152 * nodes / ms / 1e6
+    gbs = 152 * nodes / (STEPS_PER_LAUNCH * ms) / 1e6
     return {
         "value": round(nodes / ms / 1e3, 1), "unit": "MLUPS", "steps": steps,
         "warmup": chunk, "ms_per_step": round(ms, 4),
@@ -295,6 +303,7 @@ def time_batch_leg(torch, rrmhd, inputs, steps, autotune, sequential):
         "roofline": {"bound": "hbm", "achieved": round(gbs, 1),
                      "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": round(gbs / PEAK_HBM_GBS, 4),
+                     "steps_per_launch": STEPS_PER_LAUNCH,
                      "traffic": None if autotune else batch_traffic()},
         "sequential_standalone_ms_per_step": None if seq_ms is None else round(seq_ms, 4),
         "speedup_vs_sequential": None if seq_ms is None else round(seq_ms / ms, 3)}
@@ -633,9 +642,14 @@ def time_turbulence_leg(torch, rrmhd, args, fields, storage):
     ud, bd = fields
     s = rrmhd.Solver(n, n, args.tau, args.tau, storage=storage,
                      equilibrium=args.equilibrium, inplace=args.inplace)
-    launch = ("library default (row-interleaved planes, eight neighbouring tiles per "
-              "XCD, NT stores; f32: 128x2 threads, two nodes per thread in 64-bit words; "
-              "f16: 128x1 threads, four nodes per thread in 64-bit words)")
+    passes = (storage != "f16sr" and args.equilibrium == "algorithm" and not args.inplace
+              and n >= 1024)
+    per = STEPS_PER_LAUNCH if passes else 1
+    launch = (f"library default (row-interleaved planes; marching passes of {per} steps, "
+              "wavefronts of 56 stored nodes, four to a workgroup, eight neighbouring workgroups "
+              "per XCD)")
+    if n < 1024:
+        launch = "library default (LDS tiles or marching strips, several steps per launch)"
     if storage == "f16sr":
         launch = ("library default (row-interleaved planes, eight neighbouring tiles per XCD, "
                   "NT stores, 128x1 threads, one node per thread)")
@@ -676,16 +690,17 @@ def time_turbulence_leg(torch, rrmhd, args, fields, storage):
     s.close()
     nodes = n * n
     sec = ms_launches / 1e3
-    per_launch = sec / args.steps
-    achieved = BYTES_PER_NODE[storage] * nodes / per_launch / 1e9
+    per_step = sec / args.steps
+    achieved = BYTES_PER_NODE[storage] * nodes / (per * per_step) / 1e9
     # the stored counter readings belong to the method's own step kernel
     traffic = (measured_traffic(storage, n)
                if args.equilibrium == "algorithm" and not args.inplace else None)
     return {"value": round(nodes * args.steps / sec / 1e6, 1), "unit": "MLUPS",
-            "ms_per_step": round(1e3 * per_launch, 4), "launch": launch,
+            "ms_per_step": round(1e3 * per_step, 4), "launch": launch,
             "roofline": {"bound": "hbm", "achieved": round(achieved, 1),
                          "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                         "frac": round(achieved / PEAK_HBM_GBS, 4), "traffic": traffic},
+                         "frac": round(achieved / PEAK_HBM_GBS, 4),
+                         "steps_per_launch": per, "traffic": traffic},
             "wall_s_timed": round(wall, 4),
             "diagnostics_after": {k: (v if math.isfinite(v) else None) for k, v in
                                   (("E_kin", ek), ("E_mag", em), ("max_div_b", dv))},

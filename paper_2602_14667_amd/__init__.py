@@ -8,9 +8,11 @@ __all__ = ["rrmhd", "inputs"]
 
 # Sources of the step kernels; their hash tags measured traffic figures so a
 # figure taken on another kernel version is not reported.
-KERNEL_SOURCES = ("csrc/rr_node.h", "csrc/rr_pull.h", "csrc/rr_kernels.hip")
+KERNEL_SOURCES = ("csrc/rr_node.h", "csrc/rr_pull.h", "csrc/rr_walls.h", "csrc/rr_kernels.hip",
+                  "csrc/rr_multi.h", "csrc/rr_multi.hip")
 KERNEL3D_SOURCES = ("csrc/rr_node.h", "csrc/rr_pull.h", "csrc/rr_3d.hip")
-BATCH_SOURCES = ("csrc/rr_node.h", "csrc/rr_pull.h", "csrc/rr_batch.hip")
+BATCH_SOURCES = ("csrc/rr_node.h", "csrc/rr_pull.h", "csrc/rr_walls.h", "csrc/rr_multi.h",
+                 "csrc/rr_batch.hip")
 
 
 def kernel_hash(sources=KERNEL_SOURCES) -> str:

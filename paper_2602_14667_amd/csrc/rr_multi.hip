@@ -19,7 +19,8 @@ namespace rr {
 // 8192^2 FP32, 4 steps per pass, 572 us per step (117 GLUPS; 82 % of the issue
 // rate at ~240 instructions per node with 56 of 64 lanes storing, and 4.8 TB/s,
 // what a copy reaches) against 1652 us one step at a time; 4096^2 FP16 148 us
-// (90 % of the issue rate) against 222.
+// (90 % of the issue rate) against 222.  Counters at 8192^2: VALU busy 88 %, reads 1.25 x
+// the state (a workgroup of four windows reads nine lines for the seven it stores).
 // Four steps and not more: 2 / 3 / 4 / 6 steps measured, when four took 586, 1076 / 725 / 586 /
 // 625 us per step (six lose 12 of 64 lanes to the halo); two nodes per lane
 // need twice the delay registers and measured 694 us at three steps.  Four

@@ -60,6 +60,19 @@ def counter_mean(d, match):
     return sum(vals) / len(vals) if vals else None
 
 
+def steps_per_launch(name):
+    """Time steps a launch of the kernel takes: the second template argument
+    of the marching passes, else one."""
+    m = re.search(r"march<[^,<>]+, (\d+)>", name)
+    return int(m.group(1)) if m else 1
+
+
+def step_kernel(stats, one_step, passes):
+    """The step kernel of a run: the form with several steps per launch where
+    it ran, else the one whose name contains `one_step`."""
+    return ([k for k in stats if passes in k] or [k for k in stats if one_step in k])[0]
+
+
 def main(prof, out, n):
     n = int(n)
     nodes = n * n
@@ -71,12 +84,13 @@ def main(prof, out, n):
     copy_ns = [v for k, v in copy.items() if "k_copy16" in k][0]["avg_ns"]
     for st, bpn in (("f32", 152), ("f16", 76)):
         stats = kernel_stats(os.path.join(prof, f"stats_{st}"))
-        name = [k for k in stats if "k_step" in k][0]
-        avg = stats[name]["avg_ns"]
-        rd = counter_mean(os.path.join(prof, f"pmc_FETCH_SIZE_{st}"), "k_step") * 1024 * fac["FETCH_SIZE"]
-        wr = counter_mean(os.path.join(prof, f"pmc_WRITE_SIZE_{st}"), "k_step") * 1024 * fac["WRITE_SIZE"]
+        name = step_kernel(stats, "k_step", "k_march")
+        avg, per = stats[name]["avg_ns"], steps_per_launch(name)
+        rd = counter_mean(os.path.join(prof, f"pmc_FETCH_SIZE_{st}"), name) * 1024 * fac["FETCH_SIZE"]
+        wr = counter_mean(os.path.join(prof, f"pmc_WRITE_SIZE_{st}"), name) * 1024 * fac["WRITE_SIZE"]
         alg = bpn * nodes
         traffic = {"kernel": name, "kernel_hash": kernel_hash(), "n": n, "storage": st,
+                   "steps_per_launch": per,
                    "bytes_per_launch": rd + wr, "read_bytes": rd, "write_bytes": wr,
                    "algorithmic_bytes": alg, "fetch_factor": fac["FETCH_SIZE"],
                    "write_factor": fac["WRITE_SIZE"]}
@@ -89,9 +103,9 @@ def main(prof, out, n):
             "",
             "Commands (from the repository root, on the MI355X host):",
             "```",
-            f"rocprofv3 --kernel-trace --stats --output-format csv -d {prof}/stats_{st} -o run -- python3 bench.py --storage {st} --steps 50 --warmup 5 --no-cpu-baseline --no-f16-leg --no-ensemble-leg",
-            f"rocprofv3 --pmc FETCH_SIZE --output-format csv -d {prof}/pmc_FETCH_SIZE_{st} -o run -- python3 bench.py --storage {st} --steps 5 --warmup 1 --no-cpu-baseline --no-f16-leg --no-ensemble-leg",
-            f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d {prof}/pmc_WRITE_SIZE_{st} -o run -- python3 bench.py --storage {st} --steps 5 --warmup 1 --no-cpu-baseline --no-f16-leg --no-ensemble-leg",
+            f"rocprofv3 --kernel-trace --stats --output-format csv -d {prof}/stats_{st} -o run -- python3 bench.py --storage {st} --steps 48 --warmup 4 --no-cpu-baseline --no-f16-leg --no-ensemble-leg",
+            f"rocprofv3 --pmc FETCH_SIZE --output-format csv -d {prof}/pmc_FETCH_SIZE_{st} -o run -- python3 bench.py --storage {st} --steps 8 --warmup 4 --no-cpu-baseline --no-f16-leg --no-ensemble-leg",
+            f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d {prof}/pmc_WRITE_SIZE_{st} -o run -- python3 bench.py --storage {st} --steps 8 --warmup 4 --no-cpu-baseline --no-f16-leg --no-ensemble-leg",
             f"rocprofv3 --kernel-trace --stats --output-format csv -d {prof}/stats_copy -o run -- python3 bench.py --mode copy --steps 20",
             f"rocprofv3 --pmc FETCH_SIZE --output-format csv -d {prof}/pmc_FETCH_SIZE_copy -o run -- python3 bench.py --mode copy --steps 5 --warmup 1",
             f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d {prof}/pmc_WRITE_SIZE_copy -o run -- python3 bench.py --mode copy --steps 5 --warmup 1",
@@ -105,8 +119,9 @@ def main(prof, out, n):
             lines.append(f"| `{k[:90]}` | {v['calls']} | {v['avg_ns']:.0f} | {v['min_ns']:.0f} | {v['max_ns']:.0f} |")
         lines += [
             "",
-            f"* nodes per launch: {nodes}; algorithmic bytes per launch: {alg / 1e9:.3f} GB ({bpn} B/node)",
-            f"* average launch: {avg / 1e3:.1f} us -> {nodes / avg * 1e3:.0f} MLUPS, "
+            f"* nodes per launch: {nodes}; steps per launch: {per}; algorithmic bytes per launch "
+            f"(the state read and written once): {alg / 1e9:.3f} GB ({bpn} B/node)",
+            f"* average launch: {avg / 1e3:.1f} us -> {per * nodes / avg * 1e3:.0f} MLUPS, "
             f"{alg / avg:.1f} GB/s algorithmic = {alg / avg / 8000 * 100:.1f} % of 8 TB/s",
             f"* HBM traffic per launch (PMC, calibrated): read {rd / 1e9:.3f} GB "
             f"({rd / (alg / 2):.3f}x algorithmic), write {wr / 1e9:.3f} GB ({wr / (alg / 2):.3f}x); "
@@ -202,8 +217,8 @@ def step3d_summary(prof, out, n):
     fac = _calibration(prof)
     stats = kernel_stats(os.path.join(prof, "s3_stats"))
     cmd = f"python3 bench.py --workload turbulence3d --n3d {n}"
-    for st, codec, bpn in (("f32", "CodecF32>", 384), ("f16", "CodecF16U>", 192)):
-        name = [k for k in stats if "k_step3<" in k and codec in k][0]
+    for st, codec, bpn in (("f32", "CodecF32", 384), ("f16", "CodecF16U", 192)):
+        name = [k for k in stats if re.search(r"k_step3<[^,<>]*" + codec + "[,>]", k)][0]
         avg = stats[name]["avg_ns"]
         rd = counter_mean(os.path.join(prof, "s3_pmc_FETCH_SIZE"), name) * 1024 * fac["FETCH_SIZE"]
         wr = counter_mean(os.path.join(prof, "s3_pmc_WRITE_SIZE"), name) * 1024 * fac["WRITE_SIZE"]
@@ -273,10 +288,12 @@ def closure_summary(prof, out, n):
     fac = _calibration(prof)
     stats = kernel_stats(os.path.join(prof, "cl_stats"))
     cl = [k for k in stats if "k_step_closure" in k][0]
-    # the plain step: one node per thread or the multi-node form
-    pl = [k for k in stats if "k_step<" in k or "k_step_multi<" in k][0]
-    m_pl = "k_step_multi<" if "k_step_multi<" in pl else "k_step<"
-    t_cl, t_pl = stats[cl]["avg_ns"], stats[pl]["avg_ns"]
+    # the plain step: a pass of several steps, one node per thread or the
+    # multi-node form
+    pl = [k for k in stats if "k_march<" in k or "k_step<" in k or "k_step_multi<" in k]
+    pl = max(pl, key=lambda k: stats[k]["calls"])
+    m_pl, per_pl = pl, steps_per_launch(pl)
+    t_cl, t_pl = stats[cl]["avg_ns"], stats[pl]["avg_ns"] / per_pl
     rd = counter_mean(os.path.join(prof, "cl_pmc_FETCH_SIZE"), "k_step_closure") * 1024 * fac["FETCH_SIZE"]
     wr = counter_mean(os.path.join(prof, "cl_pmc_WRITE_SIZE"), "k_step_closure") * 1024 * fac["WRITE_SIZE"]
     sq = os.path.join(prof, "cl_pmc_sq")
@@ -301,9 +318,9 @@ def closure_summary(prof, out, n):
         f"rocprofv3 --kernel-trace --stats --output-format csv -d {prof}/cl_stats -o run -- {cmd} --steps 50 --warmup 5",
         f"rocprofv3 --pmc SQ_WAVES SQ_INSTS_VALU SQ_INSTS_MFMA SQ_INSTS_LDS SQ_ACTIVE_INST_VALU "
         f"SQ_VALU_MFMA_BUSY_CYCLES SQ_LDS_IDX_ACTIVE SQ_LDS_BANK_CONFLICT GRBM_GUI_ACTIVE "
-        f"--output-format csv -d {prof}/cl_pmc_sq -o run -- {cmd} --steps 3 --warmup 1",
-        f"rocprofv3 --pmc FETCH_SIZE --output-format csv -d {prof}/cl_pmc_FETCH_SIZE -o run -- {cmd} --steps 3 --warmup 1",
-        f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d {prof}/cl_pmc_WRITE_SIZE -o run -- {cmd} --steps 3 --warmup 1",
+        f"--output-format csv -d {prof}/cl_pmc_sq -o run -- {cmd} --steps 4 --warmup 4",
+        f"rocprofv3 --pmc FETCH_SIZE --output-format csv -d {prof}/cl_pmc_FETCH_SIZE -o run -- {cmd} --steps 4 --warmup 4",
+        f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d {prof}/cl_pmc_WRITE_SIZE -o run -- {cmd} --steps 4 --warmup 4",
         f"python -m paper_2602_14667_amd.profsum closure {prof} profiles {n}",
         "```",
         "",
@@ -316,7 +333,7 @@ def closure_summary(prof, out, n):
     lines += [
         "",
         f"* closure step: average launch {t_cl / 1e3:.1f} us = {t_cl / t_pl:.2f}x the plain step "
-        f"({t_pl / 1e3:.1f} us); {nodes / t_cl * 1e3:.0f} MLUPS; {alg / t_cl:.1f} GB/s algorithmic "
+        f"({t_pl / 1e3:.1f} us, {per_pl} per launch); {nodes / t_cl * 1e3:.0f} MLUPS; {alg / t_cl:.1f} GB/s algorithmic "
         f"= {alg / t_cl / 8000 * 100:.1f} % of 8 TB/s; network work 9600 FLOP/node -> "
         f"{9600 * nodes / t_cl / 1e3:.1f} TFLOP/s = {9600 * nodes / t_cl / 1e3 / 2500 * 100:.1f} % of "
         "the 2.5 PFLOP/s BF16 peak",
@@ -335,11 +352,12 @@ def closure_summary(prof, out, n):
     # clock: VALU quad-cycles x 4 and MFMA busy cycles over 1024 SIMDs, LDS
     # active cycles over 256 CUs
     clk = 2.4e9
-    for tag, t in (("closure", t_cl), ("plain", t_pl)):
+    for tag, t in (("closure", t_cl), ("plain", t_pl * per_pl)):
         c = ctr[tag]
         if None in c.values():
             continue
-        per = 64 / nodes  # wave instructions -> lane instructions per node
+        # wave instructions -> lane instructions per node and step
+        per = 64 / nodes / (per_pl if tag == "plain" else 1)
         simd_cyc = simds * t * 1e-9 * clk
         cu_cyc = cus * t * 1e-9 * clk
         lines.append(
@@ -361,32 +379,32 @@ def batch_summary(prof, out):
     from . import batch_hash
     fac = _calibration(prof)
     stats = kernel_stats(os.path.join(prof, "batch_stats"))
-    name = [k for k in stats if "k_batch_step" in k][0]
-    avg, cnt, _ = last_dispatches(os.path.join(prof, "batch_stats"), "k_batch_step", 100)
-    rd = counter_mean(os.path.join(prof, "batch_pmc_FETCH_SIZE"), "k_batch_step") * 1024 * fac["FETCH_SIZE"]
-    wr = counter_mean(os.path.join(prof, "batch_pmc_WRITE_SIZE"), "k_batch_step") * 1024 * fac["WRITE_SIZE"]
+    name = step_kernel(stats, "k_batch_step", "k_batch_march")
+    per = steps_per_launch(name)
+    avg, cnt, _ = last_dispatches(os.path.join(prof, "batch_stats"), name, 100 // per)
+    rd = counter_mean(os.path.join(prof, "batch_pmc_FETCH_SIZE"), name) * 1024 * fac["FETCH_SIZE"]
+    wr = counter_mean(os.path.join(prof, "batch_pmc_WRITE_SIZE"), name) * 1024 * fac["WRITE_SIZE"]
     from .inputs import batch_domains
     nodes = sum(d["side"] ** 2 for d in batch_domains(256, seed=0))
     alg = 152 * nodes
     traffic = {"kernel": name, "kernel_hash": batch_hash(), "nodes": nodes, "storage": "f32",
-               "bytes_per_launch": rd + wr, "read_bytes": rd, "write_bytes": wr,
+               "steps_per_launch": per, "bytes_per_launch": rd + wr, "read_bytes": rd, "write_bytes": wr,
                "algorithmic_bytes": alg, "fetch_factor": fac["FETCH_SIZE"],
                "write_factor": fac["WRITE_SIZE"]}
     with open(os.path.join(out, "traffic_batch_f32_256.json"), "w") as fh:
         json.dump(traffic, fh, indent=1)
     cmd = "python3 bench.py --workload batch --no-autotune --no-cpu-baseline"
     lines = [
-        "# batched ensemble step, 256 domains (sides 64..1024), FP32, default launch "
-        "(one workgroup per 32x8 tile)",
+        "# batched ensemble step, 256 domains (sides 64..1024), FP32, default launch",
         "",
         f"Kernel: `{name}`  (source hash {batch_hash()})",
         "",
         "Commands (from the repository root, on the MI355X host; the copy calibration runs as "
         "for the two-dimensional step summaries):",
         "```",
-        f"rocprofv3 --kernel-trace --stats --output-format csv -d {prof}/batch_stats -o run -- {cmd} --steps 100 --warmup 5",
-        f"rocprofv3 --pmc FETCH_SIZE --output-format csv -d {prof}/batch_pmc_FETCH_SIZE -o run -- {cmd} --steps 5 --warmup 1",
-        f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d {prof}/batch_pmc_WRITE_SIZE -o run -- {cmd} --steps 5 --warmup 1",
+        f"rocprofv3 --kernel-trace --stats --output-format csv -d {prof}/batch_stats -o run -- {cmd} --steps 100 --warmup 4",
+        f"rocprofv3 --pmc FETCH_SIZE --output-format csv -d {prof}/batch_pmc_FETCH_SIZE -o run -- {cmd} --steps 8 --warmup 4",
+        f"rocprofv3 --pmc WRITE_SIZE --output-format csv -d {prof}/batch_pmc_WRITE_SIZE -o run -- {cmd} --steps 8 --warmup 4",
         f"python -m paper_2602_14667_amd.profsum batch {prof} profiles",
         "```",
         "",
@@ -398,9 +416,10 @@ def batch_summary(prof, out):
                      f"| {v['max_ns']:.0f} |")
     lines += [
         "",
-        f"* nodes per launch: {nodes}; algorithmic bytes per launch: {alg / 1e9:.3f} GB (152 B/node)",
+        f"* nodes per launch: {nodes}; steps per launch: {per}; algorithmic bytes per launch "
+        f"(the state read and written once): {alg / 1e9:.3f} GB (152 B/node)",
         f"* last {cnt} dispatches (the timed region): average {avg / 1e3:.1f} us -> "
-        f"{nodes / avg * 1e3:.0f} MLUPS, {alg / avg:.1f} GB/s algorithmic = "
+        f"{per * nodes / avg * 1e3:.0f} MLUPS, {alg / avg:.1f} GB/s algorithmic = "
         f"{alg / avg / 8000 * 100:.1f} % of 8 TB/s",
         f"* HBM traffic per launch (PMC, calibrated): read {rd / 1e9:.3f} GB "
         f"({rd / (alg / 2):.3f}x algorithmic), write {wr / 1e9:.3f} GB ({wr / (alg / 2):.3f}x); "
