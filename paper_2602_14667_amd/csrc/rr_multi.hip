@@ -177,7 +177,13 @@ MultiPlan multi_plan(const Domain &D, int64_t n) {
   W.groups_x = (mw.n + W.wx - 1) / W.wx;
   const int64_t strips = 4 / W.wx;  // strips per workgroup
   double best = 0.0;
-  for (int k = 1; k <= 16; ++k) {
+  // five workgroups are resident per CU; up to about 12 M nodes one such round
+  // with longer strips beats the estimate's choice (2500^2 FP32 62.6 against
+  // 66.4 us per step, 3000^2 84.5 / 87.6, FP16 77.1 / 78.4), past that more and
+  // shorter strips even out (8192^2 FP32 549 against 567, FP16 473 / 509, 4096^2
+  // FP16 133 / 136)
+  const int kmax = (int64_t)D.nx * D.ny < 12000000 ? 5 : 16;
+  for (int k = 1; k <= kmax; ++k) {
     const int64_t groups_y = kCUs * k / W.groups_x > 0 ? kCUs * k / W.groups_x : 1;
     int rows = (int)((D.ny + groups_y * strips - 1) / (groups_y * strips));
     if (rows < 3) rows = 3;
