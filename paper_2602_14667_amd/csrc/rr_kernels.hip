@@ -490,16 +490,18 @@ __device__ __forceinline__ void g_at(const Domain &D, const typename C::T *__res
 }
 
 // One pass over the state: per-node moments and their FP64 sums, and
-// max |div b| from b staged in LDS.  Persistent workgroups of 4 waves take
-// tiles of kDTX x ROWS nodes; each tile's b, plus a one-node ring around it
+// max |div b| from b staged in LDS.  Persistent workgroups take
+// tiles of kDTX x kDTY nodes; each tile's b, plus a one-node ring around it
 // (periodic wrap; zero beyond a wall, where div b is not evaluated), goes
 // to LDS, so every node's populations are read once for its moments and
 // only the ring's magnetic planes are read again.  Tile cells that lie past
-// a ragged edge hold the b of the node they wrap to.  Tiles are 16 rows high
-// where that gives every CU one, else 4 (256^2: 5.8 us against 9.0, the 64
-// tiles of 16 rows leaving three CUs in four idle).
-constexpr int kDTX = 64;
-template <class C, bool WALLS, bool SWAPPED, int kDTY>
+// a ragged edge hold the b of the node they wrap to.
+// On grids of few tiles more, lower ones would fill the chip (256^2: tiles of 4
+// rows 5.8 us, these 7.3), but change the order of the sums, which for a
+// vanishing momentum is all there is to them; one row per wave in workgroups
+// of 16 waves keeps the order and takes 9.6.
+constexpr int kDTX = 64, kDTY = 16;
+template <class C, bool WALLS, bool SWAPPED>
 __global__ __launch_bounds__(kDiagBlock) void k_diag_tile(Domain D,
                                                           const typename C::T *__restrict__ src,
                                                           double *__restrict__ part_s,
@@ -596,7 +598,7 @@ __global__ __launch_bounds__(kDiagBlock) void k_diag_tile(Domain D,
 }
 
 // The closing sums: all eight values of a partial are loaded at once and
-// reduced together (256^2: 3.9 us against 5.4 value by value).
+// reduced together (256^2: 3.9 to 4.4 us against 5.4 value by value).
 __global__ __launch_bounds__(kDiagBlock) void k_diag_final(
     const double *__restrict__ part_s, int nb, const double *__restrict__ part_m, double inv_n2,
     double *__restrict__ out) {
@@ -1061,12 +1063,8 @@ hipError_t launch_swapped_to_pull(int storage, const Domain &D, const void *buf,
 // Workgroups of a diagnostics launch: a fixed count, so the order of the
 // FP64 sums depends on the grid size only (not on a kernel's register
 // allocation); at most one per tile.
-static int64_t diag_tiles(const Domain &D, int rows) {
-  return (int64_t)((D.nx + kDTX - 1) / kDTX) * ((D.ny + rows - 1) / rows);
-}
-static int diag_rows(const Domain &D) { return diag_tiles(D, 16) >= 256 ? 16 : 4; }
 static int diag_grid(const Domain &D) {
-  const int64_t tiles = diag_tiles(D, diag_rows(D));
+  const int64_t tiles = (int64_t)((D.nx + kDTX - 1) / kDTX) * ((D.ny + kDTY - 1) / kDTY);
   return (int)(tiles < kDiagGrid ? tiles : kDiagGrid);
 }
 
@@ -1074,22 +1072,14 @@ size_t diag_work_bytes(const Domain &) {
   return sizeof(double) * (size_t)(kDiagGrid * kSums + kDiagGrid);
 }
 
-template <class C, bool SW, int ROWS>
-static void diag_t(const Domain &D, int nb, const void *src, double *ps, double *pm,
-                   hipStream_t st) {
-  auto s = (const typename C::T *)src;
-  if (D.walls)
-    hipLaunchKernelGGL((k_diag_tile<C, true, SW, ROWS>), dim3(nb), dim3(kDiagBlock), 0, st, D, s, ps, pm);
-  else
-    hipLaunchKernelGGL((k_diag_tile<C, false, SW, ROWS>), dim3(nb), dim3(kDiagBlock), 0, st, D, s, ps, pm);
-}
 template <class C, bool SW>
 static int diag_t(const Domain &D, const void *src, double *ps, double *pm, hipStream_t st) {
+  auto s = (const typename C::T *)src;
   const int nb = diag_grid(D);
-  if (diag_rows(D) == 16)
-    diag_t<C, SW, 16>(D, nb, src, ps, pm, st);
+  if (D.walls)
+    hipLaunchKernelGGL((k_diag_tile<C, true, SW>), dim3(nb), dim3(kDiagBlock), 0, st, D, s, ps, pm);
   else
-    diag_t<C, SW, 4>(D, nb, src, ps, pm, st);
+    hipLaunchKernelGGL((k_diag_tile<C, false, SW>), dim3(nb), dim3(kDiagBlock), 0, st, D, s, ps, pm);
   return nb;
 }
 
