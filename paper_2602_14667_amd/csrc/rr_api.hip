@@ -312,7 +312,13 @@ int rrmhd_create(const rrmhd_grid *grid, double tau_f, double tau_m,
   int rc = RRMHD_OK;
   for (int k = 0; k < (h->inplace && bytes > kSmallState ? 1 : 2) && rc == RRMHD_OK; ++k) {
     hipError_t e = hipMalloc(&h->buf[k], bytes);
-    if (e != hipSuccess) rc = dev_err(e, "hipMalloc(populations)");
+    if (e == hipSuccess) continue;
+    if (h->inplace && k == 1) {  // one buffer then
+      h->buf[1] = nullptr;
+      (void)hipGetLastError();
+    } else {
+      rc = dev_err(e, "hipMalloc(populations)");
+    }
   }
   if (rc == RRMHD_OK) {
     hipError_t e = hipMalloc((void **)&h->diag_out, 8 * sizeof(double));
@@ -382,14 +388,20 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b) {
   return RRMHD_OK;
 }
 
-static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
+// captured: the caller is recording the stream into a graph of its own, whose
+// replays continue from where the last one ended only if an even number of
+// steps ends in the buffer and the phase it started from: passes then take an
+// odd number of steps, so that every launch swaps the buffers as often as its
+// steps would one by one.
+static int plain_steps(rrmhd *h, int64_t n, hipStream_t st, bool captured = false) {
   // a small single-buffer handle (kSmallState) takes the passes of a
   // two-buffer one from its usual layout; its graphs keep to the phases
-  const bool multi =
-      h->multi && !h->closure_on && (!h->inplace || (h->buf[1] && h->graph_chunk <= 0));
+  const bool multi = h->multi && !h->closure_on &&
+                     (!h->inplace || (h->buf[1] && h->graph_chunk <= 0 && !captured));
   while (n > 0) {
     rr::MultiPlan M{};
     if (multi && !h->phase) M = rr::multi_plan(h->D, n);
+    if (captured && M.steps % 2 == 0 && M.steps > 0) M.steps -= 1;
     int64_t taken = 1;
     // random bits of the stochastic-rounding codec: keyed by the step count
     h->D.sr_step = (uint32_t)h->steps;
@@ -423,7 +435,8 @@ int rrmhd_step(rrmhd *h, int64_t n) {
   if (!h || n < 0) return RRMHD_EINVAL;
   if (!h->ready) return RRMHD_ESTATE;
   const int64_t chunk = h->graph_chunk;
-  if (chunk <= 0 || n < chunk) return plain_steps(h, n, h->stream);
+  if (chunk <= 0 || n < chunk)
+    return plain_steps(h, n, h->stream, rr_stream_captured(h->stream));
   HIP_OR_RETURN(hipEventRecord(h->ev_in, h->stream));
   HIP_OR_RETURN(hipStreamWaitEvent(h->own, h->ev_in, 0));
   int64_t left = n;

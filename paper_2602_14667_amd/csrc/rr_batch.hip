@@ -540,13 +540,15 @@ int rrmhd_batch_set_fetch(rrmhd_batch *b, int tiles_per_fetch) {
   return RRMHD_OK;
 }
 
-static int plain_steps(rrmhd_batch *b, int64_t n, hipStream_t st) {
+// captured: as for a single grid, an odd number of steps per pass
+static int plain_steps(rrmhd_batch *b, int64_t n, hipStream_t st, bool captured = false) {
   while (n > 0) {
     int64_t T = b->multi && b->multi_steps > 1 ? std::min<int64_t>(n, b->multi_steps) : 1;
     if (T > 1 && b->multi_tile) {  // the steps to go in even passes
       const int64_t passes = (n + T - 1) / T;
       T = (n + passes - 1) / passes;
     }
+    if (captured && T % 2 == 0) T -= 1;
     // short remainders in tiles larger than 16 nodes: as for a single grid
     if (T < 4 && b->multi_tile > 16) T = 1;
     if (T > 1)
@@ -565,7 +567,7 @@ int rrmhd_batch_step(rrmhd_batch *b, int64_t n) {
   for (int d = 0; d < b->n; ++d)
     if (b->init_step[d] < 0) return RRMHD_ESTATE;
   const int64_t chunk = b->graph_chunk;
-  if (chunk <= 0 || n < chunk) return plain_steps(b, n, b->user);
+  if (chunk <= 0 || n < chunk) return plain_steps(b, n, b->user, rr_stream_captured(b->user));
   // graph path: order the internal stream after the caller's work
   BHIP(hipEventRecord(b->ev_in, b->user));
   BHIP(hipStreamWaitEvent(b->own, b->ev_in, 0));

@@ -23,6 +23,17 @@ RR_HIDDEN void rr_handle_default_launch(rrmhd *h);
 // 1 when the handle keeps its planes row-interleaved
 RR_HIDDEN int rr_handle_rows(const rrmhd *h);
 }
+// whether the caller is recording the stream into a graph (the null stream
+// cannot be)
+static inline bool rr_stream_captured(hipStream_t st) {
+  if (!st) return false;
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return c != hipStreamCaptureStatusNone;
+}
 // record the HIP message of a device error for rrmhd_last_error_detail and
 // map it to RRMHD_ENOMEM or RRMHD_EDEVICE
 RR_HIDDEN int rr_device_error(hipError_t e, const char *what);

@@ -116,6 +116,47 @@ def test_small_single_buffer_handles(shape, walls, storage):
     ref.close()
 
 
+@pytest.mark.parametrize("shape,n,kw", [((64, 64), 10, {}), ((200, 190), 4, {}),
+                                        ((200, 190), 16, {"walls": True}), ((900, 800), 4, {}),
+                                        ((900, 800), 6, {}), ((200, 190), 4, {"inplace": True})])
+def test_steps_recorded_by_the_caller_replay(shape, n, kw):
+    """An even number of steps recorded into a caller's graph continues from
+    where its last replay ended, with eager steps in between."""
+    from paper_2602_14667_amd import rrmhd
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        got, ref = pair(*shape, "f32", **kw)
+        both = [(got, ref)]
+        batches = [rrmhd.Batch([shape, (70, 40)], [0.55, 0.6], [0.6, 0.55]) for _ in range(2)]
+        if not kw:
+            batches[1].set_shape(-1, 32, 0, -1)
+            for d, (nx, ny) in enumerate([shape, (70, 40)]):
+                u, b = (0.02 * torch.randn(2, ny, nx, dtype=torch.float64, device="cuda")
+                        for _ in range(2))
+                for h in batches:
+                    h.init(d, u, b)
+            both.append(tuple(batches))
+        for g, r in both:
+            g.step(2 * n)
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=st):
+                g.step(n)
+            for k in range(3):
+                graph.replay()
+                torch.cuda.synchronize()
+            g.step(2)
+            r.step(5 * n + 2)
+            fields = (lambda h: [h.moments(d) for d in range(2)]) if g is batches[0] else \
+                (lambda h: [h.moments()])
+            for a, c in zip(fields(g), fields(r)):
+                for x, y in zip(a, c):
+                    assert torch.equal(x, y)
+            torch.cuda.synchronize()
+            g.close()
+            r.close()
+
+
 def check_steps(got, ref, counts):
     for n in counts:
         got.step(n)
