@@ -261,10 +261,12 @@ __device__ __forceinline__ double block_sum64(double a, double *red) {
 // |j_bar(t + fac) - j_bar(t)|^2 in a fixed tree, so that the closing sum reads
 // one value per workgroup instead of walking Nc values in a single one
 // (512^2: 258 us of one workgroup's serial loads became 4.7, and 2 here).
-__global__ __launch_bounds__(256) void k_onestep_prep(const double *__restrict__ flt0, const double *__restrict__ flt1,
-                               const double *__restrict__ feat, int nc, double omega,
-                               float *__restrict__ x, float *__restrict__ r0,
-                               double *__restrict__ dm) {
+__global__ __launch_bounds__(256) void k_onestep_prep(const double *__restrict__ flt0,
+                                                      const double *__restrict__ flt1,
+                                                      const double *__restrict__ feat, int nc,
+                                                      double omega, float *__restrict__ x,
+                                                      float *__restrict__ r0,
+                                                      double *__restrict__ dm) {
   const int64_t Nc = (int64_t)nc * nc;
   const int64_t own = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t c = own < Nc ? own : Nc - 1;  // past the end: the last node again, not stored
