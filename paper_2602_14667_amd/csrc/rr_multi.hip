@@ -124,8 +124,9 @@ static int64_t tiles_per_cu(const Domain &D, int B, int T) {
 // 15.8 / 19.6, 4096^2 148 / 222).  Short remainders stay one step at a time
 // where the halo costs more than the launches saved, and grids so narrow or
 // short that the estimate exceeds the one-step kernel's: two steps in tiles at
-// 256^2 measured 5.0 us per step against 3.9, three 3.9; FP16 grids narrower
-// than 128 nodes with more than one tile per CU 5.3 against 4.75.
+// 256^2 measured 5.0 us per step against 3.9, three 3.9.  Narrow FP16 grids: 33 x
+// 6000 5.7 / 8.7 in tiles, 100 x 3000 6.9 / 8.4, 64 x 3000 level, 127 x 8000 one
+// step at a time 16.2 (tiles 18.3).
 //
 // Stochastic rounding draws its bits per step, node and plane, so a pass
 // reproduces them, at about half the collision's instructions again: it takes
@@ -164,8 +165,7 @@ MultiPlan multi_plan(const Domain &D, int64_t n) {
     q = q4;
   }
   const double single = single_us((double)D.nx * D.ny * D.elem * kStatePlanes);
-  const bool tiles = n >= 4 && (q == 1 || ((D.elem == 4 || D.nx >= 128) &&
-                                           tile32_us(T, q) / T < 1.1 * single));
+  const bool tiles = n >= 4 && (q == 1 || tile32_us(T, q) / T < 1.1 * single);
   if (D.walls || forced)
     return tiles && (D.elem == 4 || q <= (forced ? 2 : 3)) ? tile(32, T) : M;
   if (tiles && q == 1) return tile(32, T);

@@ -74,7 +74,7 @@ def test_periodic_force_equals_single_steps(shape, storage):
 @pytest.mark.parametrize("storage", ["f32", "f16"])
 @pytest.mark.parametrize("walls", [False, True])
 @pytest.mark.parametrize("shape", [(64, 64), (65, 64), (96, 97), (256, 256), (257, 256), (353, 351),
-                                   (416, 400)])
+                                   (416, 400), (106, 2594), (67, 3001)])
 def test_step_counts_of_one_round_tiles(shape, walls, storage):
     """Grids on either side of where a pass of 5 .. 9 steps stops being one
     round of tiles, with step counts that leave uneven passes."""
