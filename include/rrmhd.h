@@ -141,7 +141,12 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b);
  * with its default launch takes two to five steps per pass over the state
  * where the grid has a form for it (not with stochastic rounding, the
  * closure or the equilibrium ablation); the state after n steps is bit for
- * bit that of n passes of one step.  Asynchronous. */
+ * bit that of n passes of one step.  Calls on the handle may be recorded into
+ * a graph of the caller's and its replays mixed with direct calls, as with one
+ * step per pass: an even number of recorded steps starts from where the last
+ * replay and an even number of direct steps have left the state.  From the
+ * first recorded call on, passes take an odd number of steps (one step on a
+ * single buffer).  Asynchronous. */
 int rrmhd_step(rrmhd *h, int64_t n);
 
 /* Pre-collision macroscopic fields of the current state (task 1): rho

@@ -9,6 +9,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <utility>
 
 #include "../../include/rrmhd.h"
 #include "rr_closure.h"
@@ -93,7 +94,9 @@ struct rrmhd {
   rrmhd_bc bc{};
   hipStream_t stream = nullptr;
   void *buf[2] = {nullptr, nullptr};
-  int cur = 0;
+  int cur = 0;  // buf[cur] holds the state: the parity of the steps taken (one buffer: 0)
+  int swapped = 0;  // whether buf[0] and buf[1] have changed names (rename_buffers)
+  bool recorded = false;  // a call was recorded into a graph of the caller's
   int64_t steps = 0;
   bool inplace = false;  // one population buffer (alternating step phases)
   size_t bytes = 0;      // bytes of one population buffer
@@ -113,7 +116,7 @@ struct rrmhd {
   bool closure_on = false;
   int closure_grid = 0;         // persistent blocks of the closure kernel
   // graph replay of runs of graph_chunk steps (0: plain launches); one graph
-  // per starting buffer (or in-place phase), on an internal stream ordered
+  // per starting allocation (and in-place phase), on an internal stream ordered
   // after the caller's stream with events
   int graph_chunk = 0;
   bool poison = false;  // debug: NaN-fill the destination buffer before each step
@@ -140,6 +143,24 @@ static hipError_t poison_buffer(const rrmhd *h, void *buf, hipStream_t st) {
 static void free_graphs(rrmhd *h) {
   for (auto &g : h->graph)
     if (g) (void)hipGraphExecDestroy(g), g = nullptr;
+}
+
+// A pass of several steps changes the buffer once.  Where as many single steps
+// would have ended in the buffer they started from (an even number, or any on
+// one buffer), the two buffers change names, so that cur stays what single
+// steps make it and init and load_state write the buffer they always wrote.
+static void rename_buffers(rrmhd *h) {
+  std::swap(h->buf[0], h->buf[1]);
+  h->swapped ^= 1;
+}
+
+// A graph that the caller records keeps the addresses of the buffers.  Its
+// replays mix with direct calls as those of single steps do only while the
+// buffers keep their names, so from the first recorded call on a handle takes
+// an odd number of steps per pass (as many changes of buffer as its steps make
+// one by one), and single steps on one buffer.
+static void note_recording(rrmhd *h) {
+  if (!h->recorded) h->recorded = rr_stream_captured(h->stream);
 }
 
 // The default launch shape, several steps per launch where a form applies.
@@ -379,6 +400,7 @@ int rrmhd_set_equilibrium(rrmhd *h, int kind) {
 
 int rrmhd_init(rrmhd *h, const double *u, const double *b) {
   if (!h || !u || !b) return RRMHD_EINVAL;
+  note_recording(h);
   HIP_OR_RETURN(rr::launch_init(h->storage, h->D, u, b, h->bc.b_wall[0],
                                 h->bc.b_wall[1], h->buf[0], h->stream));
   h->cur = 0;
@@ -388,27 +410,25 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b) {
   return RRMHD_OK;
 }
 
-// captured: the caller is recording the stream into a graph of its own, whose
-// replays continue from where the last one ended only if an even number of
-// steps ends in the buffer and the phase it started from: passes then take an
-// odd number of steps, so that every launch swaps the buffers as often as its
-// steps would one by one.
-static int plain_steps(rrmhd *h, int64_t n, hipStream_t st, bool captured = false) {
+static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
   // a small single-buffer handle (kSmallState) takes the passes of a
   // two-buffer one from its usual layout; its graphs keep to the phases
   const bool multi = h->multi && !h->closure_on &&
-                     (!h->inplace || (h->buf[1] && h->graph_chunk <= 0 && !captured));
+                     (!h->inplace || (h->buf[1] && h->graph_chunk <= 0 && !h->recorded));
+  // one buffer: an odd number of steps has been taken in passes, which leave
+  // the phase alone
+  bool owed = false;
   while (n > 0) {
     rr::MultiPlan M{};
-    if (multi && !h->phase) M = rr::multi_plan(h->D, n);
-    if (captured && M.steps % 2 == 0 && M.steps > 0) M.steps -= 1;
+    // one buffer: an odd total leaves its last step to the phases
+    if (multi && !h->phase) M = rr::multi_plan(h->D, h->inplace ? n - ((n + owed) & 1) : n);
+    if (h->recorded && M.steps > 0 && M.steps % 2 == 0) M.steps -= 1;
     int64_t taken = 1;
     // random bits of the stochastic-rounding codec: keyed by the step count
     h->D.sr_step = (uint32_t)h->steps;
     h->D.sr_key = rr::sr_step_key(h->D.sr_step);
-    if (h->inplace && M.steps <= 1) {
-      HIP_OR_RETURN(
-          rr::launch_step_inplace(h->storage, h->D, h->buf[h->cur], h->phase, h->shape, st));
+    if (h->inplace && M.steps <= 1 && !owed) {
+      HIP_OR_RETURN(rr::launch_step_inplace(h->storage, h->D, h->buf[0], h->phase, h->shape, st));
       h->phase ^= 1;
     } else {
       if (h->poison) HIP_OR_RETURN(poison_buffer(h, h->buf[h->cur ^ 1], st));
@@ -421,9 +441,13 @@ static int plain_steps(rrmhd *h, int64_t n, hipStream_t st, bool captured = fals
         taken = M.steps;
       } else {
         HIP_OR_RETURN(rr::launch_step(h->storage, h->D, h->buf[h->cur], h->buf[h->cur ^ 1],
-                                      h->shape, st));
+                                      h->inplace ? rr::default_shape(h->D) : h->shape, st));
       }
-      h->cur ^= 1;
+      if (!h->inplace && (taken & 1))
+        h->cur ^= 1;
+      else
+        rename_buffers(h);
+      owed ^= h->inplace && (taken & 1);
     }
     h->steps += taken;
     n -= taken;
@@ -434,23 +458,24 @@ static int plain_steps(rrmhd *h, int64_t n, hipStream_t st, bool captured = fals
 int rrmhd_step(rrmhd *h, int64_t n) {
   if (!h || n < 0) return RRMHD_EINVAL;
   if (!h->ready) return RRMHD_ESTATE;
+  note_recording(h);
   const int64_t chunk = h->graph_chunk;
-  if (chunk <= 0 || n < chunk)
-    return plain_steps(h, n, h->stream, rr_stream_captured(h->stream));
+  if (chunk <= 0 || n < chunk) return plain_steps(h, n, h->stream);
   HIP_OR_RETURN(hipEventRecord(h->ev_in, h->stream));
   HIP_OR_RETURN(hipStreamWaitEvent(h->own, h->ev_in, 0));
   int64_t left = n;
   while (left >= chunk) {
-    const int state = h->inplace ? h->phase + 2 * h->cur : h->cur;
+    const int state = h->inplace ? h->phase + 2 * h->swapped : h->cur ^ h->swapped;
     hipGraphExec_t &g = h->graph[state];
     if (!g) {
       hipGraph_t graph = nullptr;
-      const int c0 = h->cur, p0 = h->phase;
+      const int c0 = h->cur, p0 = h->phase, w0 = h->swapped;
       const int64_t s0 = h->steps;
       HIP_OR_RETURN(hipStreamBeginCapture(h->own, hipStreamCaptureModeThreadLocal));
       int rc = plain_steps(h, chunk, h->own);
       hipError_t ee = hipStreamEndCapture(h->own, &graph);
-      h->graph_flip[state] = h->inplace ? h->phase ^ p0 : h->cur ^ c0;
+      h->graph_flip[state] = h->inplace ? h->phase ^ p0 : (h->cur ^ h->swapped) ^ state;
+      if (h->swapped != w0) rename_buffers(h);
       h->cur = c0;  // the capture recorded the launches; nothing ran yet
       h->phase = p0;
       h->steps = s0;
@@ -463,9 +488,15 @@ int rrmhd_step(rrmhd *h, int64_t n) {
       (void)hipGraphDestroy(graph);
       if (ei != hipSuccess) return dev_err(ei, "hipGraphInstantiate");
     }
+    // built before the caller recorded its own, it may rename the buffers
+    if (h->recorded && h->graph_flip[state] != (chunk & 1)) break;
     HIP_OR_RETURN(hipGraphLaunch(g, h->own));
-    h->cur ^= h->inplace ? 0 : h->graph_flip[state];
-    h->phase ^= h->inplace ? h->graph_flip[state] : 0;
+    if (h->inplace) {
+      h->phase ^= h->graph_flip[state];
+    } else {
+      h->cur ^= (int)(chunk & 1);
+      if ((h->cur ^ h->swapped) != (state ^ h->graph_flip[state])) rename_buffers(h);
+    }
     h->steps += chunk;
     left -= chunk;
   }
@@ -500,6 +531,7 @@ int rrmhd_moments(rrmhd *h, double *rho, double *u, double *b) {
   if (!h) return RRMHD_EINVAL;
   if (!h->ready) return RRMHD_ESTATE;
   if (!rho && !u && !b) return RRMHD_OK;
+  note_recording(h);
   HIP_OR_RETURN(rr::launch_moments(h->storage, h->D, h->buf[h->cur], rho, u, b,
                                    h->stream, h->inplace ? h->phase : 0));
   return RRMHD_OK;
@@ -624,6 +656,7 @@ int64_t rrmhd_state_bytes(const rrmhd *h) {
 int rrmhd_save_state(rrmhd *h, void *dst, int64_t bytes) {
   if (!h || !dst || bytes < rrmhd_state_bytes(h)) return RRMHD_EINVAL;
   if (!h->ready) return RRMHD_ESTATE;
+  note_recording(h);
   if (h->inplace && h->phase) {
     HIP_OR_RETURN(rr::launch_swapped_to_pull(h->storage, h->D, h->buf[h->cur], dst, h->stream));
     return RRMHD_OK;
@@ -634,6 +667,7 @@ int rrmhd_save_state(rrmhd *h, void *dst, int64_t bytes) {
 
 int rrmhd_load_state(rrmhd *h, const void *src, int64_t bytes, int64_t step_count) {
   if (!h || !src || bytes < rrmhd_state_bytes(h) || step_count < 0) return RRMHD_EINVAL;
+  note_recording(h);
   HIP_OR_RETURN(copy_planes(h, const_cast<void *>(src), h->buf[0], true));
   h->cur = 0;
   h->phase = 0;
@@ -917,6 +951,7 @@ int rrmhd_closure_gelu_table(uint16_t *out, void *hip_stream) {
 int rrmhd_train_impose_fluid(rrmhd *h, const double *rho, const double *j, const double *b) {
   if (!h || !rho || !j || !b || h->D.walls || h->inplace) return RRMHD_EINVAL;
   if (!h->ready) return RRMHD_ESTATE;
+  note_recording(h);
   const int rc = rr_launch_impose_fluid(h->storage, &h->D, h->buf[h->cur], rho, j, b, h->stream);
   if (rc != RRMHD_OK) return rr_device_error(hipGetLastError(), "rrmhd_train_impose_fluid");
   return RRMHD_OK;
@@ -927,6 +962,7 @@ int rrmhd_current_vorticity(rrmhd *h, double *jz, double *wz) {
   if (!h->ready) return RRMHD_ESTATE;
   if (h->D.walls) return RRMHD_EINVAL;
   if (!jz && !wz) return RRMHD_OK;
+  note_recording(h);
   if (!h->fields_work)
     HIP_OR_RETURN(hipMalloc(&h->fields_work, sizeof(double) * 2 * (size_t)h->D.nx * h->D.ny));
   // velocity planes for the vorticity's gradient

@@ -18,6 +18,7 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "../../include/rrmhd.h"
@@ -199,8 +200,12 @@ struct rrmhd_batch {
   int *d_ctr = nullptr;  // dynamic-schedule counters (zero between launches)
   rr::BatchDom *d_doms = nullptr;
   int *d_tile_dom = nullptr;
+  // as for a single grid: cur is the parity of the steps taken, the buffers
+  // change names after a pass of an even number, and passes take an odd number
+  // once a call was recorded into a graph of the caller's
   void *buf[2] = {nullptr, nullptr};
-  int cur = 0;
+  int cur = 0, swapped = 0;
+  bool recorded = false;
   int64_t steps = 0;
   hipStream_t user = nullptr;  // caller's stream
   hipStream_t own = nullptr;   // internal stream for graph launches
@@ -212,7 +217,7 @@ struct rrmhd_batch {
   int multi_steps = 1, multi_tile = 0, multi_wgs = 0;
   int *d_wg_dom = nullptr;
   int graph_chunk = 0;
-  hipGraphExec_t graph[2] = {nullptr, nullptr};  // by starting buffer
+  hipGraphExec_t graph[2] = {nullptr, nullptr};  // by starting allocation
   int graph_flip[2] = {0, 0};  // whether a replay of it ends in the other buffer
   void *diag_work = nullptr;
   size_t diag_bytes = 0;
@@ -222,6 +227,15 @@ struct rrmhd_batch {
 static void free_graphs(rrmhd_batch *b) {
   for (auto &g : b->graph)
     if (g) (void)hipGraphExecDestroy(g), g = nullptr;
+}
+
+static void rename_buffers(rrmhd_batch *b) {
+  std::swap(b->buf[0], b->buf[1]);
+  b->swapped ^= 1;
+}
+
+static void note_recording(rrmhd_batch *b) {
+  if (!b->recorded) b->recorded = rr_stream_captured(b->user);
 }
 
 static int upload_tiles(rrmhd_batch *b) {
@@ -509,6 +523,7 @@ int rrmhd_batch_create(int n, const rrmhd_grid *grids, const double *tau_f,
 
 int rrmhd_batch_init(rrmhd_batch *b, int d, const double *u, const double *bf) {
   if (!b || d < 0 || d >= b->n || !u || !bf) return RRMHD_EINVAL;
+  note_recording(b);
   rr::Domain D = domain_of(b, d);
   char *dst = (char *)b->buf[b->cur] + b->doms[d].base * b->elem;
   BHIP(rr::launch_init(b->storage, D, u, bf, 0.0, 0.0, dst, b->user));
@@ -540,22 +555,24 @@ int rrmhd_batch_set_fetch(rrmhd_batch *b, int tiles_per_fetch) {
   return RRMHD_OK;
 }
 
-// captured: as for a single grid, an odd number of steps per pass
-static int plain_steps(rrmhd_batch *b, int64_t n, hipStream_t st, bool captured = false) {
+static int plain_steps(rrmhd_batch *b, int64_t n, hipStream_t st) {
   while (n > 0) {
     int64_t T = b->multi && b->multi_steps > 1 ? std::min<int64_t>(n, b->multi_steps) : 1;
     if (T > 1 && b->multi_tile) {  // the steps to go in even passes
       const int64_t passes = (n + T - 1) / T;
       T = (n + passes - 1) / passes;
     }
-    if (captured && T % 2 == 0) T -= 1;
+    if (b->recorded && T % 2 == 0) T -= 1;
     // short remainders in tiles larger than 16 nodes: as for a single grid
     if (T < 4 && b->multi_tile > 16) T = 1;
     if (T > 1)
       BHIP(launch_multi(b, (int)T, st));
     else
       BHIP(launch_one(b, st));
-    b->cur ^= 1;
+    if (T & 1)
+      b->cur ^= 1;
+    else
+      rename_buffers(b);
     b->steps += T;
     n -= T;
   }
@@ -566,22 +583,25 @@ int rrmhd_batch_step(rrmhd_batch *b, int64_t n) {
   if (!b || n < 0) return RRMHD_EINVAL;
   for (int d = 0; d < b->n; ++d)
     if (b->init_step[d] < 0) return RRMHD_ESTATE;
+  note_recording(b);
   const int64_t chunk = b->graph_chunk;
-  if (chunk <= 0 || n < chunk) return plain_steps(b, n, b->user, rr_stream_captured(b->user));
+  if (chunk <= 0 || n < chunk) return plain_steps(b, n, b->user);
   // graph path: order the internal stream after the caller's work
   BHIP(hipEventRecord(b->ev_in, b->user));
   BHIP(hipStreamWaitEvent(b->own, b->ev_in, 0));
   int64_t left = n;
   while (left >= chunk) {
-    hipGraphExec_t &g = b->graph[b->cur];
+    const int state = b->cur ^ b->swapped;
+    hipGraphExec_t &g = b->graph[state];
     if (!g) {
       hipGraph_t graph = nullptr;
-      const int c0 = b->cur;
+      const int c0 = b->cur, w0 = b->swapped;
       const int64_t s0 = b->steps;
       BHIP(hipStreamBeginCapture(b->own, hipStreamCaptureModeThreadLocal));
       int rc = plain_steps(b, chunk, b->own);
       hipError_t ee = hipStreamEndCapture(b->own, &graph);
-      b->graph_flip[c0] = b->cur ^ c0;
+      b->graph_flip[state] = (b->cur ^ b->swapped) ^ state;
+      if (b->swapped != w0) rename_buffers(b);
       b->cur = c0;  // capture recorded the launches; nothing ran yet
       b->steps = s0;
       if (rc != RRMHD_OK) return rc;
@@ -590,8 +610,11 @@ int rrmhd_batch_step(rrmhd_batch *b, int64_t n) {
       (void)hipGraphDestroy(graph);
       if (ei != hipSuccess) return bdev_err(ei, "hipGraphInstantiate");
     }
+    // built before the caller recorded its own, it may rename the buffers
+    if (b->recorded && b->graph_flip[state] != (chunk & 1)) break;
     BHIP(hipGraphLaunch(g, b->own));
-    b->cur ^= b->graph_flip[b->cur];
+    b->cur ^= (int)(chunk & 1);
+    if ((b->cur ^ b->swapped) != (state ^ b->graph_flip[state])) rename_buffers(b);
     b->steps += chunk;
     left -= chunk;
   }
@@ -612,6 +635,7 @@ int rrmhd_batch_set_graph_chunk(rrmhd_batch *b, int chunk) {
 int rrmhd_batch_moments(rrmhd_batch *b, int d, double *rho, double *u, double *bf) {
   if (!b || d < 0 || d >= b->n) return RRMHD_EINVAL;
   if (b->init_step[d] < 0) return RRMHD_ESTATE;
+  note_recording(b);
   rr::Domain D = domain_of(b, d);
   const char *src = (const char *)b->buf[b->cur] + b->doms[d].base * b->elem;
   BHIP(rr::launch_moments(b->storage, D, src, rho, u, bf, b->user));
