@@ -524,8 +524,10 @@ const char *rrmhd_train_last_error_detail(void);
  * the fastest.  The handle's state and step count are preserved (a handle
  * that was never initialised is timed on the rest state and stays
  * uninitialised).  cache_path (may be NULL) names a JSON file of earlier
- * results keyed by device architecture, grid size and storage; a cached
- * entry is installed without timing, and new results are added to it.
+ * results keyed by device architecture, grid size, storage and whatever else
+ * decides the form of a step (walls, force, rounding, equilibrium, closure,
+ * layout, buffers); a cached entry is installed without timing, and new
+ * results are added to it.  Entries from before passes were timed are not used.
  * Outputs (may be NULL): the chosen bx, by, xcd and its time per step. */
 int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
                    int *out_by, int *out_xcd, double *out_ms);

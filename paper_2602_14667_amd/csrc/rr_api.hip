@@ -892,6 +892,11 @@ void rr_handle_default_launch(rrmhd *h) {
   default_launch(h);
 }
 
+int rr_handle_variant(const rrmhd *h) {
+  return (h->D.walls ? 1 : 0) | (h->D.Gx != 0.0f || h->D.Gy != 0.0f ? 2 : 0) |
+         (h->D.sr ? 4 : 0) | (h->D.feq ? 8 : 0) | (h->closure_on ? 16 : 0);
+}
+
 int rr_handle_rows(const rrmhd *h) { return h && h->D.row != h->D.nx ? 1 : 0; }
 
 void rr_handle_set_ready(rrmhd *h, int ready) {

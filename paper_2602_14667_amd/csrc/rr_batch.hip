@@ -718,6 +718,11 @@ void rr_batch_set_multi(rrmhd_batch *b) {
   b->multi = true;
 }
 
+void rr_batch_pass(const rrmhd_batch *b, int *steps, int *tile) {
+  *steps = b->multi_steps;
+  *tile = b->multi_tile;
+}
+
 hipStream_t rr_batch_stream(const rrmhd_batch *b) { return b ? b->user : nullptr; }
 
 }  // extern "C"

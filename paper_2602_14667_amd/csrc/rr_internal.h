@@ -20,6 +20,9 @@ RR_HIDDEN int rr_handle_walls(const rrmhd *h);
 RR_HIDDEN int rr_handle_inplace(const rrmhd *h);
 // the default launch shape again, with several steps per launch
 RR_HIDDEN void rr_handle_default_launch(rrmhd *h);
+// what besides size, storage and layout decides the form of a step: bit 0
+// walls, 1 force, 2 stochastic rounding, 3 equilibrium ablation, 4 closure
+RR_HIDDEN int rr_handle_variant(const rrmhd *h);
 // 1 when the handle keeps its planes row-interleaved
 RR_HIDDEN int rr_handle_rows(const rrmhd *h);
 }
@@ -62,6 +65,8 @@ RR_HIDDEN int rr_batch_restore(rrmhd_batch *b, void *copy, int64_t steps);
 // batch: several steps per pass again (rrmhd_batch_set_shape and _set_fetch
 // choose the one-step kernel)
 RR_HIDDEN void rr_batch_set_multi(rrmhd_batch *b);
+// batch: the form of its passes (steps 1: none; tile 0: marching)
+RR_HIDDEN void rr_batch_pass(const rrmhd_batch *b, int *steps, int *tile);
 RR_HIDDEN hipStream_t rr_batch_stream(const rrmhd_batch *b);
 }
 

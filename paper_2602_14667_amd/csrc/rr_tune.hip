@@ -1,6 +1,7 @@
 // rr_tune.hip -- autotuner for the step kernels: times candidate launch
 // shapes on the real grid with HIP events and keeps the fastest, with an
-// optional JSON cache keyed by (device arch, nx, ny, storage).
+// optional JSON cache keyed by (device arch, what decides the form of a step,
+// nx, ny, storage).
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -125,6 +126,19 @@ std::string key_of(const char *kind, int nx, int ny, int storage) {
   return b;
 }
 
+// Key of a single grid's entry: what decides the form of a step, layout and
+// buffers, size, storage.  "passes": an entry that also says whether several
+// steps per pass win; one of an earlier key does not, and is left unused.
+std::string step_key(const rrmhd *h, int nx, int ny, int storage) {
+  static const char *const kNames[] = {"+walls", "+force", "+sr", "+feq", "+closure"};
+  std::string kind = "passes";
+  const int v = rr_handle_variant(h);
+  for (int k = 0; k < 5; ++k)
+    if (v >> k & 1) kind += kNames[k];
+  kind += rr_handle_inplace(h) ? "/step_inplace" : (rr_handle_rows(h) ? "/step_rows" : "/step");
+  return key_of(kind.c_str(), nx, ny, storage);
+}
+
 // Time `trials` steps of fn after 2 warm-up steps; best of 3 repetitions.
 template <class F>
 int time_steps(F &&fn, hipStream_t st, int trials, double *ms_out) {
@@ -165,10 +179,8 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
   if (rc != RRMHD_OK) return rc;
   cache_path = cache_file(cache_path);
   auto cache = read_cache(cache_path);
-  const bool inplace = rr_handle_inplace(h) != 0;
   const bool rows = rr_handle_rows(h) != 0;  // row-interleaved planes
-  const std::string key =
-      key_of(inplace ? "step_inplace" : (rows ? "step_rows" : "step"), nx, ny, storage);
+  const std::string key = step_key(h, nx, ny, storage);
   Entry best;
   auto it = cache.find(key);
   if (it != cache.end()) {
@@ -419,7 +431,11 @@ int rrmhd_batch_autotune(rrmhd_batch *b, const char *cache_path, int trials) {
   }
   // 4) the tuned one-step kernel against the default launch, several steps per
   // pass where the ensemble has a form for it (state preserved)
-  const std::string mkey = key_of(kb, 2, 0, storage);
+  int T = 1, tile = 0;
+  rr_batch_pass(b, &T, &tile);
+  char km[96];
+  std::snprintf(km, sizeof km, "%s_passes%d_tile%d", kb, T, tile);
+  const std::string mkey = key_of(km, 0, 0, storage);
   auto mit = cache.find(mkey);
   int multi = 0;
   if (mit != cache.end()) {
