@@ -410,19 +410,24 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b) {
   return RRMHD_OK;
 }
 
-static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
+// The next pass with n steps to go (steps <= 1: one step).  owed: on one buffer
+// an odd number of steps has been taken in passes, which leave the phase alone.
+static rr::MultiPlan next_pass(const rrmhd *h, int64_t n, bool owed) {
+  rr::MultiPlan M{};
+  if (!h->multi || h->closure_on || h->phase) return M;
   // a small single-buffer handle (kSmallState) takes the passes of a
   // two-buffer one from its usual layout; its graphs keep to the phases
-  const bool multi = h->multi && !h->closure_on &&
-                     (!h->inplace || (h->buf[1] && h->graph_chunk <= 0 && !h->recorded));
-  // one buffer: an odd number of steps has been taken in passes, which leave
-  // the phase alone
+  if (h->inplace && (!h->buf[1] || h->graph_chunk > 0 || h->recorded)) return M;
+  // one buffer: an odd total leaves its last step to the phases
+  M = rr::multi_plan(h->D, h->inplace ? n - ((n + owed) & 1) : n);
+  if (h->recorded && M.steps > 0 && M.steps % 2 == 0) M.steps -= 1;
+  return M;
+}
+
+static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
   bool owed = false;
   while (n > 0) {
-    rr::MultiPlan M{};
-    // one buffer: an odd total leaves its last step to the phases
-    if (multi && !h->phase) M = rr::multi_plan(h->D, h->inplace ? n - ((n + owed) & 1) : n);
-    if (h->recorded && M.steps > 0 && M.steps % 2 == 0) M.steps -= 1;
+    const rr::MultiPlan M = next_pass(h, n, owed);
     int64_t taken = 1;
     // random bits of the stochastic-rounding codec: keyed by the step count
     h->D.sr_step = (uint32_t)h->steps;
@@ -890,6 +895,11 @@ int rr_handle_inplace(const rrmhd *h) { return h && h->inplace ? 1 : 0; }
 void rr_handle_default_launch(rrmhd *h) {
   free_graphs(h);
   default_launch(h);
+}
+
+int rr_handle_pass_steps(const rrmhd *h, int64_t n) {
+  const int T = next_pass(h, n, false).steps;
+  return T > 1 ? T : 1;
 }
 
 int rr_handle_variant(const rrmhd *h) {

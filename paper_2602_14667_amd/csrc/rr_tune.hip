@@ -139,6 +139,10 @@ std::string step_key(const rrmhd *h, int nx, int ny, int storage) {
   return key_of(kind.c_str(), nx, ny, storage);
 }
 
+// `trials` steps rounded up to an even number of passes of T steps (even: a
+// single buffer's phase is then the one it started from).
+int whole_passes(int trials, int T) { return (trials + 2 * T - 1) / (2 * T) * 2 * T; }
+
 // Time `trials` steps of fn after 2 warm-up steps; best of 3 repetitions.
 template <class F>
 int time_steps(F &&fn, hipStream_t st, int trials, double *ms_out) {
@@ -219,8 +223,10 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
     if (rc == RRMHD_OK) {
       rr_handle_default_launch(h);
       rc = rrmhd_get_launch(h, &best.bx, &best.by, nullptr, &best.xcd, &best.nt);
+      const int T = rr_handle_pass_steps(h, 1 << 20);
       if (rc == RRMHD_OK)
-        rc = time_steps([&](int n) { return rrmhd_step(h, n); }, st, trials, &best.ms);
+        rc = time_steps([&](int n) { return rrmhd_step(h, n); }, st,
+                        T > 1 ? whole_passes(trials, T) : trials, &best.ms);
       best.multi = 1;
     }
     for (const Shape &c : cands) {
@@ -437,8 +443,10 @@ int rrmhd_batch_autotune(rrmhd_batch *b, const char *cache_path, int trials) {
   std::snprintf(km, sizeof km, "%s_passes%d_tile%d", kb, T, tile);
   const std::string mkey = key_of(km, 0, 0, storage);
   auto mit = cache.find(mkey);
-  int multi = 0;
-  if (mit != cache.end()) {
+  int multi = 1;
+  if (T == 1) {
+    // no form: nothing to choose
+  } else if (mit != cache.end()) {
     multi = mit->second.multi;
   } else {
     void *save = nullptr;
@@ -448,7 +456,8 @@ int rrmhd_batch_autotune(rrmhd_batch *b, const char *cache_path, int trials) {
     double one = 0.0, many = 0.0;
     rc = time_steps(step, rr_batch_stream(b), trials, &one);
     rr_batch_set_multi(b);
-    if (rc == RRMHD_OK) rc = time_steps(step, rr_batch_stream(b), trials, &many);
+    if (rc == RRMHD_OK)
+      rc = time_steps(step, rr_batch_stream(b), whole_passes(trials, T), &many);
     multi = many < one;
     int rc2 = rr_batch_restore(b, save, steps0);
     if (rc == RRMHD_OK) rc = rc2;

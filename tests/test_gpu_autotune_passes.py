@@ -1,5 +1,5 @@
 """What the autotuner keeps about several steps per pass: only entries of a handle
-that steps alike are shared."""
+that steps alike are shared, and passes are timed whole."""
 import json
 
 import pytest
@@ -47,3 +47,30 @@ def test_earlier_entry_does_not_turn_passes_off(tmp_path):
     new = entries(cache)
     assert any(e.get("multi") == 1 and e["ms"] > 0 for k, e in new.items() if k != old), new
     s.close()
+
+
+@pytest.mark.parametrize("trials", [1, 3])
+@pytest.mark.parametrize("kw", [{}, {"inplace": True}])
+def test_few_trials_time_whole_passes(tmp_path, kw, trials):
+    """64^2: passes of seven steps against single steps, 1.2 us to 3.1."""
+    cache = tmp_path / "tune.json"
+    s = solver(64, 64, **kw)
+    s.autotune(str(cache), trials=trials)
+    e, = entries(cache).values()
+    assert e["multi"] == 1
+    s.close()
+
+
+def test_ensemble_with_few_trials(tmp_path):
+    """A 32-node tile form (four steps and more per pass) with three trials."""
+    from paper_2602_14667_amd import rrmhd
+    print("[gpu] autotune ensemble", flush=True)
+    cache = tmp_path / "tune.json"
+    shapes = [(96, 96)] * 12
+    b = rrmhd.Batch(shapes, [0.56] * 12, [0.6] * 12)
+    f = torch.zeros(2, 96, 96, dtype=torch.float64, device="cuda")
+    for d in range(12):
+        b.init(d, f, f)
+    b.autotune(str(cache), trials=3)
+    assert [e["multi"] for k, e in entries(cache).items() if "passes" in k] == [1], entries(cache)
+    b.close()
