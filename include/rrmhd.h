@@ -520,8 +520,9 @@ const char *rrmhd_train_last_error_detail(void);
 
 /* ---- Autotuner -----------------------------------------------------------
  * Times candidate launch shapes of the step kernel on the handle's own grid
- * (trials steps each, best of three repetitions, HIP events) and installs
- * the fastest.  The handle's state and step count are preserved (a handle
+ * (trials steps each, best of three repetitions, HIP events), then several
+ * steps per pass where the grid has a form for it (at least trials steps, in
+ * whole passes), and installs the fastest shape, with passes if they win.  The handle's state and step count are preserved (a handle
  * that was never initialised is timed on the rest state and stays
  * uninitialised).  cache_path (may be NULL) names a JSON file of earlier
  * results keyed by device architecture, grid size, storage and whatever else
@@ -534,7 +535,8 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
 /* Ensemble version: a tile width for every distinct domain size (timed on a
  * standalone grid of that size) and then the work distribution (workgroup
  * count and static or dynamic schedule, timed on the ensemble, state
- * preserved), and that against the default launch; same cache file. */
+ * preserved), and that against several steps per pass where the ensemble has
+ * a form for it; same cache file. */
 int rrmhd_batch_autotune(rrmhd_batch *b, const char *cache_path, int trials);
 
 /* Measurement helper, not part of the method: copies `bytes` (a multiple of

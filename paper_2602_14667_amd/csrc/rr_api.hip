@@ -897,6 +897,11 @@ void rr_handle_default_launch(rrmhd *h) {
   default_launch(h);
 }
 
+void rr_handle_set_multi(rrmhd *h) {
+  free_graphs(h);
+  h->multi = true;
+}
+
 int rr_handle_pass_steps(const rrmhd *h, int64_t n) {
   const int T = next_pass(h, n, false).steps;
   return T > 1 ? T : 1;

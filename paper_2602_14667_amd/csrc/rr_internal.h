@@ -20,6 +20,8 @@ RR_HIDDEN int rr_handle_walls(const rrmhd *h);
 RR_HIDDEN int rr_handle_inplace(const rrmhd *h);
 // the default launch shape again, with several steps per launch
 RR_HIDDEN void rr_handle_default_launch(rrmhd *h);
+// several steps per launch again, beside the one-step shape that is set
+RR_HIDDEN void rr_handle_set_multi(rrmhd *h);
 // steps of the first pass of n (1: one step per launch)
 RR_HIDDEN int rr_handle_pass_steps(const rrmhd *h, int64_t n);
 // what besides size, storage and layout decides the form of a step: bit 0

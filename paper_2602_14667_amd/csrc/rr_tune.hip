@@ -25,7 +25,7 @@ constexpr double kMargin = 0.98;
 
 struct Entry {
   int bx = 0, by = 0, xcd = 0, grid = 0, fetch = 0, nt = 1;
-  int multi = 0;  // the default launch: several steps per pass where a form applies
+  int multi = 0;  // several steps per pass where a form applies
   double ms = 0.0;
 };
 
@@ -209,7 +209,11 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
     // nodes per thread (FP16 storage; FP32 storage on row-interleaved planes)
     // nt = 9: non-temporal stores and four nodes per thread (FP16 storage,
     // nx a multiple of 4)
-    const Shape cands[] = {{256, 1, 0, 1}, {128, 2, 0, 1}, {64, 4, 0, 1}, {128, 1, 0, 1},
+    // the default shape first, whatever was set before
+    rr_handle_default_launch(h);
+    Shape def{};
+    if (rc == RRMHD_OK) rc = rrmhd_get_launch(h, &def.bx, &def.by, nullptr, &def.xcd, &def.nt);
+    const Shape cands[] = {def,             {256, 1, 0, 1}, {128, 2, 0, 1}, {64, 4, 0, 1}, {128, 1, 0, 1},
                            {64, 1, 0, 1},  {32, 8, 0, 1},  {256, 1, 2, 1}, {128, 2, 2, 1},
                            {64, 4, 2, 1},  {128, 1, 0, 5}, {128, 2, 0, 5}, {64, 4, 0, 5},
                            {256, 1, 0, 5}, {64, 2, 0, 5},  {128, 2, 2, 5}, {64, 4, 2, 5},
@@ -218,17 +222,6 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
         (storage == RRMHD_STORE_F16 || rows) && nx % 2 == 0 && !rr_handle_walls(h);
     const bool quad_ok = storage == RRMHD_STORE_F16 && nx % 4 == 0 && !rr_handle_walls(h);
     best.ms = 1e30;
-    // the default launch first, with several steps per pass; the candidates
-    // below are shapes of the one-step kernels
-    if (rc == RRMHD_OK) {
-      rr_handle_default_launch(h);
-      rc = rrmhd_get_launch(h, &best.bx, &best.by, nullptr, &best.xcd, &best.nt);
-      const int T = rr_handle_pass_steps(h, 1 << 20);
-      if (rc == RRMHD_OK)
-        rc = time_steps([&](int n) { return rrmhd_step(h, n); }, st,
-                        T > 1 ? whole_passes(trials, T) : trials, &best.ms);
-      best.multi = 1;
-    }
     for (const Shape &c : cands) {
       if (rc != RRMHD_OK) break;
       if ((c.nt & 4) && !pair_ok) continue;
@@ -244,9 +237,21 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
         best.by = c.by;
         best.xcd = c.xcd;
         best.nt = c.nt;
-        best.multi = 0;
         best.ms = ms;
       }
+    }
+    // several steps per pass against the best shape of the one-step kernels,
+    // which takes the steps that no pass does either way.  Where no form
+    // applies to the handle as it is now, passes stay allowed.
+    if (rc == RRMHD_OK) rc = rrmhd_load_state(h, save, nb, steps0);
+    if (rc == RRMHD_OK) {
+      rr_handle_set_multi(h);
+      const int T = rr_handle_pass_steps(h, 1 << 20);
+      double ms = 0.0;
+      if (T > 1)
+        rc = time_steps([&](int n) { return rrmhd_step(h, n); }, st, whole_passes(trials, T), &ms);
+      best.multi = T == 1 || ms < best.ms;
+      if (T > 1 && best.multi) best.ms = ms;
     }
     int rc2 = rrmhd_load_state(h, save, nb, steps0);
     if (hipStreamSynchronize(st) != hipSuccess && rc2 == RRMHD_OK) rc2 = RRMHD_EDEVICE;
@@ -257,10 +262,8 @@ int rrmhd_autotune(rrmhd *h, const char *cache_path, int trials, int *out_bx,
     cache[key] = best;
     write_cache(cache_path, cache);
   }
-  if (best.multi)
-    rr_handle_default_launch(h);
-  else
-    rc = rrmhd_set_launch(h, best.bx, best.by, 1, best.xcd, best.nt > 0 ? best.nt : 1);
+  rc = rrmhd_set_launch(h, best.bx, best.by, 1, best.xcd, best.nt > 0 ? best.nt : 1);
+  if (rc == RRMHD_OK && best.multi) rr_handle_set_multi(h);
   if (out_bx) *out_bx = best.bx;
   if (out_by) *out_by = best.by;
   if (out_xcd) *out_xcd = best.xcd;
@@ -435,8 +438,8 @@ int rrmhd_batch_autotune(rrmhd_batch *b, const char *cache_path, int trials) {
                                0, -1);
     if (rc != RRMHD_OK) return rc;
   }
-  // 4) the tuned one-step kernel against the default launch, several steps per
-  // pass where the ensemble has a form for it (state preserved)
+  // 4) the tuned one-step kernel against several steps per pass, whole passes
+  // of the form that the ensemble has, if any (state preserved)
   int T = 1, tile = 0;
   rr_batch_pass(b, &T, &tile);
   char km[96];

@@ -1,5 +1,6 @@
 """What the autotuner keeps about several steps per pass: only entries of a handle
-that steps alike are shared, and passes are timed whole."""
+that steps alike are shared, passes are timed whole, and the tuned shape stays in
+force for the steps that no pass takes."""
 import json
 
 import pytest
@@ -59,6 +60,31 @@ def test_few_trials_time_whole_passes(tmp_path, kw, trials):
     e, = entries(cache).values()
     assert e["multi"] == 1
     s.close()
+
+
+def test_tuned_shape_and_passes_together(tmp_path):
+    cache = tmp_path / "tune.json"
+    a = solver(96, 80)
+    a.autotune(str(cache), trials=2)
+    got = entries(cache)
+    e, = got.values()
+    e.update(bx=16, by=8, xcd=0, nt=1, multi=1)
+    cache.write_text(json.dumps(got))
+    g = torch.Generator(device="cuda").manual_seed(1)
+    u, b = (0.03 * torch.randn(2, 80, 96, dtype=torch.float64, device="cuda", generator=g)
+            for _ in range(2))
+    ref = solver(96, 80)
+    for s in (a, ref):
+        s.init(u, b)
+    best = a.autotune(str(cache), trials=2)
+    assert (best["bx"], best["by"]) == (16, 8) and a.get_launch()[:2] == (16, 8)
+    for n in (1, 9, 12):
+        a.step(n)
+        ref.step(n)
+        for x, y in zip(a.moments(), ref.moments()):
+            assert torch.equal(x, y), n
+    a.close()
+    ref.close()
 
 
 def test_ensemble_with_few_trials(tmp_path):
