@@ -57,7 +57,9 @@ enum {
  * RRMHD_STORE_INPLACE may be OR-ed into rrmhd_grid.storage: the handle then
  * holds one population buffer instead of two (half the device memory; a
  * handle of up to 64 MiB of state keeps a second one all the same and steps
- * as a two-buffer handle does, which for such grids is the faster).  Its
+ * as a two-buffer handle does, which for such grids is the faster, while the
+ * second buffers of all such handles of the process together stay within
+ * 1 GiB).  Its
  * steps alternate between two forms that each write only the locations they
  * have just read: a pull of the upstream populations whose results go into
  * the slots just read for the opposite directions, then a read of the node's

@@ -2,6 +2,7 @@
 // handle, A/B population buffers, stream ordering, error mapping.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cerrno>
 #include <cmath>
 #include <cstdio>
@@ -81,10 +82,20 @@ int scratch_address(int *dev_out, void **out) {
 }  // namespace
 
 // Up to this state size a single-buffer handle keeps a second buffer all the
-// same, for passes of several steps: the memory saved would be negligible, and
-// such grids are bound by launches (256^2 FP32 2.26 us per step against 3.70,
-// 900 x 880 12.0 against 20.2).
+// same, for passes of several steps: such grids are bound by launches (256^2
+// FP32 2.26 us per step against 3.70, 900 x 880 12.0 against 20.2).  The second
+// buffers of all handles together stay within kSmallTotal, a 288th of the
+// memory, so that a program of many small handles still gets the memory that
+// the mode saves; handles past that keep one buffer.
 constexpr size_t kSmallState = (size_t)64 << 20;
+constexpr int64_t kSmallTotal = (int64_t)1 << 30;
+static std::atomic<int64_t> g_small_bytes{0};
+
+static bool take_small(int64_t bytes) {
+  if (g_small_bytes.fetch_add(bytes) + bytes <= kSmallTotal) return true;
+  g_small_bytes.fetch_sub(bytes);
+  return false;
+}
 
 struct rrmhd {
   rr::Domain D{};
@@ -214,6 +225,7 @@ int rrmhd_destroy(rrmhd *h) {
     hipError_t e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) rc = dev_err(e, "hipStreamSynchronize");
   }
+  if (h->inplace && h->buf[1]) g_small_bytes.fetch_sub((int64_t)h->bytes);
   for (void *&p : h->buf)
     if (p) (void)hipFree(p), p = nullptr;
   if (h->diag_work) (void)hipFree(h->diag_work);
@@ -331,15 +343,15 @@ int rrmhd_create(const rrmhd_grid *grid, double tau_f, double tau_m,
     h->poison = !h->inplace && std::atoi(e) != 0;
   const size_t bytes = h->bytes;
   int rc = RRMHD_OK;
-  for (int k = 0; k < (h->inplace && bytes > kSmallState ? 1 : 2) && rc == RRMHD_OK; ++k) {
+  for (int k = 0; k < (h->inplace ? 1 : 2) && rc == RRMHD_OK; ++k) {
     hipError_t e = hipMalloc(&h->buf[k], bytes);
-    if (e == hipSuccess) continue;
-    if (h->inplace && k == 1) {  // one buffer then
-      h->buf[1] = nullptr;
-      (void)hipGetLastError();
-    } else {
-      rc = dev_err(e, "hipMalloc(populations)");
-    }
+    if (e != hipSuccess) rc = dev_err(e, "hipMalloc(populations)");
+  }
+  if (h->inplace && rc == RRMHD_OK && bytes <= kSmallState && take_small((int64_t)bytes) &&
+      hipMalloc(&h->buf[1], bytes) != hipSuccess) {  // one buffer then
+    h->buf[1] = nullptr;
+    g_small_bytes.fetch_sub((int64_t)bytes);
+    (void)hipGetLastError();
   }
   if (rc == RRMHD_OK) {
     hipError_t e = hipMalloc((void **)&h->diag_out, 8 * sizeof(double));
