@@ -70,7 +70,11 @@ __device__ __forceinline__ float gelu32(float z) {
 __device__ __forceinline__ void gelu_pair(float z, float &h, float &g) {
   float es, s;
   gelu_parts(z, h, es, s);
-  const float w = fmaf(0.21406445f, z * z, 1.5957691f);  // 2 v'(z): 6 sqrt(2/pi) 0.044715, 2 sqrt(2/pi)
+  // 2 v'(z): 6 sqrt(2/pi) 0.044715, 2 sqrt(2/pi).  It only counts while s (1 - s)
+  // does; past |z| = 16, where that is below 2^-450, it stops growing, or z^3
+  // would outrun the smallest s of gelu_parts (2^-126) from |z| = 1e12 on.
+  const float zc = __builtin_amdgcn_fmed3f(z, -16.0f, 16.0f);
+  const float w = fmaf(0.21406445f, zc * zc, 1.5957691f);
   g = fmaf(h * w, es, s);
 }
 
