@@ -14,9 +14,8 @@ horizon) are timed after 100 warm-up steps.
 Prints one JSON line.  MLUPS = nodes x steps / seconds / 1e6.  The roofline
 object prices the algorithmic traffic of a launch (19 reads + 19 writes per
 node: 152 B in FP32 storage, 76 B in FP16) against 8 TB/s.  A launch of the
-default form takes several steps over the state (STEPS_PER_LAUNCH) and reads
-and writes it once; single-buffer handles, the equilibrium ablation and
-stochastic rounding take one.
+default form takes several steps over the state and reads and writes it once:
+the library says how many launches the timed steps take.
 """
 import argparse
 import json
@@ -30,9 +29,6 @@ sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0
 BYTES_PER_NODE = {"f32": 152, "f16": 76, "f16sr": 76}
-# steps per launch of the default form on periodic grids of 1024^2 and more and
-# on the 256-domain ensemble (csrc/rr_multi.hip, csrc/rr_batch.hip)
-STEPS_PER_LAUNCH = 4
 
 
 def kernel_hash():
@@ -266,6 +262,8 @@ def time_batch_leg(torch, rrmhd, inputs, steps, autotune, sequential):
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
     steps = max(chunk, (steps // chunk) * chunk)
+    passes, workgroups = b.step_passes(steps)
+    per = steps / passes
     e0.record(st)
     b.step(steps)
     e1.record(st)
@@ -290,20 +288,20 @@ def time_batch_leg(torch, rrmhd, inputs, steps, autotune, sequential):
             seq_ms += f0.elapsed_time(f1) / 20
             s.close()
     b.close()
-    gbs = 152 * nodes / (STEPS_PER_LAUNCH * ms) / 1e6
+    gbs = 152 * nodes / (per * ms) / 1e6
     return {
         "value": round(nodes / ms / 1e3, 1), "unit": "MLUPS", "steps": steps,
         "warmup": chunk, "ms_per_step": round(ms, 4),
         "config": {"workload": "256 periodic domains, sides 64..1024, "
                                "OT or turbulence, tau in [0.501, 0.6]",
                    "nodes": nodes, "tiles": info["tiles"],
-                   "workgroups_per_launch": info["grid"],
+                   "workgroups_per_launch": workgroups,
                    "graph_chunk": chunk, "autotuned": autotune,
                    "autotune_s": round(tune_s, 2)},
         "roofline": {"bound": "hbm", "achieved": round(gbs, 1),
                      "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": round(gbs / PEAK_HBM_GBS, 4),
-                     "steps_per_launch": STEPS_PER_LAUNCH,
+                     "steps_per_launch": round(per, 3),
                      "traffic": None if autotune else batch_traffic()},
         "sequential_standalone_ms_per_step": None if seq_ms is None else round(seq_ms, 4),
         "speedup_vs_sequential": None if seq_ms is None else round(seq_ms / ms, 3)}
@@ -642,14 +640,9 @@ def time_turbulence_leg(torch, rrmhd, args, fields, storage):
     ud, bd = fields
     s = rrmhd.Solver(n, n, args.tau, args.tau, storage=storage,
                      equilibrium=args.equilibrium, inplace=args.inplace)
-    passes = (storage != "f16sr" and args.equilibrium == "algorithm" and not args.inplace
-              and n >= 1024)
-    per = STEPS_PER_LAUNCH if passes else 1
-    launch = (f"library default (row-interleaved planes; marching passes of {per} steps, "
+    launch = ("library default (row-interleaved planes; marching passes of 4 steps, "
               "wavefronts of 56 stored nodes, four to a workgroup, eight neighbouring workgroups "
               "per XCD)")
-    if n < 1024:
-        launch = "library default (LDS tiles or marching strips, several steps per launch)"
     if storage == "f16sr":
         launch = ("library default (row-interleaved planes, eight neighbouring tiles per XCD, "
                   "NT stores, 128x1 threads, one node per thread)")
@@ -666,6 +659,9 @@ def time_turbulence_leg(torch, rrmhd, args, fields, storage):
                   "forms")
     s.init(ud, bd)
     s.step(args.warmup)
+    per = args.steps / s.step_passes(args.steps)
+    if per > 1 and n < 1024:
+        launch = "library default (LDS tiles or marching strips, several steps per launch)"
     torch.cuda.synchronize()
     st = torch.cuda.current_stream()
     e0 = torch.cuda.Event(enable_timing=True)
@@ -700,7 +696,7 @@ def time_turbulence_leg(torch, rrmhd, args, fields, storage):
             "roofline": {"bound": "hbm", "achieved": round(achieved, 1),
                          "peak": PEAK_HBM_GBS, "unit": "GB/s",
                          "frac": round(achieved / PEAK_HBM_GBS, 4),
-                         "steps_per_launch": per, "traffic": traffic},
+                         "steps_per_launch": round(per, 3), "traffic": traffic},
             "wall_s_timed": round(wall, 4),
             "diagnostics_after": {k: (v if math.isfinite(v) else None) for k, v in
                                   (("E_kin", ek), ("E_mag", em), ("max_div_b", dv))},

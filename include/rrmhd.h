@@ -150,6 +150,9 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b);
  * first recorded call on, passes take an odd number of steps (one step on a
  * single buffer).  Asynchronous. */
 int rrmhd_step(rrmhd *h, int64_t n);
+/* *out = passes over the state that rrmhd_step(h, n) would take now.  Host-side
+ * only. */
+int rrmhd_step_passes(const rrmhd *h, int64_t n, int64_t *out);
 
 /* Pre-collision macroscopic fields of the current state (task 1): rho
  * [ny][nx], u and b [2][ny][nx], FP64 device arrays; any may be NULL.  With a
@@ -374,6 +377,9 @@ int rrmhd_batch_init(rrmhd_batch *b, int d, const double *u, const double *bf);
  * rrmhd_batch_set_shape or _set_fetch a pass is one step of the kernel whose
  * shape and schedule they choose. */
 int rrmhd_batch_step(rrmhd_batch *b, int64_t n);
+/* *out = passes over the ensemble that rrmhd_batch_step(b, n) would take now,
+ * *workgroups (may be NULL) = workgroups of the first.  Host-side only. */
+int rrmhd_batch_step_passes(const rrmhd_batch *b, int64_t n, int64_t *out, int *workgroups);
 /* Steps per captured hipGraph (0: plain launches, the default). */
 int rrmhd_batch_set_graph_chunk(rrmhd_batch *b, int chunk);
 /* Tile width bx (a divisor of 256, tile = bx x 256/bx) for domain d, or for

@@ -422,11 +422,12 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b) {
   return RRMHD_OK;
 }
 
-// The next pass with n steps to go (steps <= 1: one step).  owed: on one buffer
-// an odd number of steps has been taken in passes, which leave the phase alone.
-static rr::MultiPlan next_pass(const rrmhd *h, int64_t n, bool owed) {
+// The next pass with n steps to go from a phase (steps <= 1: one step).  owed: on
+// one buffer an odd number of steps has been taken in passes, which leave the
+// phase alone.
+static rr::MultiPlan next_pass(const rrmhd *h, int64_t n, int phase, bool owed) {
   rr::MultiPlan M{};
-  if (!h->multi || h->closure_on || h->phase) return M;
+  if (!h->multi || h->closure_on || phase) return M;
   // a small single-buffer handle (kSmallState) takes the passes of a
   // two-buffer one from its usual layout; its graphs keep to the phases
   if (h->inplace && (!h->buf[1] || h->graph_chunk > 0 || h->recorded)) return M;
@@ -439,7 +440,7 @@ static rr::MultiPlan next_pass(const rrmhd *h, int64_t n, bool owed) {
 static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
   bool owed = false;
   while (n > 0) {
-    const rr::MultiPlan M = next_pass(h, n, owed);
+    const rr::MultiPlan M = next_pass(h, n, h->phase, owed);
     int64_t taken = 1;
     // random bits of the stochastic-rounding codec: keyed by the step count
     h->D.sr_step = (uint32_t)h->steps;
@@ -521,6 +522,26 @@ int rrmhd_step(rrmhd *h, int64_t n) {
   if (rc != RRMHD_OK) return rc;
   HIP_OR_RETURN(hipEventRecord(h->ev_out, h->own));
   HIP_OR_RETURN(hipStreamWaitEvent(h->stream, h->ev_out, 0));
+  return RRMHD_OK;
+}
+
+int rrmhd_step_passes(const rrmhd *h, int64_t n, int64_t *out) {
+  if (!h || n < 0 || !out) return RRMHD_EINVAL;
+  int64_t passes = 0;
+  int phase = h->phase;
+  auto run = [&](int64_t m) {
+    for (bool owed = false; m > 0; ++passes) {
+      const int T = next_pass(h, m, phase, owed).steps;
+      if (h->inplace && T <= 1 && !owed)
+        phase ^= 1;
+      else
+        owed ^= h->inplace && (T <= 1 || T % 2);
+      m -= T > 1 ? T : 1;
+    }
+  };
+  for (; h->graph_chunk > 0 && n >= h->graph_chunk; n -= h->graph_chunk) run(h->graph_chunk);
+  run(n);
+  *out = passes;
   return RRMHD_OK;
 }
 
@@ -915,7 +936,7 @@ void rr_handle_set_multi(rrmhd *h) {
 }
 
 int rr_handle_pass_steps(const rrmhd *h, int64_t n) {
-  const int T = next_pass(h, n, false).steps;
+  const int T = next_pass(h, n, h->phase, false).steps;
   return T > 1 ? T : 1;
 }
 

@@ -555,18 +555,24 @@ int rrmhd_batch_set_fetch(rrmhd_batch *b, int tiles_per_fetch) {
   return RRMHD_OK;
 }
 
+// Steps of the next pass with n >= 1 to go.
+static int next_pass(const rrmhd_batch *b, int64_t n) {
+  int64_t T = b->multi && b->multi_steps > 1 ? std::min<int64_t>(n, b->multi_steps) : 1;
+  if (T > 1 && b->multi_tile) {  // the steps to go in even passes
+    const int64_t passes = (n + T - 1) / T;
+    T = (n + passes - 1) / passes;
+  }
+  if (b->recorded && T % 2 == 0) T -= 1;
+  // short remainders in tiles larger than 16 nodes: as for a single grid
+  if (T < 4 && b->multi_tile > 16) T = 1;
+  return (int)T;
+}
+
 static int plain_steps(rrmhd_batch *b, int64_t n, hipStream_t st) {
   while (n > 0) {
-    int64_t T = b->multi && b->multi_steps > 1 ? std::min<int64_t>(n, b->multi_steps) : 1;
-    if (T > 1 && b->multi_tile) {  // the steps to go in even passes
-      const int64_t passes = (n + T - 1) / T;
-      T = (n + passes - 1) / passes;
-    }
-    if (b->recorded && T % 2 == 0) T -= 1;
-    // short remainders in tiles larger than 16 nodes: as for a single grid
-    if (T < 4 && b->multi_tile > 16) T = 1;
+    const int T = next_pass(b, n);
     if (T > 1)
-      BHIP(launch_multi(b, (int)T, st));
+      BHIP(launch_multi(b, T, st));
     else
       BHIP(launch_one(b, st));
     if (T & 1)
@@ -622,6 +628,23 @@ int rrmhd_batch_step(rrmhd_batch *b, int64_t n) {
   if (rc != RRMHD_OK) return rc;
   BHIP(hipEventRecord(b->ev_out, b->own));
   BHIP(hipStreamWaitEvent(b->user, b->ev_out, 0));
+  return RRMHD_OK;
+}
+
+int rrmhd_batch_step_passes(const rrmhd_batch *b, int64_t n, int64_t *out, int *workgroups) {
+  if (!b || n < 0 || !out) return RRMHD_EINVAL;
+  if (workgroups)
+    *workgroups = n > 0 && next_pass(b, b->graph_chunk > 0 && n > b->graph_chunk ? b->graph_chunk
+                                                                                 : n) > 1
+                      ? b->multi_wgs
+                      : launch_grid(b);
+  int64_t passes = 0;
+  auto run = [&](int64_t m) {
+    for (; m > 0; ++passes) m -= next_pass(b, m);
+  };
+  for (; b->graph_chunk > 0 && n >= b->graph_chunk; n -= b->graph_chunk) run(b->graph_chunk);
+  run(n);
+  *out = passes;
   return RRMHD_OK;
 }
 

@@ -22,7 +22,7 @@ FEQ_ALGORITHM, FEQ_FULL_MAXWELL = 0, 1
 EXPORTED = [
     "rrmhd_create", "rrmhd_init", "rrmhd_step", "rrmhd_moments",
     "rrmhd_diagnostics", "rrmhd_diagnostics_noalloc", "rrmhd_invariants", "rrmhd_record",
-    "rrmhd_step_count",
+    "rrmhd_step_count", "rrmhd_step_passes", "rrmhd_batch_step_passes",
     "rrmhd_state_bytes", "rrmhd_save_state", "rrmhd_load_state", "rrmhd_save", "rrmhd_load",
     "rrmhd_set_launch", "rrmhd_get_launch", "rrmhd_set_stream", "rrmhd_set_equilibrium", "rrmhd_set_graph_chunk",
     "rrmhd_set_debug_poison",
@@ -93,6 +93,9 @@ def lib():
                                                 ctypes.POINTER(ctypes.c_double)]
         L.rrmhd_invariants.argtypes = [vp, ctypes.POINTER(ctypes.c_double)]
         L.rrmhd_record.argtypes = [vp, ctypes.POINTER(ctypes.c_double)]
+        L.rrmhd_step_passes.argtypes = [vp, i64, ctypes.POINTER(i64)]
+        L.rrmhd_batch_step_passes.argtypes = [vp, i64, ctypes.POINTER(i64),
+                                              ctypes.POINTER(ctypes.c_int)]
         L.rrmhd_step_count.argtypes = [vp, ctypes.POINTER(i64)]
         L.rrmhd_state_bytes.argtypes = [vp]
         L.rrmhd_state_bytes.restype = i64
@@ -406,6 +409,12 @@ class Solver:
         v = ctypes.c_int64()
         _check(lib().rrmhd_step_count(self._h, ctypes.byref(v)),
                "rrmhd_step_count")
+        return v.value
+
+    def step_passes(self, n):
+        """Passes over the state that step(n) would take now."""
+        v = ctypes.c_int64()
+        _check(lib().rrmhd_step_passes(self._h, int(n), ctypes.byref(v)), "rrmhd_step_passes")
         return v.value
 
     def state_bytes(self):
@@ -741,6 +750,14 @@ class Batch:
                                          ctypes.byref(grid)), "rrmhd_batch_info")
         return dict(nodes=nodes.value, steps=steps.value, tiles=nt.value,
                     grid=grid.value)
+
+    def step_passes(self, n):
+        """(passes over the ensemble that step(n) would take now, workgroups of
+        the first)."""
+        v, wg = ctypes.c_int64(), ctypes.c_int()
+        self._chk(lib().rrmhd_batch_step_passes(self._h, int(n), ctypes.byref(v),
+                                                ctypes.byref(wg)), "rrmhd_batch_step_passes")
+        return v.value, wg.value
 
 
 def _ptr_t(t):
