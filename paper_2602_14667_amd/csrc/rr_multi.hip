@@ -149,6 +149,10 @@ MultiPlan multi_plan(const Domain &D, int64_t n) {
     P.tile = B;
     const int64_t passes = (n + T - 1) / T;
     P.steps = (int)((n + passes - 1) / passes);
+    // an even share below what 32 x 32 tiles take would end in single steps:
+    // full passes first then (512 x 500 FP32, run of six: 5 + 1 steps 5.6 us per
+    // step, 3 + 1 + 1 + 1 8.5)
+    if (B == 32 && n / passes < 4) P.steps = (int)(n < T ? n : T);
     return P;
   };
   for (int T = 7; T >= 5; --T)
