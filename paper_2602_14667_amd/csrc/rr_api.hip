@@ -432,7 +432,7 @@ static rr::MultiPlan next_pass(const rrmhd *h, int64_t n, int phase, bool owed) 
   // two-buffer one from its usual layout; its graphs keep to the phases
   if (h->inplace && (!h->buf[1] || h->graph_chunk > 0 || h->recorded)) return M;
   // one buffer: an odd total leaves its last step to the phases
-  M = rr::multi_plan(h->D, h->inplace ? n - ((n + owed) & 1) : n);
+  M = rr::multi_plan(h->D, h->inplace ? n - ((n + owed) & 1) : n, h->inplace);
   if (h->recorded && M.steps > 0 && M.steps % 2 == 0) M.steps -= 1;
   return M;
 }

@@ -47,7 +47,8 @@ struct MultiPlan {
                                 // per row, nodes per window, rows per strip
 };
 constexpr int kMultiSteps = 5;
-MultiPlan multi_plan(const Domain &D, int64_t n);  // for n >= 2 remaining steps
+// for n >= 2 remaining steps; one_buffer: single steps go in place
+MultiPlan multi_plan(const Domain &D, int64_t n, bool one_buffer);
 hipError_t launch_multi(const MultiPlan &M, int storage, const Domain &D, const void *src,
                         void *dst, hipStream_t st);
 

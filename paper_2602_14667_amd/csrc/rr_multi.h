@@ -281,9 +281,9 @@ inline double march_us(double w, int rows) {
 // The same for a pass of T steps in 32 x 32 tiles, one workgroup per CU at a
 // time (131 KB of LDS), q tiles per CU.
 inline double tile32_us(int T, double q) { return T == 5 ? 1.5 + 13.0 * q : 2.0 + 11.5 * q; }
-// One step of the one-step kernels, `bytes` of state: a launch, or the state
-// read and written through HBM.
-inline double single_us(double bytes) { return 3.0 + 2.0 * bytes / 5.4e6; }
+// One step of the one-step kernels, `bytes` of state: a launch, and the state
+// read and written at `rate` bytes per us (through HBM).
+inline double single_us(double bytes, double rate = 5.4e6) { return 3.0 + 2.0 * bytes / rate; }
 
 // Windows of equal width covering a row of nx nodes, in multiples of 8.
 struct MarchWindows {

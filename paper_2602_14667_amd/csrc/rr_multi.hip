@@ -102,6 +102,22 @@ static void multi_t(const MultiPlan &M, const Domain &D, const void *src, void *
     tile_b<C, 32>(M, D, src, dst, st);
 }
 
+// The estimate of single_us for this grid.  The rate (bytes per us) of a state
+// that the caches hold is higher where a step is whole waves of one row, 64
+// nodes (64 x 3000 and 64 x 5000: FP32 5.8 and 6.9 to 10.2 us per step, FP16 4.7
+// and 6.2, walls as periodic), and in one buffer, half the footprint (512 x 500
+// FP32 6.5 us against 9.8 in two, 64 x 5000 6.9 / 10.2, 127 x 4000 FP16 7.8 / 9.9).
+// At the common rate passes were taken that lose to it: 64 x 5000 FP16 walls 7.0
+// against 6.2, one buffer FP32 8.0 / 6.9, 127 x 4000 FP16 in one buffer 9.6 / 7.8.
+static double single_us(const Domain &D, bool one_buffer) {
+  const double bytes = (double)D.nx * D.ny * D.elem * kStatePlanes;
+  const bool f32 = D.elem == 4;
+  double rate = 5.4e6;
+  if (one_buffer) rate = f32 ? 9.0e6 : 6.0e6;
+  if (D.nx == 64 && bytes < 128e6) rate = one_buffer && f32 ? 12.0e6 : 8.0e6;
+  return single_us(bytes, rate);
+}
+
 // Tiles per CU of a pass of T steps in B x B tiles.
 static int64_t tiles_per_cu(const Domain &D, int B, int T) {
   const int64_t out = B - 2 * (T - 1);
@@ -140,7 +156,7 @@ static int64_t tiles_per_cu(const Domain &D, int B, int T) {
 // 700 x 500 8.2 / 8.5, 1000 x 600 12.4 / 11.4, 2048^2 70 / 59), forced beyond two
 // (700 x 500 9.8 / 9.9, 2048^2 86 / 76).  From nine tiles per CU on five steps
 // beat four (1500 x 1000 28.0 / 29.0, 2048^2 73 / 82).
-MultiPlan multi_plan(const Domain &D, int64_t n) {
+MultiPlan multi_plan(const Domain &D, int64_t n, bool one_buffer) {
   MultiPlan M{};
   if (n < 2 || D.feq || D.nx > (1 << 30) || D.ny > (1 << 30)) return M;
   const bool forced = D.Gx != 0.0f || D.Gy != 0.0f;
@@ -168,7 +184,7 @@ MultiPlan multi_plan(const Domain &D, int64_t n) {
     T = 4;
     q = q4;
   }
-  const double single = single_us((double)D.nx * D.ny * D.elem * kStatePlanes);
+  const double single = single_us(D, one_buffer);
   const bool tiles = n >= 4 && (q == 1 || tile32_us(T, q) / T < 1.1 * single);
   if (D.walls || forced)
     return tiles && (D.elem == 4 || q <= (forced ? 2 : 3)) ? tile(32, T) : M;

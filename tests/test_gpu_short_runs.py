@@ -1,10 +1,19 @@
-"""Runs whose length is no whole number of passes: how many passes they take, and that
-the bits stay those of single steps."""
+"""Runs whose length is no whole number of passes, and grids where single steps are
+the faster: how many passes they take, and that the bits stay those of single steps."""
 import pytest
 
 from test_gpu_multi import check, pair
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape,storage,kw", [
+    ((64, 5000), "f16", {"walls": True}), ((64, 5000), "f16", {}), ((64, 3000), "f16", {}),
+    ((64, 5000), "f32", {"inplace": True}), ((127, 4000), "f16", {"inplace": True})])
+def test_single_steps_where_they_are_faster(shape, storage, kw):
+    got, ref = pair(*shape, storage, **kw)
+    assert got.step_passes(40) == 40
+    check(got, ref, [3])
 
 
 @pytest.mark.parametrize("shape,storage,kw,passes", [
