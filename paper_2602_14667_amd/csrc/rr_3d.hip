@@ -378,7 +378,7 @@ __host__ __device__ constexpr int opp_plane(int P) {
   return kQ + 3 * oj + a;
 }
 
-template <class C, int P>
+template <class C, bool NT, int P>
 __device__ __forceinline__ void st_push(typename C::T *buf, const Dom3 &D, const Src3 &S,
                                         const float *v) {
   int a, b, c;
@@ -394,12 +394,12 @@ __device__ __forceinline__ void st_push(typename C::T *buf, const Dom3 &D, const
   }
   // the source entry of -c is the node x + c
   const uint32_t off = S.slab[1 - c] + S.row[1 - b] + S.col[1 - a];
-  rr::st_at<typename C::T, false>(buf + (int64_t)opp_plane(P) * D.plane, off, C::enc(v[P], 1.0f));
+  rr::st_at<typename C::T, NT>(buf + (int64_t)opp_plane(P) * D.plane, off, C::enc(v[P], 1.0f));
 }
-template <class C, int... P>
+template <class C, bool NT, int... P>
 __device__ __forceinline__ void push_all(typename C::T *buf, const Dom3 &D, const Src3 &S,
                                          const float *v, std::integer_sequence<int, P...>) {
-  (st_push<C, P>(buf, D, S, v), ...);
+  (st_push<C, NT, P>(buf, D, S, v), ...);
 }
 
 template <class C, int... P>
@@ -410,7 +410,7 @@ __device__ __forceinline__ void load_own(const typename C::T *buf, const Dom3 &D
    ...);
 }
 
-template <class C, int PHASE, bool LIN>
+template <class C, int PHASE, bool LIN, bool NT>
 __global__ __launch_bounds__(256) void k_step3_inplace(Dom3 D, int tiles_x, int xcd,
                                                        typename C::T *buf) {
   const Node3 P = node3<LIN>(D, tiles_x, xcd);
@@ -427,9 +427,9 @@ __global__ __launch_bounds__(256) void k_step3_inplace(Dom3 D, int tiles_x, int 
   float(&g)[3 * kQm] = *reinterpret_cast<float(*)[3 * kQm]>(v + kQ);
   collide3(d, g, D.om_c, D.omm_c);
   if constexpr (PHASE == 0)
-    push_all<C>(buf, D, S, v, std::make_integer_sequence<int, kPlanes>{});
+    push_all<C, NT>(buf, D, S, v, std::make_integer_sequence<int, kPlanes>{});
   else
-    store_all<C, false>(buf, D, own, v, std::make_integer_sequence<int, kPlanes>{});
+    store_all<C, NT>(buf, D, own, v, std::make_integer_sequence<int, kPlanes>{});
 }
 
 // Debug fill of a population buffer with a NaN pattern (32-bit words).
@@ -757,12 +757,14 @@ static void launch_step3(rrmhd3d *h, dim3 grid, dim3 block, int tiles_x, const v
   else if (!h->inplace)
     hipLaunchKernelGGL((rr3::k_step3<C, LIN, false>), grid, block, 0, h->stream, h->D, tiles_x,
                        h->xcd, (const T *)src, (T *)dst);
-  else if (h->phase == 0)
-    hipLaunchKernelGGL((rr3::k_step3_inplace<C, 0, LIN>), grid, block, 0, h->stream, h->D,
-                       tiles_x, h->xcd, (T *)h->buf[0]);
+  else if (h->nt)
+    hipLaunchKernelGGL((h->phase == 0 ? rr3::k_step3_inplace<C, 0, LIN, true>
+                                      : rr3::k_step3_inplace<C, 1, LIN, true>),
+                       grid, block, 0, h->stream, h->D, tiles_x, h->xcd, (T *)h->buf[0]);
   else
-    hipLaunchKernelGGL((rr3::k_step3_inplace<C, 1, LIN>), grid, block, 0, h->stream, h->D,
-                       tiles_x, h->xcd, (T *)h->buf[0]);
+    hipLaunchKernelGGL((h->phase == 0 ? rr3::k_step3_inplace<C, 0, LIN, false>
+                                      : rr3::k_step3_inplace<C, 1, LIN, false>),
+                       grid, block, 0, h->stream, h->D, tiles_x, h->xcd, (T *)h->buf[0]);
 }
 
 // One step from src to dst (in place: of the one buffer, whatever they are).
@@ -867,9 +869,20 @@ int rrmhd3d_create(int32_t nx, int32_t ny, int32_t nz, int32_t storage, double t
   // buffers do not fit the 256 MiB last-level cache (256^3 FP32 1114 against
   // 1153 us, 43 x 299 x 83 FP32 at 410 MB 74 against 79); buffers that do are
   // read back from it by the next step (128 x 170 x 57 FP16 at 238 MB 41
-  // against 48, 71 x 61 x 59 FP32 at 98 MB 16 against 20).  One buffer is
-  // written where it was just read and takes plain stores.
+  // against 48, 71 x 61 x 59 FP32 at 98 MB 16 against 20).
   h->nt = 2 * bytes > ((size_t)256 << 20);
+  if (h->inplace) {
+    // One buffer is written where it was just read and takes plain stores (136^3
+    // FP32 198 against 219 us, 120^3 122 / 122, 250^3 1231 / 1357).  Boxes of
+    // FP32 a little past the cache are the exception where rows are whole waves
+    // of 64 or the planes a power of two apart, streaming in workgroups of 64
+    // against plain: 64 x 160 x 160 91 / 101, 64 x 180 x 150 99 / 116, 64 x 256 x
+    // 128 130 / 158, 128^3 136 / 161, 512 x 64 x 64 140 / 162; from 64 x 200 x 150
+    // (352 MiB) to 64 x 256 x 200 level.
+    const size_t mib = bytes >> 20;
+    h->nt = elem == 4 && mib >= 256 && mib < 400 && (nx == 64 || (N & (N - 1)) == 0);
+    if (h->nt) h->linear = 64;
+  }
   int rc = RRMHD_OK;
   for (int k = 0; k < (h->inplace ? 1 : 2) && rc == RRMHD_OK; ++k)
     if (hipMalloc(&h->buf[k], bytes) != hipSuccess) rc = RRMHD_ENOMEM;
