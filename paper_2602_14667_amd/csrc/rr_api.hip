@@ -438,9 +438,15 @@ static rr::MultiPlan next_pass(const rrmhd *h, int64_t n, int phase, bool owed) 
 }
 
 static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
-  bool owed = false;
+  // a grid without a pass for n steps has none for fewer: asked once (64 x 3000
+  // FP16 5.05 -> 4.83 us per step, bound by the host when asked for each)
+  bool owed = false, single = false;
   while (n > 0) {
-    const rr::MultiPlan M = next_pass(h, n, h->phase, owed);
+    rr::MultiPlan M{};
+    if (!single) {
+      M = next_pass(h, n, h->phase, owed);
+      single = M.steps <= 1 && !h->phase;
+    }
     int64_t taken = 1;
     // random bits of the stochastic-rounding codec: keyed by the step count
     h->D.sr_key = rr::sr_step_key((uint32_t)h->steps);
