@@ -59,10 +59,9 @@ enum {
  * handle of up to 64 MiB of state keeps a second one all the same and steps
  * as a two-buffer handle does, which for such grids is the faster, while the
  * second buffers of all such handles of the process together stay within
- * 1 GiB).  Its
- * steps alternate between two forms that each write only the locations they
- * have just read: a pull of the upstream populations whose results go into
- * the slots just read for the opposite directions, then a read of the node's
+ * 1 GiB).  Its steps alternate between two forms that each write only the
+ * locations they have just read: a pull of the upstream populations whose results
+ * go into the slots just read for the opposite directions, then a read of the node's
  * own (swapped) slots with a local store, which restores the usual layout.
  * The per-node arithmetic is unchanged, so a single-buffer handle evolves
  * bit for bit as a two-buffer one; moments, diagnostics, fields and
@@ -140,12 +139,12 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b);
  * node: moments, equilibria, non-equilibrium Hermite coefficients with the
  * recursive third/fourth orders, regularised reconstruction, collision and
  * streaming (done as a pull, fused into one kernel).  A two-buffer handle
- * with its default launch takes two to five steps per pass over the state
- * where the grid has a form for it (not with stochastic rounding, the
- * closure or the equilibrium ablation); the state after n steps is bit for
- * bit that of n passes of one step.  Calls on the handle may be recorded into
- * a graph of the caller's and its replays mixed with direct calls, as with one
- * step per pass: an even number of recorded steps starts from where the last
+ * with its default launch takes two to nine steps per pass over the state
+ * where the grid has a form for it that is the faster (with stochastic
+ * rounding on small grids only; not with the closure or the equilibrium
+ * ablation); the state after n steps is bit for bit that of n passes of one
+ * step.  Calls on the handle may be recorded into a graph of the caller's and its
+ * replays mixed with direct calls, as with one step per pass: an even number of recorded steps starts from where the last
  * replay and an even number of direct steps have left the state.  From the
  * first recorded call on, passes take an odd number of steps (one step on a
  * single buffer).  Asynchronous. */
@@ -241,8 +240,8 @@ int rrmhd_load(rrmhd *h, const char *path);
 
 /* Launch shape of the one-step kernel (the tuning knob of the autotuner; the
  * default is picked from the grid).  A handle whose shape was set takes one
- * step per pass from then on.  bx x by threads per workgroup
- * (bx * by <= 256, bx >= 1, by >= 1), ry consecutive rows per thread (>= 1),
+ * step per pass from then on (until rrmhd_autotune finds passes the faster).
+ * bx x by threads per workgroup (bx * by <= 256, bx >= 1, by >= 1), ry consecutive rows per thread (>= 1),
  * xcd = 1 renumbers workgroups so each XCD gets one contiguous run of tiles,
  * xcd = 2 so each XCD gets 8 neighbouring tiles out of every 64; nt bit 0
  * writes populations with non-temporal stores, bit 1 reads them with
@@ -372,10 +371,10 @@ int rrmhd_batch_create(int n, const rrmhd_grid *grids, const double *tau_f,
 /* Equilibrium initial state of domain d (as rrmhd_init). */
 int rrmhd_batch_init(rrmhd_batch *b, int d, const double *u, const double *bf);
 /* Advance every domain n steps (all domains must have been initialised).  With
- * the default launch a pass over the ensemble takes two to five steps where
+ * the default launch a pass over the ensemble takes two to nine steps where
  * there is a form for it, bit for bit the same as one step per pass; after
  * rrmhd_batch_set_shape or _set_fetch a pass is one step of the kernel whose
- * shape and schedule they choose. */
+ * shape and schedule they choose.  Recorded calls as for rrmhd_step. */
 int rrmhd_batch_step(rrmhd_batch *b, int64_t n);
 /* *out = passes over the ensemble that rrmhd_batch_step(b, n) would take now,
  * *workgroups (may be NULL) = workgroups of the first.  Host-side only. */

@@ -472,7 +472,7 @@ __global__ void k_swapped_to_pull3(Dom3 D, const T *__restrict__ buf, T *__restr
 // Each node evaluates its own equilibria once, from factors shared by all
 // populations, and writes population p to the slot x - c_p it is pulled from
 // (the former kernel evaluated, per slot, the equilibrium of the node upstream:
-// 34 field reads and full evaluations per node).  256^3 FP32: 845 us (2406),
+// 34 field reads and full evaluations per node).  256^3 FP32: 807 us (2406),
 // bound by its writes.
 struct EqD3 {
   double f[3][3];  // f[a][c + 1]: D1Q3 factor, direction a, speed c

@@ -44,12 +44,11 @@ hipError_t launch_step(int storage, const Domain &D, const void *src, void *dst,
                        const LaunchShape &L, hipStream_t st);
 // Several steps in one pass (rr_multi.h).  steps = 0: none applies.
 struct MultiPlan {
-  int steps;  // steps per pass, 2 .. kMultiSteps
-  int tile;   // 0: marching strips; else the side of an LDS tile (16, 24, 32)
+  int steps;  // steps per pass: 2 .. 4 marching, up to 9 in tiles
+  int tile;   // 0: marching strips; else the side of an LDS tile (16, 32)
   int wx, groups_x, out, rows;  // marching: windows per workgroup, workgroups
                                 // per row, nodes per window, rows per strip
 };
-constexpr int kMultiSteps = 5;
 // for n >= 2 remaining steps; one_buffer: single steps go in place
 MultiPlan multi_plan(const Domain &D, int64_t n, bool one_buffer);
 // step: the first step's number, for the random bits of stochastic rounding.

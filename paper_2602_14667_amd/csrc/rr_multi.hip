@@ -16,10 +16,11 @@ namespace rr {
 // narrower than that).  Eight neighbouring workgroups of every 64 share an XCD.
 //
 // Bound by the vector ALU, and at sizes far past the caches by HBM as well:
-// 8192^2 FP32, 4 steps per pass, 572 us per step (117 GLUPS; 82 % of the issue
-// rate at ~240 instructions per node with 56 of 64 lanes storing, and 4.8 TB/s,
-// what a copy reaches) against 1652 us one step at a time; 4096^2 FP16 148 us
-// (90 % of the issue rate) against 222.  Counters at 8192^2: VALU busy 88 %, reads 1.25 x
+// 8192^2 FP32, 4 steps per pass, 558 us per step over 10,000 steps (120 GLUPS;
+// ~260 VALU instructions per node and step with 56 of 64 lanes storing take 510
+// at 39.3 T lane instructions/s, and 11.5 GB per pass are 5.1 TB/s, what a copy
+// reaches) against 1652 us one step at a time; 4096^2 FP16 (~290) 133 us against
+// 222.  Counters at 8192^2: VALU busy 88 %, reads 1.25 x
 // the state (a workgroup of four windows reads nine lines for the seven it stores).
 // Four steps and not more: 2 / 3 / 4 / 6 steps measured, when four took 586, 1076 / 725 / 586 /
 // 625 us per step (six lose 12 of 64 lanes to the halo); two nodes per lane
@@ -132,17 +133,17 @@ static int64_t tiles_per_cu(const Domain &D, int B, int T) {
 // round (us per step, one at a time in brackets: 64^2 FP32 7 steps 1.17 (3.12),
 // 5 steps 1.28; 96^2 6 steps 1.40 (3.20); 128^2 5 steps 1.64 (3.26); 192^2, 32 x
 // 32, 9 steps 2.01 (3.50), 5 steps 2.41; 256^2 9 steps 2.26 (3.90), 5 steps 2.73;
-// 320^2 7 steps 2.53 (4.35); FP16 within 15 % of these; 24 x 24 tiles were
+// 320^2 7 steps 2.53 (4.35); FP16 within 15 % of these; tiles of 24 x 24 were
 // between the two or level with them everywhere).  The steps to go are shared
 // out evenly among the passes.  Above that the estimates decide between 32 x
 // 32 tiles and marching strips (512^2 FP32 5.7 / 9.6 in tiles, 768^2 9.8 / 20.0,
-// 1024^2 14.9 / 30.5, 2048^2 45 / 108, 8192^2 572 / 1652 marching; FP16 1024^2
-// 15.8 / 19.6, 4096^2 148 / 222).  Short remainders stay one step at a time
+// 1024^2 13.6 / 30.2, 2048^2 45 / 108, 8192^2 558 / 1652 marching; FP16 1024^2
+// 14.4 / 19.3, 4096^2 133 / 222).  Short remainders stay one step at a time
 // where the halo costs more than the launches saved, and grids so narrow or
 // short that the estimate exceeds the one-step kernel's: two steps in tiles at
 // 256^2 measured 5.0 us per step against 3.9, three 3.9.  Narrow FP16 grids: 33 x
-// 6000 5.7 / 8.7 in tiles, 100 x 3000 6.9 / 8.4, 64 x 3000 level, 127 x 8000 one
-// step at a time 16.2 (tiles 18.3).
+// 6000 5.7 / 8.7 in tiles, 100 x 3000 6.9 / 8.4, one step at a time 64 x 3000
+// 4.7 (level) and 127 x 8000 16.2 (tiles 18.3).
 //
 // Stochastic rounding draws its bits per step, node and plane, so a pass
 // reproduces them, at about half the collision's instructions again: it takes
@@ -200,8 +201,8 @@ MultiPlan multi_plan(const Domain &D, int64_t n, bool one_buffer) {
   // five workgroups are resident per CU; up to about 12 M nodes one such round
   // with longer strips beats the estimate's choice (2500^2 FP32 62.6 against
   // 66.4 us per step, 3000^2 84.5 / 87.6, FP16 77.1 / 78.4), past that more and
-  // shorter strips even out (8192^2 FP32 549 against 567, FP16 473 / 509, 4096^2
-  // FP16 133 / 136)
+  // shorter strips even out (8192^2 FP32 3 % faster than one round, FP16 7 %,
+  // 4096^2 FP16 2 %)
   const int kmax = (int64_t)D.nx * D.ny < 12000000 ? 5 : 16;
   for (int k = 1; k <= kmax; ++k) {
     const int64_t groups_y = kCUs * k / W.groups_x > 0 ? kCUs * k / W.groups_x : 1;

@@ -1,7 +1,7 @@
 """Several steps per launch (LDS tiles and marching strips) against the one-step
 kernels, bit for bit: a handle whose launch shape was set explicitly takes one
 step per launch.  Sizes sit at the edges of the launch rule's forms: tiles of
-16, 24 and 32 nodes, one and several tiles per CU, windows and strips with
+16 and 32 nodes, one and several tiles per CU, windows and strips with
 remainders, grids narrower than a window and strips that end inside one.
 """
 import numpy as np
