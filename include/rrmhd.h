@@ -143,11 +143,12 @@ int rrmhd_init(rrmhd *h, const double *u, const double *b);
  * where the grid has a form for it that is the faster (with stochastic
  * rounding on small grids only; not with the closure or the equilibrium
  * ablation); the state after n steps is bit for bit that of n passes of one
- * step.  Calls on the handle may be recorded into a graph of the caller's and its
- * replays mixed with direct calls, as with one step per pass: an even number of recorded steps starts from where the last
- * replay and an even number of direct steps have left the state.  From the
- * first recorded call on, passes take an odd number of steps (one step on a
- * single buffer).  Asynchronous. */
+ * step.  Calls on the handle may be recorded into a graph of the caller's and
+ * its replays mixed with direct calls, as with one step per pass: an even
+ * number of recorded steps starts from where the last replay and an even
+ * number of direct steps have left the state.  From the first recorded call
+ * on, passes take an odd number of steps (one step on a single buffer).
+ * Asynchronous. */
 int rrmhd_step(rrmhd *h, int64_t n);
 /* *out = passes over the state that rrmhd_step(h, n) would take now.  Host-side
  * only. */
@@ -241,7 +242,8 @@ int rrmhd_load(rrmhd *h, const char *path);
 /* Launch shape of the one-step kernel (the tuning knob of the autotuner; the
  * default is picked from the grid).  A handle whose shape was set takes one
  * step per pass from then on (until rrmhd_autotune finds passes the faster).
- * bx x by threads per workgroup (bx * by <= 256, bx >= 1, by >= 1), ry consecutive rows per thread (>= 1),
+ * bx x by threads per workgroup (bx * by <= 256, bx >= 1, by >= 1), ry
+ * consecutive rows per thread (>= 1),
  * xcd = 1 renumbers workgroups so each XCD gets one contiguous run of tiles,
  * xcd = 2 so each XCD gets 8 neighbouring tiles out of every 64; nt bit 0
  * writes populations with non-temporal stores, bit 1 reads them with
