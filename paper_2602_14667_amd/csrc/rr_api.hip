@@ -112,6 +112,8 @@ struct rrmhd {
   bool inplace = false;  // one population buffer (alternating step phases)
   size_t bytes = 0;      // bytes of one population buffer
   int phase = 0;         // in-place: 0 pull layout, 1 swapped layout
+  int offset = 0;        // in-place: phase against the parity of the steps taken
+                         // (passes of an odd number of steps leave the phase)
   bool ready = false;
   rr::LaunchShape shape{};
   // several steps per launch where multi_plan has a form for them; off once a
@@ -169,9 +171,29 @@ static void rename_buffers(rrmhd *h) {
 // replays mix with direct calls as those of single steps do only while the
 // buffers keep their names, so from the first recorded call on a handle takes
 // an odd number of steps per pass (as many changes of buffer as its steps make
-// one by one), and single steps on one buffer.
+// one by one), and single steps on one buffer.  There the phase of a new start
+// (init, load_state, load) then is the offset that passes had left before the
+// recording, so that it goes with the parity of the steps as it did then.
 static void note_recording(rrmhd *h) {
   if (!h->recorded) h->recorded = rr_stream_captured(h->stream);
+}
+
+// A new state is written in the pull layout into start_buffer, then installed.
+// With an offset to keep (which only passes leave, so there is a second buffer)
+// that is the second one, and the exchange of the layouts fills the first.
+static void *start_buffer(const rrmhd *h) {
+  return h->buf[h->inplace && h->recorded && h->offset ? 1 : 0];
+}
+static int started(rrmhd *h, int64_t steps) {
+  if (!h->recorded) h->offset = 0;
+  if (start_buffer(h) != h->buf[0])
+    HIP_OR_RETURN(rr::launch_swapped_to_pull(h->storage, h->D, h->buf[1], h->buf[0], h->D.plane,
+                                             h->D.row, h->stream));
+  h->cur = 0;
+  h->phase = h->offset;
+  h->steps = steps;
+  h->ready = true;
+  return RRMHD_OK;
 }
 
 // The default launch shape, several steps per launch where a form applies.
@@ -413,26 +435,23 @@ int rrmhd_set_equilibrium(rrmhd *h, int kind) {
 int rrmhd_init(rrmhd *h, const double *u, const double *b) {
   if (!h || !u || !b) return RRMHD_EINVAL;
   note_recording(h);
+  // the first allocation again: a run after another then starts in the buffer
+  // that the caches hold (576 x 136, init + 13 steps + moments 49 us, in the other
+  // one 52)
+  if (h->swapped && !h->recorded) rename_buffers(h);
   HIP_OR_RETURN(rr::launch_init(h->storage, h->D, u, b, h->bc.b_wall[0],
-                                h->bc.b_wall[1], h->buf[0], h->stream));
-  h->cur = 0;
-  h->phase = 0;
-  h->steps = 0;
-  h->ready = true;
-  return RRMHD_OK;
+                                h->bc.b_wall[1], start_buffer(h), h->stream));
+  return started(h, 0);
 }
 
-// The next pass with n steps to go from a phase (steps <= 1: one step).  owed: on
-// one buffer an odd number of steps has been taken in passes, which leave the
-// phase alone.
-static rr::MultiPlan next_pass(const rrmhd *h, int64_t n, int phase, bool owed) {
+// The next pass with n steps to go from a phase (steps <= 1: one step).
+static rr::MultiPlan next_pass(const rrmhd *h, int64_t n, int phase) {
   rr::MultiPlan M{};
   if (!h->multi || h->closure_on || phase) return M;
   // a small single-buffer handle (kSmallState) takes the passes of a
   // two-buffer one from its usual layout; its graphs keep to the phases
   if (h->inplace && (!h->buf[1] || h->graph_chunk > 0 || h->recorded)) return M;
-  // one buffer: an odd total leaves its last step to the phases
-  M = rr::multi_plan(h->D, h->inplace ? n - ((n + owed) & 1) : n, h->inplace);
+  M = rr::multi_plan(h->D, n, h->inplace);
   if (h->recorded && M.steps > 0 && M.steps % 2 == 0) M.steps -= 1;
   return M;
 }
@@ -440,17 +459,17 @@ static rr::MultiPlan next_pass(const rrmhd *h, int64_t n, int phase, bool owed) 
 static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
   // a grid without a pass for n steps has none for fewer: asked once (64 x 3000
   // FP16 5.05 -> 4.83 us per step, bound by the host when asked for each)
-  bool owed = false, single = false;
+  bool single = false;
   while (n > 0) {
     rr::MultiPlan M{};
     if (!single) {
-      M = next_pass(h, n, h->phase, owed);
+      M = next_pass(h, n, h->phase);
       single = M.steps <= 1 && !h->phase;
     }
     int64_t taken = 1;
     // random bits of the stochastic-rounding codec: keyed by the step count
     h->D.sr_key = rr::sr_step_key((uint32_t)h->steps);
-    if (h->inplace && M.steps <= 1 && !owed) {
+    if (h->inplace && M.steps <= 1) {
       HIP_OR_RETURN(rr::launch_step_inplace(h->storage, h->D, h->buf[0], h->phase, h->shape, st));
       h->phase ^= 1;
     } else {
@@ -465,13 +484,13 @@ static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
         taken = M.steps;
       } else {
         HIP_OR_RETURN(rr::launch_step(h->storage, h->D, h->buf[h->cur], h->buf[h->cur ^ 1],
-                                      h->inplace ? rr::default_shape(h->D) : h->shape, st));
+                                      h->shape, st));
       }
       if (!h->inplace && (taken & 1))
         h->cur ^= 1;
       else
         rename_buffers(h);
-      owed ^= h->inplace && (taken & 1);
+      if (h->inplace) h->offset ^= (int)(taken & 1);
     }
     h->steps += taken;
     n -= taken;
@@ -536,12 +555,9 @@ int rrmhd_step_passes(const rrmhd *h, int64_t n, int64_t *out) {
   int64_t passes = 0;
   int phase = h->phase;
   auto run = [&](int64_t m) {
-    for (bool owed = false; m > 0; ++passes) {
-      const int T = next_pass(h, m, phase, owed).steps;
-      if (h->inplace && T <= 1 && !owed)
-        phase ^= 1;
-      else
-        owed ^= h->inplace && (T <= 1 || T % 2);
+    for (; m > 0; ++passes) {
+      const int T = next_pass(h, m, phase).steps;
+      if (h->inplace && T <= 1) phase ^= 1;
       m -= T > 1 ? T : 1;
     }
   };
@@ -702,7 +718,8 @@ int rrmhd_save_state(rrmhd *h, void *dst, int64_t bytes) {
   if (!h->ready) return RRMHD_ESTATE;
   note_recording(h);
   if (h->inplace && h->phase) {
-    HIP_OR_RETURN(rr::launch_swapped_to_pull(h->storage, h->D, h->buf[h->cur], dst, h->stream));
+    HIP_OR_RETURN(rr::launch_swapped_to_pull(h->storage, h->D, h->buf[0], dst,
+                                             (int64_t)h->D.nx * h->D.ny, h->D.nx, h->stream));
     return RRMHD_OK;
   }
   HIP_OR_RETURN(copy_planes(h, dst, (const char *)h->buf[h->cur], false));
@@ -712,12 +729,8 @@ int rrmhd_save_state(rrmhd *h, void *dst, int64_t bytes) {
 int rrmhd_load_state(rrmhd *h, const void *src, int64_t bytes, int64_t step_count) {
   if (!h || !src || bytes < rrmhd_state_bytes(h) || step_count < 0) return RRMHD_EINVAL;
   note_recording(h);
-  HIP_OR_RETURN(copy_planes(h, const_cast<void *>(src), h->buf[0], true));
-  h->cur = 0;
-  h->phase = 0;
-  h->steps = step_count;
-  h->ready = true;
-  return RRMHD_OK;
+  HIP_OR_RETURN(copy_planes(h, const_cast<void *>(src), start_buffer(h), true));
+  return started(h, step_count);
 }
 
 }  // extern "C"
@@ -856,7 +869,8 @@ int rrmhd_save(rrmhd *h, const char *path) {
   if (h->inplace && h->phase) {
     // between the two step forms: gather the swapped layout first
     HIP_OR_RETURN(hipMalloc(&tmp, row * rr::kStatePlanes));
-    hipError_t e = rr::launch_swapped_to_pull(h->storage, h->D, h->buf[h->cur], tmp, h->stream);
+    hipError_t e = rr::launch_swapped_to_pull(h->storage, h->D, h->buf[0], tmp,
+                                              (int64_t)h->D.nx * h->D.ny, h->D.nx, h->stream);
     if (e != hipSuccess) {
       (void)hipFree(tmp);
       return dev_err(e, "launch_swapped_to_pull");
@@ -900,7 +914,8 @@ int rrmhd_load(rrmhd *h, const char *path) {
   }
   bool touched = false;
   if (rc == RRMHD_OK)
-    rc = rr_ck_read_planes(f, path, sizeof hd, (char *)h->buf[0], (size_t)h->D.plane * h->elem,
+    rc = rr_ck_read_planes(f, path, sizeof hd, (char *)start_buffer(h),
+                           (size_t)h->D.plane * h->elem,
                            (size_t)h->D.nx * h->D.ny * h->elem, rr::kStatePlanes, &touched,
                            h->D.row != h->D.nx ? (size_t)h->D.row * h->elem : 0,
                            h->D.row != h->D.nx ? h->D.ny : 1);
@@ -909,11 +924,7 @@ int rrmhd_load(rrmhd *h, const char *path) {
     if (touched) h->ready = false;  // part of the state was overwritten
     return rc;
   }
-  h->cur = 0;
-  h->phase = 0;
-  h->steps = hd.steps;
-  h->ready = true;
-  return RRMHD_OK;
+  return started(h, hd.steps);
 }
 
 int rr_handle_info(const rrmhd *h, int *nx, int *ny, int *storage, hipStream_t *stream,
@@ -942,7 +953,7 @@ void rr_handle_set_multi(rrmhd *h) {
 }
 
 int rr_handle_pass_steps(const rrmhd *h, int64_t n) {
-  const int T = next_pass(h, n, h->phase, false).steps;
+  const int T = next_pass(h, n, h->phase).steps;
   return T > 1 ? T : 1;
 }
 

@@ -73,10 +73,11 @@ hipError_t launch_diagnostics(int storage, const Domain &D, const void *src,
 // into the opposite slots; 1: read own swapped slots, store locally) on buf.
 hipError_t launch_step_inplace(int storage, const Domain &D, void *buf, int phase,
                                const LaunchShape &L, hipStream_t st);
-// The swapped layout of buf rewritten in the pull layout into dst (dense
-// planes of nx * ny elements).
+// The swapped layout of buf rewritten in the pull layout into dst, with planes
+// `plane` and rows `row` elements apart (dense: nx * ny and nx); or the pull
+// layout in the swapped one.
 hipError_t launch_swapped_to_pull(int storage, const Domain &D, const void *buf, void *dst,
-                                  hipStream_t st);
+                                  int64_t plane, int64_t row, hipStream_t st);
 
 LaunchShape default_shape(const Domain &D);
 

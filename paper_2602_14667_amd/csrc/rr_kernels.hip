@@ -204,14 +204,16 @@ __global__ __launch_bounds__(256) void k_step_inplace(Domain D, int tiles_x, int
   }
 }
 
-// Swapped layout -> pull layout, into a dense copy (planes of nx * ny):
-// dst[i][x] = f*_i(x), found at buf[opp(i)][x + c_i], or in the node's own
-// slot i when x + c_i lies beyond a wall.
+// Swapped layout -> pull layout, into a copy with planes `plane` and rows `row`
+// elements apart: dst[i][x] = f*_i(x), found at buf[opp(i)][x + c_i], or in the
+// node's own slot i when x + c_i lies beyond a wall.  The exchange is its own
+// inverse, so it takes the pull layout to the swapped one as well.
 template <class T>
-__global__ void k_swapped_to_pull(Domain D, const T *__restrict__ buf, T *__restrict__ dst) {
+__global__ void k_swapped_to_pull(Domain D, const T *__restrict__ buf, T *__restrict__ dst,
+                                  int64_t plane, int64_t row) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y;
   if (x >= D.nx) return;
-  const int64_t N = (int64_t)D.nx * D.ny, o = (int64_t)y * D.nx + x;
+  const int64_t o = (int64_t)y * row + x;
   const int64_t ob = (int64_t)y * D.row + x;
   auto src_of = [&](int p, int op, int cxv, int cyv) -> T {
     int tx = x + cxv, ty = y + cyv;
@@ -220,10 +222,11 @@ __global__ void k_swapped_to_pull(Domain D, const T *__restrict__ buf, T *__rest
     ty = ty < 0 ? ty + D.ny : (ty >= D.ny ? ty - D.ny : ty);
     return buf[(int64_t)op * D.plane + (int64_t)ty * D.row + tx];
   };
-  for (int i = 0; i < kQ; ++i) dst[(int64_t)i * N + o] = src_of(i, opp_f(i), cx(i), cy(i));
+  for (int i = 0; i < kQ; ++i) dst[(int64_t)i * plane + o] = src_of(i, opp_f(i), cx(i), cy(i));
   for (int j = 0; j < kQm; ++j)
     for (int c = 0; c < 2; ++c)
-      dst[(int64_t)gplane(j, c) * N + o] = src_of(gplane(j, c), gplane(opp_g(j), c), ex(j), ey(j));
+      dst[(int64_t)gplane(j, c) * plane + o] =
+          src_of(gplane(j, c), gplane(opp_g(j), c), ex(j), ey(j));
 }
 
 // ---------------------------------------------------------------------------
@@ -1049,14 +1052,14 @@ hipError_t launch_step_inplace(int storage, const Domain &D, void *buf, int phas
 }
 
 hipError_t launch_swapped_to_pull(int storage, const Domain &D, const void *buf, void *dst,
-                                  hipStream_t st) {
+                                  int64_t plane, int64_t row, hipStream_t st) {
   const dim3 block(64), grid((D.nx + 63) / 64, D.ny);
   if (storage == kF16)
     hipLaunchKernelGGL(k_swapped_to_pull<uint16_t>, grid, block, 0, st, D,
-                       (const uint16_t *)buf, (uint16_t *)dst);
+                       (const uint16_t *)buf, (uint16_t *)dst, plane, row);
   else
     hipLaunchKernelGGL(k_swapped_to_pull<float>, grid, block, 0, st, D, (const float *)buf,
-                       (float *)dst);
+                       (float *)dst, plane, row);
   return hipGetLastError();
 }
 
