@@ -468,7 +468,7 @@ static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
     }
     int64_t taken = 1;
     // random bits of the stochastic-rounding codec: keyed by the step count
-    h->D.sr_key = rr::sr_step_key((uint32_t)h->steps);
+    h->D.sr_key = M.steps > 1 ? (uint32_t)h->steps : rr::sr_step_key((uint32_t)h->steps);
     if (h->inplace && M.steps <= 1) {
       HIP_OR_RETURN(rr::launch_step_inplace(h->storage, h->D, h->buf[0], h->phase, h->shape, st));
       h->phase ^= 1;
@@ -479,8 +479,7 @@ static int plain_steps(rrmhd *h, int64_t n, hipStream_t st) {
                                               h->buf[h->cur], h->buf[h->cur ^ 1],
                                               h->closure_grid, st));
       } else if (M.steps > 1) {
-        HIP_OR_RETURN(rr::launch_multi(M, h->storage, h->D, (uint32_t)h->steps, h->buf[h->cur],
-                                       h->buf[h->cur ^ 1], st));
+        HIP_OR_RETURN(rr::launch_multi(M, h->storage, h->D, h->buf[h->cur], h->buf[h->cur ^ 1], st));
         taken = M.steps;
       } else {
         HIP_OR_RETURN(rr::launch_step(h->storage, h->D, h->buf[h->cur], h->buf[h->cur ^ 1],

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(B *B) void k_batch_tiles(const BatchDom *__restrict
   D.s = s;
   D.inv_s = inv_s;
   const int t = (int)blockIdx.x - W.wg_first, ty = t / W.mt_x, tx = t - ty * W.mt_x;
-  tile_steps<C, B, false, false>(D, ex, tx, ty, T, 0u, src + W.base, dst + W.base);
+  tile_steps<C, B, false, false>(D, ex, tx, ty, T, src + W.base, dst + W.base);
 }
 
 }  // namespace rr

@@ -24,11 +24,13 @@ struct Domain {
   int feq;           // 0: the algorithm's equilibrium; 1: with the u.M
                      // cross terms of the third and fourth orders (ablation)
   int sr = 0;             // FP16 storage written with stochastic rounding
-  uint32_t sr_key = 0;    // its per-step key (set before each step)
+  uint32_t sr_key = 0;    // its per-step key (set before each step); for a pass of
+                          // several steps the first step's number
 };
 // Every one-step kernel takes a Domain by value: eight more bytes (a member for
 // the passes of several steps) cost each launch 0.2 to 0.3 us (400^2 FP32 7.17 ->
-// 7.44 us per step, 300 x 290 4.21 -> 4.43).
+// 7.44 us per step, 300 x 290 4.21 -> 4.43), and an argument of the tile passes
+// beside it 0.3 us of theirs (256^2 8 steps 17.7 -> 18.0).
 static_assert(sizeof(Domain) == 80, "launch cost of the one-step kernels");
 
 struct LaunchShape {
@@ -51,9 +53,8 @@ struct MultiPlan {
 };
 // for n >= 2 remaining steps; one_buffer: single steps go in place
 MultiPlan multi_plan(const Domain &D, int64_t n, bool one_buffer);
-// step: the first step's number, for the random bits of stochastic rounding.
-hipError_t launch_multi(const MultiPlan &M, int storage, const Domain &D, uint32_t step,
-                        const void *src, void *dst, hipStream_t st);
+hipError_t launch_multi(const MultiPlan &M, int storage, const Domain &D, const void *src,
+                        void *dst, hipStream_t st);
 
 hipError_t launch_init(int storage, const Domain &D, const double *u,
                        const double *b, double bwx, double bwy, void *dst,

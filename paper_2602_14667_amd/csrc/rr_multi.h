@@ -202,12 +202,11 @@ constexpr int kMoving = moving_slot(kPlanes);
 // pulls from memory, the later ones from the neighbours through LDS (two
 // buffers, so one barrier per step).  After T steps the inner B - 2 (T - 1)
 // square is valid and stored; tile (tx, ty) stores the square at (tx, ty) times
-// that side.  step: the first step's number (random bits).  With walls the tiles cover [0, ny) in y, threads beyond a wall
+// that side.  With walls the tiles cover [0, ny) in y, threads beyond a wall
 // idle, and bounce-back reads the node's own values as the one-step kernel does.
 template <class C, int B, bool WALLS, bool FORCED>
 __device__ __forceinline__ void tile_steps(const Domain &D, float (&ex)[2][kMoving][B * B], int tx,
-                                           int ty, int T, uint32_t step,
-                                           const typename C::T *__restrict__ src,
+                                           int ty, int T, const typename C::T *__restrict__ src,
                                            typename C::T *__restrict__ dst) {
   constexpr int N = B * B;
   const int halo = T - 1, out = B - 2 * halo;
@@ -226,7 +225,8 @@ __device__ __forceinline__ void tile_steps(const Domain &D, float (&ex)[2][kMovi
   }
   const bool lo = WALLS && y == 0, hi = WALLS && y == D.ny - 1;
   const CollideParams P{D.om_c, D.omm_c, D.Gx, D.Gy, D.src_c};
-  PlaneGeom G{D.plane, D.nx, D.ny, D.s, D.inv_s, D.sr_key, D.row};
+  PlaneGeom G{D.plane, D.nx, D.ny, D.s, D.inv_s, 0u, D.row};
+  if constexpr (codec_sr<C>::value) G.sr_key = sr_step_key(D.sr_key);
   float v[kPlanes];
   float(&d)[kQ] = *reinterpret_cast<float(*)[kQ]>(v);
   float(&g)[2 * kQm] = *reinterpret_cast<float(*)[2 * kQm]>(v + kQ);
@@ -240,7 +240,7 @@ __device__ __forceinline__ void tile_steps(const Domain &D, float (&ex)[2][kMovi
     if (s == T) break;
     float(&b)[kMoving][N] = ex[s & 1];
     const uint32_t seed = node_seed<C>(G, x, y);
-    if constexpr (codec_sr<C>::value) G.sr_key = sr_step_key(step + s);  // of the next step
+    if constexpr (codec_sr<C>::value) G.sr_key = sr_step_key(D.sr_key + s);  // of the next step
 #pragma unroll
     for (int p = 0; p < kPlanes; ++p) {
       v[p] = through_storage<C>(v[p], D.s, D.inv_s, seed, p);

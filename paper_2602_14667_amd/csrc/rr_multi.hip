@@ -44,12 +44,12 @@ __global__ __launch_bounds__(256) void k_march(PlaneGeom G, CollideParams P, int
 
 // ---- tiles with LDS exchange ---------------------------------------------------
 template <class C, int B, bool WALLS, bool FORCED>
-__global__ __launch_bounds__(B *B) void k_tile_steps(Domain D, int tiles_x, int T, uint32_t step,
+__global__ __launch_bounds__(B *B) void k_tile_steps(Domain D, int tiles_x, int T,
                                                      const typename C::T *__restrict__ src,
                                                      typename C::T *__restrict__ dst) {
   __shared__ float ex[2][kMoving][B * B];
   const int ty = blockIdx.x / tiles_x, tx = blockIdx.x - ty * tiles_x;
-  tile_steps<C, B, WALLS, FORCED>(D, ex, tx, ty, T, step, src, dst);
+  tile_steps<C, B, WALLS, FORCED>(D, ex, tx, ty, T, src, dst);
 }
 
 // ---- launch rules ------------------------------------------------------------------
@@ -73,7 +73,7 @@ static void march_t(const MultiPlan &M, const Domain &D, const void *src, void *
 }
 
 template <class C, int B>
-static void tile_b(const MultiPlan &M, const Domain &D, uint32_t step, const void *src, void *dst,
+static void tile_b(const MultiPlan &M, const Domain &D, const void *src, void *dst,
                    hipStream_t st) {
   using T = typename C::T;
   const int out = B - 2 * (M.steps - 1);
@@ -83,24 +83,24 @@ static void tile_b(const MultiPlan &M, const Domain &D, uint32_t step, const voi
   auto s = (const T *)src;
   auto d = (T *)dst;
   if (D.walls && forced)
-    hipLaunchKernelGGL((k_tile_steps<C, B, true, true>), grid, block, 0, st, D, tiles_x, M.steps, step, s, d);
+    hipLaunchKernelGGL((k_tile_steps<C, B, true, true>), grid, block, 0, st, D, tiles_x, M.steps, s, d);
   else if (D.walls)
-    hipLaunchKernelGGL((k_tile_steps<C, B, true, false>), grid, block, 0, st, D, tiles_x, M.steps, step, s, d);
+    hipLaunchKernelGGL((k_tile_steps<C, B, true, false>), grid, block, 0, st, D, tiles_x, M.steps, s, d);
   else if (forced)
-    hipLaunchKernelGGL((k_tile_steps<C, B, false, true>), grid, block, 0, st, D, tiles_x, M.steps, step, s, d);
+    hipLaunchKernelGGL((k_tile_steps<C, B, false, true>), grid, block, 0, st, D, tiles_x, M.steps, s, d);
   else
-    hipLaunchKernelGGL((k_tile_steps<C, B, false, false>), grid, block, 0, st, D, tiles_x, M.steps, step, s, d);
+    hipLaunchKernelGGL((k_tile_steps<C, B, false, false>), grid, block, 0, st, D, tiles_x, M.steps, s, d);
 }
 
 template <class C>
-static void multi_t(const MultiPlan &M, const Domain &D, uint32_t step, const void *src, void *dst,
+static void multi_t(const MultiPlan &M, const Domain &D, const void *src, void *dst,
                     hipStream_t st) {
   if (M.tile == 0)
     march_t<C>(M, D, src, dst, st);
   else if (M.tile == 16)
-    tile_b<C, 16>(M, D, step, src, dst, st);
+    tile_b<C, 16>(M, D, src, dst, st);
   else
-    tile_b<C, 32>(M, D, step, src, dst, st);
+    tile_b<C, 32>(M, D, src, dst, st);
 }
 
 // The estimate of single_us for this grid.  The rate (bytes per us) of a state
@@ -221,18 +221,18 @@ MultiPlan multi_plan(const Domain &D, int64_t n, bool one_buffer) {
   return W;
 }
 
-hipError_t launch_multi(const MultiPlan &M, int storage, const Domain &D, uint32_t step,
-                        const void *src, void *dst, hipStream_t st) {
+hipError_t launch_multi(const MultiPlan &M, int storage, const Domain &D, const void *src,
+                        void *dst, hipStream_t st) {
   if (storage == kF16 && D.sr && M.tile == 16)
-    tile_b<CodecF16SR, 16>(M, D, step, src, dst, st);
+    tile_b<CodecF16SR, 16>(M, D, src, dst, st);
   else if (storage == kF16 && D.sr)
-    tile_b<CodecF16SR, 32>(M, D, step, src, dst, st);
+    tile_b<CodecF16SR, 32>(M, D, src, dst, st);
   else if (storage != kF16)
-    multi_t<CodecF32>(M, D, step, src, dst, st);
+    multi_t<CodecF32>(M, D, src, dst, st);
   else if (D.s == 1.0f)
-    multi_t<CodecF16U>(M, D, step, src, dst, st);
+    multi_t<CodecF16U>(M, D, src, dst, st);
   else
-    multi_t<CodecF16>(M, D, step, src, dst, st);
+    multi_t<CodecF16>(M, D, src, dst, st);
   return hipGetLastError();
 }
 
